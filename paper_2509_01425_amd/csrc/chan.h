@@ -53,13 +53,13 @@ struct DevRing {
 
 enum : uint32_t { kModeSpsc = 0, kModeMpscLock = 1, kModeMpscNoLock = 2 };
 
-// One consumer unit (one workgroup).  kModeMpscLock: a member of the team
+// One consumer unit.  kModeMpscLock: a member (one workgroup) of the team
 // that consumes the shared ring of a locking MPSC channel (K producers told
 // apart by the entry's producer tag); the team shares a claim counter and a
 // round table (rounds[k] = end + 1 of round k once defined, 0 before).
 // kModeSpsc: n_rings independent rings, each with exactly one producer stream
 // (SPSC rings and non-locking MPSC sub-rings, possibly of different
-// channels); ring q belongs to stream stream_of_prod[prod_stream_base + q].
+// channels), consumed by one wave or one workgroup; ring q belongs to stream stream_of_prod[prod_stream_base + q].
 struct DevChannel {
   uint32_t mode;
   uint32_t n_rings;
@@ -88,8 +88,17 @@ struct DevStream {
   uint64_t src_bytes;  // size of the source slot
 };
 
-// Per-workgroup role: kind 0 = up to four producer waves (ids = streams),
-// kind 1 = one consumer unit (ids[0] = unit).
+// Per-workgroup role: up to four waves that are producers (ids = streams) or
+// consumers (ids = units) on their own, or a whole workgroup as the producer
+// of stream ids[0], the consumer of unit ids[0] or a locking team's member
+// (unit ids[0]).
+enum : uint32_t {
+  kRoleProducerWaves = 0,
+  kRoleProducerGroup = 1,
+  kRoleConsumerWaves = 2,
+  kRoleConsumerGroup = 3,
+  kRoleLockMember = 4,
+};
 struct DevRole {
   uint32_t kind;
   uint32_t count;

@@ -11,12 +11,13 @@
 // pump_kernel.
 #include <algorithm>
 #include <cstring>
-#include <map>
+#include <numeric>
 #include <queue>
 #include <utility>
 #include <vector>
 
 #include "chan.h"
+#include "pump_plan.h"
 #include "residency.h"
 #include "runtime.h"
 
@@ -41,6 +42,10 @@ struct hicr_channel_s {
   // this is the ring's message counter when the next pump starts.
   std::vector<uint64_t> dev_msgs;
   bool user_kernels = false;  // handed to caller kernels (hicr_device.h)
+  // While a pump is being set up: the channel's number in it (-1: not in it)
+  // and every producer's stream (kNoStream: none).
+  int64_t pump_idx = -1;
+  std::vector<uint32_t> pump_stream;
   struct RingHost {
     uint64_t tm = 0, tb = 0;  // producer side: enqueued
     uint64_t hm = 0, hb = 0;  // consumer side: released
@@ -50,6 +55,8 @@ struct hicr_channel_s {
 };
 
 namespace {
+
+constexpr uint32_t kNoStream = ~0u;
 
 uint64_t entry_size(uint64_t e) { return e & kEntrySizeMask; }
 
@@ -64,7 +71,7 @@ int check_hbm_slot(hicr_ctx c, hicr_slot s, uint64_t need, const char *what) {
 }
 
 bool registered(hicr_ctx c, hicr_channel ch) {
-  return std::find(c->channels.begin(), c->channels.end(), ch) != c->channels.end();
+  return c->channels.count(ch) != 0;
 }
 
 // A device buffer [p, p + bytes) must lie inside one allocation of the device.
@@ -212,7 +219,7 @@ int hicr_channel_create(hicr_ctx c, const hicr_channel_cfg *cfg, hicr_channel *o
       free_channel(ch);
       return fail(c, HICR_ENOMEM, "coordination counters: %s", hipGetErrorString(e));
     }
-    c->channels.push_back(ch);
+    c->channels.insert(ch);
     *out = ch;
     return HICR_OK;
   });
@@ -226,7 +233,7 @@ int hicr_channel_destroy(hicr_channel ch) {
     if (!registered(c, ch)) return HICR_EINVAL;
     (void)hipSetDevice(c->device);
     int rc = wait_all(c);
-    c->channels.erase(std::find(c->channels.begin(), c->channels.end(), ch));
+    c->channels.erase(ch);
     free_channel(ch);
     return rc;
   });
@@ -408,10 +415,15 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
                 uint64_t timeout_ns, hipStream_t s, Extra *xout, bool dev_tables) {
   const uint32_t n = (uint32_t)st.size();
   if (n_msgs && (!msg_off || !msg_size)) return fail(c, HICR_EINVAL, "message arrays missing");
-  // channels in order of first appearance
+  // channels in order of first appearance; the marks this leaves in them are
+  // taken back however the call ends
   std::vector<hicr_channel> chans;
-  std::map<hicr_channel, uint32_t> chan_idx;
-  std::map<std::pair<hicr_channel, uint32_t>, uint32_t> prod_stream;
+  struct Unmark {
+    std::vector<hicr_channel> &chans;
+    ~Unmark() {
+      for (hicr_channel ch : chans) ch->pump_idx = -1;
+    }
+  } unmark{chans};
   for (uint32_t i = 0; i < n; i++) {
     hicr_channel ch = st[i].channel;
     if (!ch || !registered(c, ch)) return fail(c, HICR_EINVAL, "stream %u: unknown channel", i);
@@ -421,12 +433,14 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
     if (ch->user_kernels)
       return fail(c, HICR_EINVAL, "stream %u: channel belongs to user kernels", i);
     if (st[i].producer >= ch->cfg.producers) return fail(c, HICR_EINVAL, "stream %u: producer", i);
-    if (!prod_stream.emplace(std::make_pair(ch, st[i].producer), i).second)
-      return fail(c, HICR_EINVAL, "stream %u: producer already has a stream", i);
-    if (!chan_idx.count(ch)) {
-      chan_idx[ch] = (uint32_t)chans.size();
+    if (ch->pump_idx < 0) {
+      ch->pump_stream.assign(ch->cfg.producers, kNoStream);
       chans.push_back(ch);
+      ch->pump_idx = (int64_t)chans.size() - 1;
     }
+    if (ch->pump_stream[st[i].producer] != kNoStream)
+      return fail(c, HICR_EINVAL, "stream %u: producer already has a stream", i);
+    ch->pump_stream[st[i].producer] = i;
     if (st[i].first_msg > n_msgs || st[i].n_msgs > n_msgs - st[i].first_msg)
       return fail(c, HICR_ERANGE, "stream %u: messages outside the arrays", i);
     if (dev_tables) {
@@ -451,12 +465,11 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
                   (unsigned long long)total);
   }
   if (n == 0) return HICR_OK;
-  // Consumer units.  A locking MPSC channel's shared ring is one unit (one
-  // consumer, one total order).  Every other ring -- an SPSC channel's ring or
-  // a non-locking MPSC producer's sub-ring -- has exactly one producer and is
-  // consumed on its own; such rings are spread over as many consumer
-  // workgroups as the device still holds, balanced by bytes (longest first),
-  // so one channel's producers do not all wait on one workgroup.
+  // Endpoints.  A locking MPSC channel's shared ring (one total order) is
+  // drained by a team of workgroups.  Every other ring -- an SPSC channel's
+  // ring or a non-locking MPSC producer's sub-ring -- has exactly one producer
+  // and is consumed on its own.  pump_plan.h says which endpoints are
+  // workgroups and which are waves, four to a workgroup.
   const uint32_t prod_wgs = (n + 3) / 4;
   const uint64_t cap = (uint64_t)c->n_cu * (uint64_t)c->pump_occ;
   // bytes per stream; with device tables the host balances by message count
@@ -474,11 +487,10 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   uint64_t trace_total = 0;
   for (uint32_t k = 0; k < chans.size(); k++) {
     chan_trace[k] = trace_total;
-    for (uint32_t p = 0; p < chans[k]->cfg.producers; p++) {
-      auto it = prod_stream.find(std::make_pair(chans[k], p));
-      if (it == prod_stream.end()) continue;
-      stream_trace[it->second] = trace_total;  // independent rings: producer after producer
-      trace_total += st[it->second].n_msgs;
+    for (uint32_t sid : chans[k]->pump_stream) {
+      if (sid == kNoStream) continue;
+      stream_trace[sid] = trace_total;  // independent rings: producer after producer
+      trace_total += st[sid].n_msgs;
     }
   }
   std::vector<uint32_t> indep;  // streams whose ring is consumed on its own
@@ -486,57 +498,52 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   std::vector<uint32_t> lock_chans;
   uint64_t all_bytes = 0;
   for (uint32_t k = 0; k < chans.size(); k++) {
-    for (uint32_t p = 0; p < chans[k]->cfg.producers; p++) {
-      auto it = prod_stream.find(std::make_pair(chans[k], p));
-      if (it == prod_stream.end()) continue;
-      chan_bytes[k] += stream_bytes[it->second];
-      chan_msgs[k] += st[it->second].n_msgs;
-      if (chans[k]->cfg.mode != HICR_CH_MPSC_LOCK) indep.push_back(it->second);
+    for (uint32_t sid : chans[k]->pump_stream) {
+      if (sid == kNoStream) continue;
+      chan_bytes[k] += stream_bytes[sid];
+      chan_msgs[k] += st[sid].n_msgs;
+      if (chans[k]->cfg.mode != HICR_CH_MPSC_LOCK) indep.push_back(sid);
     }
     all_bytes += chan_bytes[k];
     if (chans[k]->cfg.mode == HICR_CH_MPSC_LOCK) lock_chans.push_back(k);
   }
-  const uint64_t min_units = (indep.size() + kMaxProducers - 1) / kMaxProducers;
-  if ((uint64_t)prod_wgs + lock_chans.size() + min_units > cap)
-    return fail(c, HICR_EINVAL, "%llu workgroups do not fit the device at once (%d x %d)",
-                (unsigned long long)(prod_wgs + lock_chans.size() + min_units), c->n_cu,
-                c->pump_occ);
   // A locking MPSC ring is drained by a team sized to its share of the bytes
-  // (every consumer workgroup should carry about the same), at most
-  // kMaxTeam, and trimmed while the single-producer rings would not fit.
-  const uint64_t budget = cap - prod_wgs;
-  const uint64_t per_unit = std::max<uint64_t>(1, all_bytes / std::max<uint64_t>(1, budget));
-  std::map<uint32_t, uint32_t> team;
-  uint64_t team_total = 0;
-  for (uint32_t k : lock_chans) {
-    const uint64_t t = std::min<uint64_t>(kMaxTeam, std::max<uint64_t>(1, (chan_bytes[k] + per_unit - 1) / per_unit));
-    team[k] = (uint32_t)t;
-    team_total += t;
-  }
-  while (team_total + min_units > budget) {
-    uint32_t big = lock_chans[0];
-    for (uint32_t k : lock_chans)
-      if (team[k] > team[big]) big = k;
-    team[big]--;  // the fit check above guarantees one member per channel fits
-    team_total--;
-  }
-  const uint32_t n_indep_units =
-      (uint32_t)std::min<uint64_t>(indep.size(), budget - team_total);
-  // longest first onto the least loaded unit (at most kMaxProducers rings each)
-  std::vector<std::vector<uint32_t>> unit_streams(n_indep_units);
-  {
-    std::vector<uint32_t> order = indep;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t x, uint32_t y) { return stream_bytes[x] > stream_bytes[y]; });
+  // (every consumer workgroup should carry about the same), at most kMaxTeam.
+  const uint64_t budget = cap > prod_wgs ? cap - prod_wgs : 1;
+  const uint64_t per_unit = std::max<uint64_t>(1, all_bytes / budget);
+  std::vector<uint64_t> want;
+  for (uint32_t k : lock_chans)
+    want.push_back(std::min<uint64_t>(kMaxTeam, (chan_bytes[k] + per_unit - 1) / per_unit));
+  const PumpPlan plan = plan_endpoints(cap, n - indep.size(), indep.size(), want, kMaxProducers);
+  if (!plan.fits)
+    return fail(c, HICR_EINVAL, "%llu workgroups do not fit the device at once (%d x %d)",
+                (unsigned long long)plan.need, c->n_cu, c->pump_occ);
+  const uint32_t n_indep_units = (uint32_t)plan.ind_units;
+  std::vector<uint32_t> team(chans.size(), 0);  // members (locking channels)
+  for (size_t t = 0; t < lock_chans.size(); t++) team[lock_chans[t]] = plan.team[t];
+  // longest first onto the least loaded unit (at most kMaxProducers rings
+  // each): unit u consumes unit_streams[unit_begin[u] .. unit_begin[u + 1])
+  std::vector<uint32_t> unit_streams = indep, unit_begin(n_indep_units + 1, 0);
+  std::stable_sort(unit_streams.begin(), unit_streams.end(),
+                   [&](uint32_t x, uint32_t y) { return stream_bytes[x] > stream_bytes[y]; });
+  if (n_indep_units == indep.size()) {
+    std::iota(unit_begin.begin(), unit_begin.end(), 0u);
+  } else {
+    std::vector<std::vector<uint32_t>> load(n_indep_units);
     using Load = std::pair<uint64_t, uint32_t>;
     std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
     for (uint32_t u = 0; u < n_indep_units; u++) heap.push(Load(0, u));
-    for (uint32_t sid : order) {
+    for (uint32_t sid : unit_streams) {
       Load l = heap.top();
       heap.pop();
-      unit_streams[l.second].push_back(sid);
+      load[l.second].push_back(sid);
       l.first += stream_bytes[sid] + 1;
-      if (unit_streams[l.second].size() < kMaxProducers) heap.push(l);
+      if (load[l.second].size() < kMaxProducers) heap.push(l);
+    }
+    unit_streams.clear();
+    for (uint32_t u = 0; u < n_indep_units; u++) {
+      unit_streams.insert(unit_streams.end(), load[u].begin(), load[u].end());
+      unit_begin[u + 1] = (uint32_t)unit_streams.size();
     }
   }
   // tables
@@ -573,30 +580,28 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
     rg.base_m = ch->dev_msgs[0];
     rings.push_back(rg);
     uint32_t any = 0;
-    for (uint32_t p = 0; p < d.K; p++) {
-      auto it = prod_stream.find(std::make_pair(ch, p));
-      if (it != prod_stream.end()) any = it->second;
-    }
-    for (uint32_t p = 0; p < d.K; p++) {
-      auto it = prod_stream.find(std::make_pair(ch, p));
-      sop.push_back(it != prod_stream.end() ? it->second : any);
-      if (it != prod_stream.end()) {
-        unit_of[it->second] = (uint32_t)dch.size();
-        ring_of[it->second] = d.first_ring;
-        d.total_msgs += st[it->second].n_msgs;
+    for (uint32_t sid : ch->pump_stream)
+      if (sid != kNoStream) any = sid;
+    for (uint32_t sid : ch->pump_stream) {
+      sop.push_back(sid != kNoStream ? sid : any);
+      if (sid != kNoStream) {
+        unit_of[sid] = (uint32_t)dch.size();
+        ring_of[sid] = d.first_ring;
+        d.total_msgs += st[sid].n_msgs;
       }
     }
     lock_unit_first.push_back((uint32_t)dch.size());
     for (uint32_t m = 0; m < team[k]; m++) dch.push_back(d);  // claim/rounds set below
   }
-  for (const auto &us : unit_streams) {
+  for (uint32_t u = 0; u < n_indep_units; u++) {
     DevChannel d{};
     d.mode = kModeSpsc;  // independent single-producer rings
-    d.n_rings = (uint32_t)us.size();
+    d.n_rings = unit_begin[u + 1] - unit_begin[u];
     d.first_ring = (uint32_t)rings.size();
     d.K = d.n_rings;
     d.prod_stream_base = (uint32_t)sop.size();
-    for (uint32_t sid : us) {
+    for (uint32_t i = unit_begin[u]; i < unit_begin[u + 1]; i++) {
+      const uint32_t sid = unit_streams[i];
       hicr_channel ch = st[sid].channel;
       const uint32_t r = ch->cfg.mode == HICR_CH_MPSC_NOLOCK ? st[sid].producer : 0;
       unit_of[sid] = (uint32_t)dch.size();
@@ -608,7 +613,6 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
     dch.push_back(d);
   }
   const uint32_t nch = (uint32_t)dch.size();
-  const uint32_t n_wgs = prod_wgs + nch;
   for (uint32_t i = 0; i < n; i++) {
     ds[i].channel = unit_of[i];
     ds[i].producer = st[i].producer;
@@ -630,12 +634,28 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
     if (rc != HICR_OK) return rc;
   }
   std::vector<DevRole> roles;
-  for (uint32_t i = 0; i < n; i += 4) {
-    DevRole r{0, std::min<uint32_t>(4, n - i), {0, 0, 0, 0}};
-    for (uint32_t w = 0; w < r.count; w++) r.ids[w] = i + w;
-    roles.push_back(r);
-  }
-  for (uint32_t k = 0; k < nch; k++) roles.push_back(DevRole{1, 1, {k, 0, 0, 0}});
+  auto add_roles = [&](bool groups, uint32_t group_kind, uint32_t wave_kind,
+                       const std::vector<uint32_t> &ids) {
+    const uint32_t per = groups ? 1 : 4;
+    for (size_t i = 0; i < ids.size(); i += per) {
+      DevRole r{groups ? group_kind : wave_kind, std::min<uint32_t>(per, (uint32_t)(ids.size() - i)),
+                {0, 0, 0, 0}};
+      for (uint32_t w = 0; w < r.count; w++) r.ids[w] = ids[i + w];
+      roles.push_back(r);
+    }
+  };
+  std::vector<uint32_t> members(nch - n_indep_units), units(n_indep_units);  // in this order in dch
+  std::iota(members.begin(), members.end(), 0u);
+  std::iota(units.begin(), units.end(), (uint32_t)members.size());
+  std::vector<uint32_t> lock_prods, prods = indep;
+  for (uint32_t i = 0; i < n; i++)
+    if (st[i].channel->cfg.mode == HICR_CH_MPSC_LOCK)
+      (plan.lock_groups ? lock_prods : prods).push_back(i);
+  add_roles(true, kRoleProducerGroup, kRoleProducerWaves, lock_prods);
+  add_roles(plan.ind_groups, kRoleProducerGroup, kRoleProducerWaves, prods);
+  add_roles(plan.ind_groups, kRoleConsumerGroup, kRoleConsumerWaves, units);
+  add_roles(true, kRoleLockMember, kRoleLockMember, members);
+  const uint32_t n_wgs = (uint32_t)roles.size();
   // one upload: [err words | rings | channels | streams | sop | roles | msg_off | msg_size],
   // then the locking teams' device scratch (not uploaded; its head is zeroed)
   auto align = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
@@ -707,7 +727,7 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
       l.same_stream = p.stream == s;
       l.shares_channel = false;
       for (hicr_channel ch : p.chans)
-        if (chan_idx.count(ch)) l.shares_channel = true;
+        if (ch->pump_idx >= 0) l.shares_channel = true;
       live.push_back(l);
     }
     for (size_t i : residency_waits(live, n_wgs, cap))

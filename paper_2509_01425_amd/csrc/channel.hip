@@ -4,50 +4,54 @@
 //   producer: wait until the consumer's released counters leave room for the
 //             message (entries tm - hm < E, bytes tb - hb + s <= P), write the
 //             payload at byte position tb mod P (split across the ring end),
-//             write the entry, release fence, publish tm + 1;
-//   consumer: acquire-read tm; while tm > hm read entry hm mod E and the
-//             payload at hb mod P, then release fence and publish hb + s and
-//             hm + 1 -- the notification that frees the producer's room.
+//             write the entry, wait until those writes have reached the
+//             device's coherence point, publish tm + 1;
+//   consumer: read tm; while tm > hm read entry hm mod E and the payload at
+//             hb mod P, then publish hb + s and hm + 1 -- the notification
+//             that frees the producer's room.
 // Locking MPSC: a ticket lock (FIFO-fair) guards the room check and the
 // reservation of [rb, rb + s) / entry rm; the copy runs outside the lock and
 // publication follows ticket order, so the shared ring holds one total order
-// and never overflows.  Non-locking MPSC: one ring per producer; the
-// consumer polls them round robin.
+// and never overflows.  Non-locking MPSC: one ring per producer.
 //
-// pump_kernel is persistent: every workgroup is either four independent
-// producer waves (one stream each) or one consumer (all four waves).  Waits
-// poll with relaxed device-scope loads and take one acquire fence once the
-// condition holds (an acquire per poll would invalidate the L2 on every
-// spin).  Producers copy up to 16 messages at a time (8 on a locking ring),
-// message by message; the producer of a long stream through a ring of its
-// own holds full batches of 16 unpublished, up to a ring's worth of entries
-// (E / 16 batches), and publishes them with one release (fewer releases, each
-// of which writes back the XCD's L2); consumers take up to 32 per release
-// across all of their rings and copy each batch as one index space of
-// 16-byte vectors.  Producers check every message against their stream's
-// slots before moving a byte.  The host launches no more workgroups than the
-// device holds at once, and every wait gives up after a no-progress time-out
-// or on the abort word, so every wave exits.
+// Everything that two workgroups exchange inside one pump -- payload, entries,
+// records, counters -- moves with agent-scope accesses (cache bit sc1: loads
+// miss the caches that are not coherent across XCDs, stores write through
+// them), so no fence is needed beside them: a producer's writes are visible
+// device-wide once its wave has waited for them (s_waitcnt vmcnt(0)), and a
+// consumer may free room once its loads have returned.  An agent-scope
+// release fence writes back the whole L2 of its XCD and an acquire
+// invalidates it; with one of each per batch those write-backs bounded the
+// pump (1,536 streams, 500 K messages of 16 B - 64 KiB: 6.28 ms with the
+// fences and plain payload accesses, 2.59 ms now = 6.0 TB/s of source, ring
+// and output bytes; 1,024 SPSC streams and 64 locking rings, 150 K messages to
+// 256 KiB: 7.6 ms, 3.48 ms now, set by the locking rings' ordered steps).
+//
+// pump_kernel is persistent: an endpoint (the producer of one stream, the
+// consumer of one or more single-producer rings) is either one wave, four of
+// them to a workgroup, or a whole workgroup when the device holds one for
+// every endpoint (few streams: the copy rate of one wave would bound each).
+// Either way its messages are cut into chunks of kChunkRows KiB that the
+// endpoint's waves take in turn, with the next chunk's loads issued before
+// the current chunk's stores.  A single-producer ring's messages lie back to
+// back in the ring and in the output, so its consumer copies everything it
+// takes as one range.  The host launches no more workgroups than the device
+// holds at once, and every wait gives up after a no-progress time-out or on
+// the abort word, so every wave exits.
 #include "chan.h"
+#include "internal.h"
+#include "span.h"
 
 namespace hicr {
 
-#define GLOBAL __attribute__((address_space(1)))
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef v4u v4u_any __attribute__((aligned(1)));
 
-
-__device__ __forceinline__ uint64_t ld_acq(uint64_t a) {
-  return __hip_atomic_load((uint64_t *)a, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint64_t ld_rlx(uint64_t a) {
   return __hip_atomic_load((uint64_t *)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_rlx(uint64_t a, uint64_t v) {
   __hip_atomic_store((uint64_t *)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_rel(uint64_t a, uint64_t v) {
-  __hip_atomic_store((uint64_t *)a, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // A 16-byte payload store (ring or output).
@@ -157,6 +161,29 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
   return ((uint64_t)__shfl((unsigned)(v >> 32), src) << 32) | (uint64_t)__shfl((unsigned)v, src);
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// A table entry that nothing writes while the kernel runs, at an index that
+// is the same in every lane: read through the scalar cache into scalar
+// registers (the compiler does so by itself only before the first store).
+template <class T>
+__device__ __forceinline__ T table(const T *p) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  const __attribute__((address_space(4))) uint32_t *w =
+      (const __attribute__((address_space(4))) uint32_t *)uni64((uint64_t)p);
+  uint32_t t[sizeof(T) / 4];
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(T) / 4; i++) t[i] = w[i];
+  T v;
+  __builtin_memcpy(&v, t, sizeof(T));
+  return v;
+}
+
 // Inclusive prefix sum over the 64 lanes of a wave.
 __device__ __forceinline__ uint64_t wave_scan(uint64_t v, uint32_t lane) {
 #pragma unroll
@@ -167,158 +194,221 @@ __device__ __forceinline__ uint64_t wave_scan(uint64_t v, uint32_t lane) {
   return v;
 }
 
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Lane `lane` (uniform) of a 64-bit value held in every lane's registers.
+__device__ __forceinline__ uint64_t lane64(uint64_t v, uint32_t lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
 }
 
-// A contiguous piece of a batched copy: n bytes d <- s.  a0 is the first
-// 16-byte-aligned destination byte inside it (clipped), nv its 16-byte body
-// vectors, v0 the body vectors of all earlier segments.
-struct Seg {
-  uint64_t d, s, n, a0, nv, v0;
+// Store two words of one 16-byte unit with one access (lanes outside `on`
+// store nothing), so that whoever reads the first also finds the second.
+__device__ __forceinline__ void st_pair(uint64_t a, uint64_t w0, uint64_t w1, bool on) {
+  v4i v;
+  v.x = (int32_t)w0;
+  v.y = (int32_t)(w0 >> 32);
+  v.z = (int32_t)w1;
+  v.w = (int32_t)(w1 >> 32);
+  bstore<16>(span_rsrc(a, 16), on ? 0u : ~0u, v);
+}
+
+// Nothing the compiler sees moves across this point.
+__device__ __forceinline__ void order() { asm volatile("" ::: "memory"); }
+
+// Wait until this wave's memory accesses have completed: its agent-scope
+// stores are then visible to every other wave of the device.
+__device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// n bytes d <- s (uniform), at most kChunkBytes of destination lines.
+constexpr int kChunkRows = 4;  // 1 KiB rows
+constexpr uint32_t kChunkBytes = 1024u * kChunkRows;
+struct Chunk {
+  uint64_t d, s;
+  uint32_t n;
 };
 
-__device__ __forceinline__ Seg make_seg(uint64_t d, uint64_t s, uint64_t n) {
-  Seg g;
-  g.d = d;
-  g.s = s;
-  g.n = n;
-  uint64_t a0 = (d + 15) & ~(uint64_t)15;
-  if (a0 > d + n) a0 = d + n;
-  uint64_t a1 = (d + n) & ~(uint64_t)15;
-  if (a1 < a0) a1 = a0;
-  g.a0 = a0;
-  g.nv = (a1 - a0) >> 4;
-  g.v0 = 0;
-  return g;
-}
+// Cache policies: ring accesses at agent scope (sc1), and nothing is used
+// again by the wave that touches it (nt).
+// Ring bytes are written without nt: the consumer reads most of them soon
+// after, and they then come from the memory-side cache (4.03 against 4.42 ms
+// a pass on the first configuration above; reading the ring without nt
+// 4.3-4.4 ms).
+constexpr int kAgent = 16;
+constexpr int kAgentStream = 18;
+constexpr int kReadStream = 2;
 
-// All TEAM threads copy nseg segments (held in LDS, every one non-empty, at
-// most kMaxSegs) as one index space of 16-byte vectors, so a batch of small
-// messages costs about one memory round trip instead of one per message.
-// Branch-free like team_copy: the head and tail bytes (slot 32 g + j: j < 16
-// head byte j of segment g, else tail byte j - 16) and the vectors are
-// clamped into range, so repeated copies write equal values, and a vector's
-// segment is found by a fixed binary search (log2 kMaxSegs steps) over the segments'
-// first vectors (v0) instead of a data-dependent loop; the compiler then
-// issues a round's U loads back to back.
-constexpr uint32_t kMaxSegs = 64;  // a power of two
-template <int TEAM, int U>
-__device__ void seg_copy(const Seg *sg, uint32_t nseg, uint64_t total_v, uint32_t t) {
-  if (nseg == 0) return;
-  constexpr int kB = (32 * kMaxSegs + TEAM - 1) / TEAM;  // byte slots per thread
-  unsigned char bv[kB];
-  uint64_t bd[kB];
-#pragma unroll
-  for (int q = 0; q < kB; q++) {
-    uint32_t x = t + (uint32_t)q * TEAM;
-    if (x > nseg * 32 - 1) x = nseg * 32 - 1;
-    const Seg &g = sg[x >> 5];
-    const uint32_t j = x & 31;
-    const uint64_t nh = g.a0 - g.d, a1 = g.a0 + 16 * g.nv, nt = g.d + g.n - a1;
-    uint64_t off;
-    if (j < 16)
-      off = nh ? (j < nh ? j : nh - 1) : 0;
-    else
-      off = nt ? (a1 - g.d) + (j - 16 < nt ? j - 16 : nt - 1) : 0;
-    bv[q] = *(const GLOBAL unsigned char *)(g.s + off);
-    bd[q] = g.d + off;
+// A chunk on its way: the 16-byte destination vectors of its rows, and in
+// lanes 0-15 the at most 15 bytes before the first, in lanes 16-31 the at
+// most 15 bytes after the last of them.  Loads and stores of what a chunk
+// does not have are out of the buffer resource's range: they read zero and
+// write nothing.  So a chunk costs the same instructions whatever its length
+// (also 0), and the compiler can count exactly which of them a store waits
+// for; with a branch around the loads it waits for all of them.
+template <int LP, int SP>
+struct Flight {
+  v4i v[kChunkRows];
+  uint32_t byte;
+  __device__ __forceinline__ static uint32_t head(const Chunk &c) {
+    const uint32_t h = (uint32_t)(-c.d) & 15u;
+    return h < c.n ? h : c.n;
   }
+  // (lanes past the tail get offsets past the chunk by themselves)
+  __device__ __forceinline__ static uint32_t byte_off(const Chunk &c, uint32_t lane) {
+    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u);
+    const uint32_t h = lane < nh ? lane : ~0u;
+    return lane < 16 ? h : body + lane - 16;
+  }
+  __device__ __forceinline__ void load(const Chunk &c, uint32_t lane) {
+    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u), o = nh + 16 * lane;
+    const rsrc_t r = span_rsrc(c.s, body);
+    byte = bload8<LP>(span_rsrc(c.s, c.n), byte_off(c, lane));
 #pragma unroll
-  for (int q = 0; q < kB; q++) *(GLOBAL unsigned char *)(bd[q]) = bv[q];
-  for (uint64_t b = 0; b < total_v; b += (uint64_t)TEAM * U) {
-    uint64_t sa[U], da[U];
+    for (int k = 0; k < kChunkRows; k++) v[k] = bload<LP>(r, o + 1024u * k);
+  }
+  __device__ __forceinline__ void store(const Chunk &c, uint32_t lane) const {
+    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u), o = nh + 16 * lane;
+    const rsrc_t r = span_rsrc(c.d, body);
 #pragma unroll
-    for (int k = 0; k < U; k++) {
-      uint64_t v = b + t + (uint64_t)k * TEAM;
-      if (v > total_v - 1) v = total_v - 1;
-      uint32_t c = 0;  // last segment with v0 <= v
-#pragma unroll
-      for (uint32_t st = kMaxSegs / 2; st; st >>= 1) {
-        const uint32_t i = c + st < nseg ? c + st : nseg - 1;
-        c = (c + st < nseg && sg[i].v0 <= v) ? c + st : c;
-      }
-      const Seg &g = sg[c];
-      const uint64_t w = 16 * (v - g.v0);
-      sa[k] = g.s + (g.a0 - g.d) + w;
-      da[k] = g.a0 + w;
+    for (int k = 0; k < kChunkRows; k++) bstore<SP>(r, o + 1024u * k, v[k]);
+    bstore8<SP>(span_rsrc(c.d, c.n), byte_off(c, lane), byte);
+  }
+};
+
+// j messages between a ring and other memory, as a sequence of chunks: lane l
+// holds message l's size, ring position (below P) and other address.  Chunks
+// end at destination line boundaries, message ends and the ring end.
+template <bool kToRing>
+struct Feed {
+  uint64_t payload, P;
+  uint64_t v_size, v_pos, v_addr;
+  uint32_t j, l;
+  uint64_t left, pos, addr;
+  __device__ __forceinline__ Chunk next() {
+    while (left == 0 && l < j) {
+      left = lane64(v_size, l);
+      pos = lane64(v_pos, l);
+      addr = lane64(v_addr, l);
+      l++;
     }
-    v4u r[U];
-#pragma unroll
-    for (int k = 0; k < U; k++) r[k] = *(const GLOBAL v4u_any *)(sa[k]);
-#pragma unroll
-    for (int k = 0; k < U; k++) st16(da[k], r[k]);
+    Chunk c;
+    const uint64_t ring = payload + pos;
+    c.d = kToRing ? ring : addr;
+    c.s = kToRing ? addr : ring;
+    uint64_t n = kChunkBytes - (c.d & (kLineBytes - 1));
+    if (n > left) n = left;
+    if (n > P - pos) n = P - pos;
+    c.n = __builtin_amdgcn_readfirstlane((uint32_t)n);
+    left -= n;
+    addr += n;
+    pos += n;
+    if (pos == P) pos = 0;
+    return c;
   }
+  __device__ __forceinline__ void skip(uint32_t k) {
+    for (uint32_t i = 0; i < k; i++) (void)next();
+  }
+};
+
+// Move the messages of a feed with an endpoint of WAVES waves: wave w takes
+// chunks w, w + WAVES, ...  On return every load has completed; stores may
+// still be in flight.
+template <int WAVES, bool kToRing>
+__device__ __forceinline__ void move_feed(Feed<kToRing> f, uint32_t wave, uint32_t lane) {
+  typedef Flight<kToRing ? kReadStream : kAgentStream, kToRing ? kAgent : kAgentStream> F;
+  f.l = 0;
+  f.left = f.pos = f.addr = 0;
+  if (WAVES > 1) f.skip(wave);
+  auto take = [&]() {
+    const Chunk c = f.next();
+    if (WAVES > 1) f.skip(WAVES - 1);
+    return c;
+  };
+  Chunk a = take();
+  if (a.n == 0) return;
+  F fa, fb;
+  fa.load(a, lane);
+  do {
+    const Chunk b = take();
+    fb.load(b, lane);
+    fa.store(a, lane);
+    a = take();
+    fa.load(a, lane);
+    fb.store(b, lane);
+  } while (a.n);
+  order();
 }
 
-// Messages a producer publishes at once: 16 on a ring of its own, 8 on a
-// locking MPSC ring, where a larger reservation keeps the other producers
-// waiting for room longer (measured: 16 gave +15% on the non-locking pump and
-// -5% on the locking one).
-constexpr uint32_t kProdBatch = 16;
-constexpr uint32_t kProdBatchLocking = 8;
-constexpr uint32_t kConsBatch = 32;  // messages a consumer takes at once
-static_assert(2 * kConsBatch <= kMaxSegs, "a consumer batch is at most 2 segments per message");
+// What the first wave of a workgroup endpoint tells the others per batch.
+struct Cast {
+  uint64_t w[4];
+  uint32_t stop, late_stop;
+};
 
-// One producer wave drives one stream: it takes as many of its next messages
-// as the ring has room for (up to kProdBatch, or kProdBatchLocking), copies
-// them as one batch and writes their entries.  A locking ring publishes every
-// batch (in reservation order).  On a ring of its own, a stream of more than
-// four rings' worth of entries keeps full batches unpublished, up to
-// E / kProdBatch of them, and publishes them with one release; when the next
-// message does not fit, it publishes what it holds before it waits (the
-// consumer cannot free room for messages it has not seen).  Measured on the
-// channel configuration (~650 messages per stream), one process alternating:
-// 3,564-3,680 GB/s holding up to four batches against 2,873-3,207 with a
-// release per batch, message latency p99 0.9 ms against 2.2-2.6 ms.  Short
-// streams publish every batch: holding in the serving loop's bursts (at most
-// 256 messages) raised its latency p99 from 1.9 to 3.1 ms, and holding only
-// while the consumer had a batch left to work on still to 2.3 ms, as a burst
-// loses the overlap of its producer and consumer.
-__device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t lane, Seg *sg) {
+// Messages a producer publishes at once.  On a locking ring a batch also ends
+// at an eighth of the ring's bytes (unless its first message is larger), and
+// so does a round of the consumer team: the ring holds several batches and
+// rounds at different stages at once, where one of half the ring made the
+// others wait (64 rings, 8 producers each, messages to 256 KiB: 1.80 ms with
+// the eighths, 2.15 ms without; with 1,024 SPSC streams beside them 4.84
+// against 5.1 ms a pass; a sixteenth 1.84, a quarter 1.83).
+constexpr uint32_t kProdBatch = 16;
+constexpr uint32_t kLockShare = 8;
+
+// The producer of one stream (WAVES waves): it takes as many of its next
+// messages as the ring has room for, copies them as one batch and writes
+// their entries.  A batch is published at the top of the next turn, after
+// one wait that covers its stores and the loads of the next messages' sizes.
+template <int WAVES>
+__device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, uint32_t lane,
+                             Cast *cast) {
   // the stream id is the same in every lane of the wave; saying so lets the
   // stream and ring descriptors live in scalar registers
   const uint32_t sid = __builtin_amdgcn_readfirstlane(sid_in);
-  const DevStream st = a.streams[sid];
-  const DevRing r = a.rings[st.ring];
-  const bool locking = a.chans[st.channel].mode == kModeMpscLock;
+  const DevStream st = table(&a.streams[sid]);
+  const DevRing r = table(&a.rings[st.ring]);
+  const bool locking = table(&a.chans[st.channel].mode) == kModeMpscLock;
   const uint64_t c = r.coord;
   const uint64_t tm_a = c + offsetof(RingCoord, prod), hm_a = c + offsetof(RingCoord, cons),
                  hb_a = hm_a + 8, tk_a = c + offsetof(RingCoord, lock), sv_a = tk_a + 8,
                  rm_a = tk_a + 16, rb_a = tk_a + 24;
   // rings are empty when a pump starts: the producer side resumes at the
   // consumer's released counters
-  uint64_t tm = ld_acq(tm_a), tb = ld_acq(hb_a);
+  uint64_t tm = uni64(ld_rlx(tm_a)), tb = uni64(ld_rlx(hb_a));
   Watch w{0, a.timeout_ticks, a.err, 0};
   w.progress();
   uint64_t m = 0;
   uint64_t out_run = 0;  // output bytes of this stream's earlier messages
-  const uint64_t max_held =
-      locking || st.n_msgs <= 4 * r.E ? 1 : (r.E / kProdBatch > 1 ? r.E / kProdBatch : 1);
-  uint64_t pub_m = 0;  // messages published
-  uint64_t held = 0;   // full batches copied and not yet published
-  // the release covers the payload and entries of every message since the
-  // last publication; then the counters move past them
-  auto publish = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    if (a.ts_push)
-      for (uint64_t k = lane; k < m - pub_m; k += 64) a.ts_push[st.first_msg + pub_m + k] = wall_clock64();
-    if (lane == 0) {
-      // a ring of its own also publishes its byte counter, the form user
-      // kernels (hicr_device.h) resume from
-      st_rlx(tm_a + 8, tb);
-      st_rlx(tm_a, tm);
-    }
-    pub_m = m;
-    held = 0;
-  };
-  while (m < st.n_msgs) {
-    // sizes and offsets of the next messages of this batch, one per lane
-    const bool have = lane < (locking ? kProdBatchLocking : kProdBatch) && m + lane < st.n_msgs;
+  uint32_t last_j = 0;   // messages of the batch not yet published
+  for (;;) {
+    // sizes and offsets of the next messages, one per lane
+    const bool have = lane < kProdBatch && m + lane < st.n_msgs;
     const uint64_t sz = have ? a.msg_size[st.first_msg + m + lane] : 0;
     const uint64_t off = have ? a.msg_off[st.first_msg + m + lane] : 0;
+    drain();
+    if (WAVES > 1) __syncthreads();
+    bool stop = false;
+    if (wave == 0 && last_j) {
+      // the previous batch's payload and entries are in place: publish it, on
+      // a locking ring in reservation order
+      if (locking)
+        while (uni64(ld_rlx(tm_a)) != tm - last_j) {
+          __builtin_amdgcn_s_sleep(1);
+          if (w.expired()) {
+            stop = true;
+            break;
+          }
+        }
+      if (!stop) {
+        if (a.ts_push && lane < last_j) a.ts_push[st.first_msg + m - last_j + lane] = wall_clock64();
+        if (lane == 0) {
+          // a ring of its own also publishes its byte counter, the form user
+          // kernels (hicr_device.h) resume from
+          if (!locking) st_rlx(tm_a + 8, tb);
+          st_rlx(tm_a, tm);
+        }
+      }
+      w.progress();
+    }
     const uint64_t incl = wave_scan(sz, lane);
     // every message is checked before a byte of it moves (the host has not
     // seen message tables that live on the device): it fits the ring, its
@@ -326,319 +416,269 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t lane, 
     // output slot
     const bool bad = have && (sz > r.P || off > st.src_bytes || sz > st.src_bytes - off ||
                               out_run + incl > st.out_bytes);
+    if (m >= st.n_msgs) return;
     if (__ballot(bad)) {
-      if (lane == 0)
+      if (wave == 0 && lane == 0)
         __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
-    uint64_t ticket = 0;
-    if (locking) {
-      if (lane == 0)
-        ticket = __hip_atomic_fetch_add((uint64_t *)tk_a, 1ull, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-      ticket = shfl64(ticket, 0);
-      while (ld_rlx(sv_a) != ticket) {
-        __builtin_amdgcn_s_sleep(1);
-        if (w.expired()) return;
+    uint64_t my_tm = tm, my_tb = tb, hm = 0, hb = 0, ticket = 0;
+    if (wave == 0) {
+      if (locking && !stop) {
+        if (lane == 0)
+          ticket = __hip_atomic_fetch_add((uint64_t *)tk_a, 1ull, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+        ticket = shfl64(ticket, 0);
+        while (uni64(ld_rlx(sv_a)) != ticket) {
+          __builtin_amdgcn_s_sleep(1);
+          if (w.expired()) {
+            stop = true;
+            break;
+          }
+        }
+        order();
+        my_tm = uni64(ld_rlx(rm_a));
+        my_tb = uni64(ld_rlx(rb_a));
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      // wait until at least the first message fits, then take every leading
+      // message that fits in the room seen (one view of the consumer for the
+      // whole endpoint)
+      const uint64_t s0 = shfl64(sz, 0);
+      while (!stop) {
+        hm = uni64(ld_rlx(hm_a));
+        hb = uni64(ld_rlx(hb_a));
+        if (my_tm - hm < r.E && my_tb - hb + s0 <= r.P) break;
+        __builtin_amdgcn_s_sleep(2);
+        if (w.expired()) stop = true;
+      }
+      order();
     }
-    uint64_t my_tm = locking ? ld_rlx(rm_a) : tm;
-    uint64_t my_tb = locking ? ld_rlx(rb_a) : tb;
-    // wait until at least the first message fits, then take every leading
-    // message that fits in the room seen
-    uint64_t hm, hb;
-    const uint64_t s0 = shfl64(sz, 0);
-    for (;;) {
-      hm = shfl64(ld_rlx(hm_a), 0);  // one view of the consumer for the whole wave
-      hb = shfl64(ld_rlx(hb_a), 0);
-      if (my_tm - hm < r.E && my_tb - hb + s0 <= r.P) break;
-      if (held) publish();
-      __builtin_amdgcn_s_sleep(2);
-      if (w.expired()) return;
+    if (WAVES > 1) {
+      if (wave == 0 && lane == 0) {
+        cast->w[0] = my_tm;
+        cast->w[1] = my_tb;
+        cast->w[2] = hm;
+        cast->w[3] = hb;
+        cast->stop = stop;
+      }
+      __syncthreads();
+      my_tm = cast->w[0];
+      my_tb = cast->w[1];
+      hm = cast->w[2];
+      hb = cast->w[3];
+      stop = cast->stop;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the consumer's reads are done
-    const bool fits = have && (my_tm + lane + 1 - hm <= r.E) && (my_tb + incl - hb <= r.P);
+    if (stop) return;
+    const bool fits = have && (my_tm + lane + 1 - hm <= r.E) && (my_tb + incl - hb <= r.P) &&
+                      (!locking || lane == 0 || incl <= r.P / kLockShare);
     const uint64_t fm = __ballot(fits);
     const uint32_t j = (uint32_t)__ffsll((unsigned long long)~fm) - 1;  // leading fitting lanes
     const uint64_t bytes = shfl64(incl, (int)j - 1);
-    if (locking && lane == 0) {
-      st_rlx(rm_a, my_tm + j);
-      st_rlx(rb_a, my_tb + bytes);
-      st_rel(sv_a, ticket + 1);
+    if (locking && wave == 0) {
+      if (lane == 0) {
+        st_rlx(rm_a, my_tm + j);
+        st_rlx(rb_a, my_tb + bytes);
+      }
+      drain();  // the next holder of the lock sees both
+      if (lane == 0) st_rlx(sv_a, ticket + 1);
     }
     // entries (and, on a locking ring, the records the consumer team reads)
-    // are written now, before the copy, so sizes and offsets need not stay
-    // in registers across it; the release before publication covers them
-    if (lane < j) {
-      *(GLOBAL uint64_t *)(r.entries + 8 * ((my_tm + lane) % r.E)) =
-          sz | ((uint64_t)st.producer << 48);
+    // are written now; the wait before publication covers them
+    if (wave == 0 && lane < j) {
+      st_rlx(r.entries + 8 * ((my_tm + lane) % r.E), sz | ((uint64_t)st.producer << 48));
       if (locking) {
         // the message's record for the consumer team: ring byte position,
         // output address, message index (a counter outside this pump's
         // records means the ring's state is not what the host planned for)
         const uint64_t idx = my_tm + lane - r.base_m;
         if (idx < r.side_n) {
-          uint64_t *rec = (uint64_t *)(r.side + 24 * idx);
-          rec[0] = my_tb + incl - sz;
-          rec[1] = st.out_base + out_run + incl - sz;
-          rec[2] = st.first_msg + m + lane;
+          const uint64_t rec = r.side + 24 * idx;
+          st_rlx(rec, my_tb + incl - sz);
+          st_rlx(rec + 8, st.out_base + out_run + incl - sz);
+          st_rlx(rec + 16, st.first_msg + m + lane);
         } else {
           __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
     }
-    // segments: message l of the batch -> ring bytes at (my_tb + excl_l) mod P
-    if (lane < j) {
-      const uint64_t pos = (my_tb + incl - sz) % r.P;
-      const uint64_t first = r.P - pos < sz ? r.P - pos : sz;
-      sg[2 * lane] = make_seg(r.payload + pos, st.src_base + off, first);
-      sg[2 * lane + 1] = make_seg(r.payload, st.src_base + off + first, sz - first);
-    }
-    wave_sync();
-    // one segment after another, each in full rounds of 4 KiB (a batch as
-    // one index space of vectors needs a search per vector, which kept the
-    // loads of a round from overlapping)
-    for (uint32_t g = 0; g < 2 * j; g++) team_copy<64, 4>(sg[g].d, sg[g].s, sg[g].n, lane);
-    if (locking) {
-      // publish in reservation order, carrying the predecessors' writes
-      while (ld_rlx(tm_a) != my_tm) {
-        __builtin_amdgcn_s_sleep(1);
-        if (w.expired()) return;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
-      if (a.ts_push && lane < j) a.ts_push[st.first_msg + m + lane] = wall_clock64();
-      if (lane == 0) st_rlx(tm_a, my_tm + j);
-    }
+    Feed<true> f;
+    f.payload = r.payload;
+    f.P = r.P;
+    f.v_size = sz;
+    f.v_pos = (my_tb + incl - sz) % r.P;
+    f.v_addr = st.src_base + off;
+    f.j = j;
+    move_feed<WAVES, true>(f, wave, lane);
     tm = my_tm + j;
     tb = my_tb + bytes;
     m += j;
     out_run += bytes;
-    if (!locking) {
-      if (held + 1 < max_held && j == kProdBatch && m < st.n_msgs)
-        held++;
-      else
-        publish();
-    }
-    wave_sync();
+    last_j = j;
     w.progress();
   }
 }
 
-// One consumer workgroup drains a set of independent rings, each with a
-// single producer stream (SPSC rings, non-locking MPSC sub-rings): each round
-// it looks at all of its rings at once, takes up to kConsBatch published
-// messages (round robin over rings), copies them as one batch to their
-// streams' outputs and releases each ring's room with one store pair.
-__device__ void run_consumer(const PumpArgs &a, uint32_t cid, uint32_t tid) {
-  __shared__ uint64_t s_hm[kMaxProducers], s_hb[kMaxProducers];
-  __shared__ uint64_t s_outpos[kMaxProducers], s_cnt[kMaxProducers];
-  __shared__ uint32_t s_take[kMaxProducers];
-  __shared__ uint64_t s_ent[kConsBatch];
-  __shared__ uint32_t s_ring_of[kConsBatch];
-  __shared__ uint64_t s_idx_of[kConsBatch];
-  __shared__ uint64_t s_rbytes[kMaxProducers];
-  __shared__ Seg s_seg[2 * kConsBatch];
-  __shared__ uint32_t s_k, s_stop, s_nseg;
-  __shared__ uint64_t s_total_v;
-  // per-ring and per-producer tables, staged once so the planning loop
-  // below touches LDS only
-  __shared__ uint64_t s_rpay[kMaxProducers], s_rent[kMaxProducers], s_rcoord[kMaxProducers];
-  __shared__ uint64_t s_pout[kMaxProducers], s_pbytes[kMaxProducers];
-  __shared__ uint64_t s_pfirst[kMaxProducers], s_pn[kMaxProducers], s_ptrace[kMaxProducers];
-  __shared__ uint64_t s_rP[kMaxProducers], s_rE[kMaxProducers];
-  __shared__ uint32_t s_psid[kMaxProducers];
-  const DevChannel ch = a.chans[cid];
-  const uint32_t lane = tid & 63, wave = tid >> 6;
-  for (uint32_t i = tid; i < ch.n_rings; i += kPumpBlock) {
-    const DevRing rg = a.rings[ch.first_ring + i];
-    const uint64_t c = rg.coord + offsetof(RingCoord, cons);
-    s_hm[i] = ld_acq(c);
-    s_hb[i] = ld_acq(c + 8);
-    s_rpay[i] = rg.payload;
-    s_rent[i] = rg.entries;
-    s_rcoord[i] = rg.coord;
-    s_rP[i] = rg.P;
-    s_rE[i] = rg.E;
+// The consumer of a set of independent rings (WAVES waves), each with a
+// single producer stream (SPSC rings, non-locking MPSC sub-rings): lane q
+// keeps ring q's state.  Each turn takes up to 64 published messages of one
+// ring (round robin over the rings that have any), at most a quarter of the
+// ring's bytes unless the first message is larger, so that the producer gets
+// room back while the rest is copied; copies them as one range to their
+// stream's output and releases their room.
+template <int WAVES>
+__device__ void run_consumer(const PumpArgs &a, uint32_t uid_in, uint32_t wave, uint32_t lane,
+                             Cast *cast) {
+  const uint32_t uid = __builtin_amdgcn_readfirstlane(uid_in);
+  const DevChannel u = table(&a.chans[uid]);
+  const bool mine = lane < u.n_rings;
+  uint64_t coord = 0, hm = 0, hb = 0, pos = 0, out_pos = 0, cnt = 0;
+  if (mine) {
+    const DevRing rg = a.rings[u.first_ring + lane];
+    coord = rg.coord;
+    hm = ld_rlx(coord + offsetof(RingCoord, cons));
+    hb = ld_rlx(coord + offsetof(RingCoord, cons) + 8);
+    pos = hb % rg.P;
   }
-  for (uint32_t p = tid; p < ch.K; p += kPumpBlock) {
-    const uint32_t sid = a.stream_of_prod[ch.prod_stream_base + p];
-    const DevStream so = a.streams[sid];
-    s_psid[p] = sid;
-    s_pout[p] = so.out_base;
-    s_pbytes[p] = so.out_bytes;
-    s_pfirst[p] = so.first_msg;
-    s_pn[p] = so.n_msgs;
-    s_ptrace[p] = so.trace_base;
-    s_outpos[p] = 0;
-    s_cnt[p] = 0;
-  }
-  __syncthreads();
   Watch w{0, a.timeout_ticks, a.err, 0};
   w.progress();
   uint64_t done = 0;
   uint32_t rr = 0;
-  while (done < ch.total_msgs) {
-    if (wave == 0) {
-      uint64_t av = 0;
-      uint32_t ri = 0;
-      bool stop = false;
+  for (;;) {
+    uint64_t r_pos = 0, dst = 0, bytes = 0;
+    uint32_t q = 0, k = 0;
+    bool stop = done >= u.total_msgs;
+    if (wave == 0 && !stop) {
+      uint64_t av = 0, ready;
       for (;;) {
-        av = 0;
-        if (lane < ch.n_rings) {
-          ri = (rr + lane) % ch.n_rings;
-          av = ld_rlx(s_rcoord[ri] + offsetof(RingCoord, prod)) - s_hm[ri];
-        }
-        if (__ballot(av > 0)) break;
+        av = mine ? ld_rlx(coord + offsetof(RingCoord, prod)) - hm : 0;
+        ready = __ballot(av > 0);
+        if (ready) break;
         __builtin_amdgcn_s_sleep(2);
         if (w.expired()) {
           stop = true;
           break;
         }
       }
-      // quotas in ring order starting at rr: take while the batch has room
-      const uint64_t left = ch.total_msgs - done;
-      const uint64_t cap = left < kConsBatch ? left : kConsBatch;
-      const uint64_t want = av < cap ? av : cap;
-      const uint64_t incl = wave_scan(want, lane);
-      uint64_t take = 0;
-      if (incl - want < cap) take = (incl <= cap) ? want : cap - (incl - want);
-      if (lane < ch.n_rings) s_take[ri] = (uint32_t)take;
-      const uint64_t k = shfl64(wave_scan(take, lane), 63);
-      if (lane == 0) {
-        s_stop = stop;
-        s_k = (uint32_t)k;
-      }
-    }
-    __syncthreads();
-    if (s_stop) break;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const uint32_t k = s_k;
-    // message i of the batch: ring and index within it (rings in order from rr)
-    if (tid == 0) {
-      uint32_t i = 0;
-      for (uint32_t q = 0; q < ch.n_rings && i < k; q++) {
-        const uint32_t ri = (rr + q) % ch.n_rings;
-        for (uint32_t x = 0; x < s_take[ri]; x++, i++) {
-          s_ring_of[i] = ri;
-          s_idx_of[i] = s_hm[ri] + x;
+      order();
+      if (!stop) {
+        const uint64_t from = ready >> rr;
+        q = from ? rr + (uint32_t)__ffsll((unsigned long long)from) - 1
+                 : (uint32_t)__ffsll((unsigned long long)ready) - 1;
+        const DevRing rg = table(&a.rings[u.first_ring + q]);
+        const uint32_t sid = table(&a.stream_of_prod[u.prod_stream_base + q]);
+        const DevStream so = table(&a.streams[sid]);
+        const uint64_t q_hm = lane64(hm, q), q_out = lane64(out_pos, q), q_cnt = lane64(cnt, q);
+        uint64_t n = lane64(av, q);
+        if (n > 64) n = 64;
+        if (n > rg.E) n = rg.E;
+        uint64_t e = 0;
+        if (lane < n) {
+          uint64_t i = q_hm % rg.E + lane;
+          if (i >= rg.E) i -= rg.E;
+          e = ld_rlx(rg.entries + 8 * i);
         }
-      }
-    }
-    __syncthreads();
-    if (tid < k) {
-      const uint32_t ri = s_ring_of[tid];
-      s_ent[tid] = *(const GLOBAL uint64_t *)(s_rent[ri] + 8 * (s_idx_of[tid] % s_rE[ri]));
-    }
-    __syncthreads();
-    if (tid == 0) {
-      // plan the copies; entries are checked against the plan first, so a
-      // malformed entry stops the pump instead of writing out of bounds
-      uint32_t bad = 0, nseg = 0;
-      for (uint32_t q = 0; q < ch.n_rings; q++) s_rbytes[q] = 0;
-      for (uint32_t i = 0; i < k; i++) {
-        const uint32_t ri = s_ring_of[i];
-        const uint64_t e = s_ent[i];
-        const uint64_t sz = e & kEntrySizeMask;
-        const uint32_t p = ri;  // ring q carries producer stream q of the unit
-        const uint64_t P = s_rP[ri];
-        if (sz > P || s_outpos[p] + sz > s_pbytes[p] || s_cnt[p] >= s_pn[p]) {
-          bad = 1;
-          break;
+        const uint64_t sz = e & kEntrySizeMask, incl = wave_scan(sz, lane);
+        const uint64_t some = __ballot(lane < n && (lane == 0 || incl <= rg.P / 4));
+        k = (uint32_t)__popcll(some);  // leading lanes: incl never decreases
+        bytes = lane64(incl, k - 1);
+        // entries are checked against the plan before any byte moves, so a
+        // malformed entry stops the pump instead of writing out of bounds
+        const bool bad = lane < k && (sz > rg.P || q_out + incl > so.out_bytes ||
+                                      q_cnt + lane >= so.n_msgs);
+        if (__ballot(bad)) {
+          if (lane == 0)
+            __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+          stop = true;
+        } else if (lane < k) {
+          if (a.trace) a.trace[so.trace_base + q_cnt + lane] = sid;
+          if (a.ts_pop) a.ts_pop[so.first_msg + q_cnt + lane] = wall_clock64();
         }
-        const uint64_t pos = (s_hb[ri] + s_rbytes[ri]) % P;
-        const uint64_t first = P - pos < sz ? P - pos : sz;
-        const uint64_t dst = s_pout[p] + s_outpos[p];
-        if (first) s_seg[nseg++] = make_seg(dst, s_rpay[ri] + pos, first);
-        if (sz > first) s_seg[nseg++] = make_seg(dst + first, s_rpay[ri], sz - first);
-        s_rbytes[ri] += sz;
-        s_outpos[p] += sz;
-        if (a.trace) a.trace[s_ptrace[p] + s_cnt[p]] = s_psid[p];
-        if (a.ts_pop) a.ts_pop[s_pfirst[p] + s_cnt[p]] = wall_clock64();
-        s_cnt[p] += 1;
-      }
-      uint64_t v = 0;
-      for (uint32_t g = 0; g < nseg; g++) {
-        s_seg[g].v0 = v;
-        v += s_seg[g].nv;
-      }
-      s_nseg = nseg;
-      s_total_v = v;
-      if (bad) {
-        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_stop = 1;
+        r_pos = lane64(pos, q);
+        dst = so.out_base + q_out;
       }
     }
-    __syncthreads();
-    if (s_stop) break;
-    seg_copy<kPumpBlock, 4>(s_seg, s_nseg, s_total_v, tid);
-    __syncthreads();  // every read of the rings has completed
-    if (tid == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      for (uint32_t q = 0; q < ch.n_rings; q++) {
-        const uint32_t t = s_take[q];
-        if (!t) continue;
-        const uint64_t c = s_rcoord[q] + offsetof(RingCoord, cons);
-        s_hb[q] += s_rbytes[q];
-        s_hm[q] += t;
-        st_rlx(c + 8, s_hb[q]);
-        st_rlx(c, s_hm[q]);
+    if (WAVES > 1) {
+      if (wave == 0 && lane == 0) {
+        cast->w[0] = q;
+        cast->w[1] = r_pos;
+        cast->w[2] = dst;
+        cast->w[3] = bytes;
+        cast->stop = stop;
       }
+      __syncthreads();
+      q = (uint32_t)cast->w[0];
+      r_pos = cast->w[1];
+      dst = cast->w[2];
+      bytes = cast->w[3];
+      stop = cast->stop;
     }
-    done += k;
-    rr = (rr + 1) % ch.n_rings;
+    if (stop) return;
+    Feed<false> f;
+    {
+      const DevRing rg = table(&a.rings[u.first_ring + q]);
+      f.payload = rg.payload;
+      f.P = rg.P;
+    }
+    f.v_size = bytes;
+    f.v_pos = r_pos;
+    f.v_addr = dst;
+    f.j = 1;
+    move_feed<WAVES, false>(f, wave, lane);
+    if (WAVES > 1) __syncthreads();  // every wave's reads of the ring have returned
+    if (wave == 0) {
+      if (lane == q) {
+        hb += bytes;
+        hm += k;
+        out_pos += bytes;
+        cnt += k;
+        pos += bytes;
+        if (pos >= f.P) pos -= f.P;
+      }
+      st_pair(lane64(coord, q) + offsetof(RingCoord, cons), hm, hb, lane == q);
+      done += k;
+      rr = q + 1 < u.n_rings ? q + 1 : 0;
+    }
     w.progress();
   }
-  __threadfence();
 }
 
 // A locking MPSC ring consumed by a team of workgroups.  The ring holds one
 // total order; it is cut into rounds of consecutive messages.  A member
 // claims the next round number; once the previous round is defined the new
-// round starts where that one ends and takes up to kConsBatch messages that
+// round starts where that one ends and takes up to kLockBatch messages that
 // are already published (so a round never waits on room the ring cannot
 // give); the member copies it and releases the ring room in round order.
 // Each message's ring position and output address come from the record its
 // producer wrote before publishing, so a member never needs another round's
 // entries (which producers may already be reusing).
-__device__ void run_lock_team(const PumpArgs &a, uint32_t uid, uint32_t tid) {
-  __shared__ uint64_t s_pout[kMaxProducers], s_pbytes[kMaxProducers];
-  __shared__ uint64_t s_pfirst[kMaxProducers], s_pn[kMaxProducers];
-  __shared__ uint32_t s_psid[kMaxProducers];
-  __shared__ uint64_t s_sz[kConsBatch], s_pos[kConsBatch], s_out[kConsBatch];
-  __shared__ uint32_t s_p[kConsBatch], s_bad;
-  __shared__ Seg s_seg[2 * kConsBatch];
-  __shared__ uint64_t s_start, s_end, s_total_v, s_bend;
-  __shared__ uint32_t s_stop, s_nseg;
-  const DevChannel u = a.chans[uid];
-  const DevRing r = a.rings[u.first_ring];
+constexpr uint32_t kLockBatch = 32;
+__device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave, uint32_t lane,
+                              Cast *cast) {
+  const uint32_t uid = __builtin_amdgcn_readfirstlane(uid_in);
+  const DevChannel u = table(&a.chans[uid]);
+  const DevRing r = table(&a.rings[u.first_ring]);
   const uint64_t tm_a = r.coord + offsetof(RingCoord, prod);
-  const uint64_t hm_a = r.coord + offsetof(RingCoord, cons), hb_a = hm_a + 8;
+  const uint64_t hm_a = r.coord + offsetof(RingCoord, cons);
   const uint64_t last = r.base_m + u.total_msgs;  // counter after this pump's messages
   uint64_t *rounds = (uint64_t *)u.rounds;
-  for (uint32_t p = tid; p < u.K; p += kPumpBlock) {
-    const uint32_t sid = a.stream_of_prod[u.prod_stream_base + p];
-    const DevStream so = a.streams[sid];
-    s_psid[p] = sid;
-    s_pout[p] = so.out_base;
-    s_pbytes[p] = so.out_bytes;
-    s_pfirst[p] = so.first_msg;
-    s_pn[p] = so.n_msgs;
-  }
   Watch w{0, a.timeout_ticks, a.err, 0};
   w.progress();
   for (;;) {
-    if (tid == 0) {
-      uint32_t stop = 0;
-      const uint64_t k = __hip_atomic_fetch_add((uint64_t *)u.claim, 1ull, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
+    if (wave == 0) {
+      bool stop = false;
+      uint64_t k = 0;
+      if (lane == 0)
+        k = __hip_atomic_fetch_add((uint64_t *)u.claim, 1ull, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+      k = shfl64(k, 0);
       uint64_t start = r.base_m;
       if (k > 0) {
         uint64_t v;
-        while ((v = ld_rlx((uint64_t)&rounds[k - 1])) == 0) {
+        while ((v = uni64(ld_rlx((uint64_t)&rounds[k - 1]))) == 0) {
           __builtin_amdgcn_s_sleep(1);
           if (w.expired()) {
-            stop = 1;
+            stop = true;
             break;
           }
         }
@@ -647,112 +687,115 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid, uint32_t tid) {
       uint64_t end = start;
       if (!stop && start < last) {
         uint64_t tm;
-        while ((tm = ld_rlx(tm_a)) <= start) {
+        while ((tm = uni64(ld_rlx(tm_a))) <= start) {
           __builtin_amdgcn_s_sleep(2);
           if (w.expired()) {
-            stop = 1;
+            stop = true;
             break;
           }
         }
         if (!stop) {
-          end = start + kConsBatch;
+          order();
+          end = start + kLockBatch;
           if (end > tm) end = tm;
           if (end > last) end = last;
+          const uint64_t e =
+              lane < end - start ? ld_rlx(r.entries + 8 * ((start + lane) % r.E)) : 0;
+          const uint64_t incl = wave_scan(e & kEntrySizeMask, lane);
+          end = start + __popcll(__ballot(lane < end - start &&
+                                          (lane == 0 || incl <= r.P / kLockShare)));
         }
       }
       // round k is defined even when empty: later claimers see where it ends
-      if (!stop) st_rlx((uint64_t)&rounds[k], end + 1);
-      s_start = start;
-      s_end = end;
-      s_stop = stop || start >= last;
-      s_bad = 0;
+      if (!stop && lane == 0) st_rlx((uint64_t)&rounds[k], end + 1);
+      if (lane == 0) {
+        cast->w[0] = start;
+        cast->w[1] = end;
+        cast->stop = stop || start >= last;
+      }
+      order();
     }
     __syncthreads();
-    if (s_stop) break;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // records and payload of the round
-    const uint64_t start = s_start, n = s_end - s_start;
-    if (tid < n) {
-      const uint64_t seq = start + tid;
-      const uint64_t e = *(const GLOBAL uint64_t *)(r.entries + 8 * (seq % r.E));
-      const uint64_t *rec = (const uint64_t *)(r.side + 24 * (seq - r.base_m));
-      const uint64_t sz = e & kEntrySizeMask, pos = rec[0], out = rec[1], mi = rec[2];
+    if (cast->stop) return;
+    const uint64_t start = cast->w[0], n = cast->w[1] - start;
+    // every wave reads the round's entries and records (lane i: message i)
+    uint64_t sz = 0, pos = 0, out = 0;
+    bool bad = false;
+    if (lane < n) {
+      const uint64_t seq = start + lane;
+      const uint64_t e = ld_rlx(r.entries + 8 * (seq % r.E));
+      const uint64_t rec = r.side + 24 * (seq - r.base_m);
+      const uint64_t mi = ld_rlx(rec + 16);
+      sz = e & kEntrySizeMask;
+      pos = ld_rlx(rec);
+      out = ld_rlx(rec + 8);
       const uint32_t p = (uint32_t)(e >> 48) % u.K;
+      const uint32_t sid = a.stream_of_prod[u.prod_stream_base + p];
+      const DevStream so = a.streams[sid];
       // checked against the producer's stream before any byte moves
-      if (sz > r.P || out < s_pout[p] || out - s_pout[p] > s_pbytes[p] ||
-          sz > s_pbytes[p] - (out - s_pout[p]) || mi < s_pfirst[p] || mi - s_pfirst[p] >= s_pn[p])
-        atomicOr(&s_bad, 1u);
-      s_sz[tid] = sz;
-      s_pos[tid] = pos;
-      s_out[tid] = out;
-      s_p[tid] = p;
-      if (a.trace) a.trace[u.trace_base + (seq - r.base_m)] = s_psid[p];
-      if (a.ts_pop) a.ts_pop[mi] = wall_clock64();
-    }
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t nseg = 0;
-      uint64_t v = 0;
-      for (uint32_t i = 0; i < n; i++) {
-        const uint64_t sz = s_sz[i], pos = s_pos[i] % r.P;
-        const uint64_t first = r.P - pos < sz ? r.P - pos : sz;
-        if (first) {
-          s_seg[nseg] = make_seg(s_out[i], r.payload + pos, first);
-          s_seg[nseg].v0 = v;
-          v += s_seg[nseg++].nv;
-        }
-        if (sz > first) {
-          s_seg[nseg] = make_seg(s_out[i] + first, r.payload, sz - first);
-          s_seg[nseg].v0 = v;
-          v += s_seg[nseg++].nv;
-        }
+      bad = sz > r.P || out < so.out_base || out - so.out_base > so.out_bytes ||
+            sz > so.out_bytes - (out - so.out_base) || mi < so.first_msg ||
+            mi - so.first_msg >= so.n_msgs;
+      if (wave == 0 && !bad) {
+        if (a.trace) a.trace[u.trace_base + (seq - r.base_m)] = sid;
+        if (a.ts_pop) a.ts_pop[mi] = wall_clock64();
       }
-      s_nseg = nseg;
-      s_total_v = v;
-      s_bend = n ? s_pos[n - 1] + s_sz[n - 1] : 0;
-      if (s_bad) {
+    }
+    if (__ballot(bad)) {
+      if (lane == 0)
         __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_stop = 1;
-      }
+      return;  // the same in every wave
     }
-    __syncthreads();
-    if (s_stop) break;
-    seg_copy<kPumpBlock, 4>(s_seg, s_nseg, s_total_v, tid);
-    __syncthreads();  // every read of the ring has completed
-    if (tid == 0) {
+    Feed<false> f;
+    f.payload = r.payload;
+    f.P = r.P;
+    f.v_size = sz;
+    f.v_pos = pos % r.P;
+    f.v_addr = out;
+    f.j = (uint32_t)n;
+    move_feed<kPumpBlock / 64, false>(f, wave, lane);
+    __syncthreads();  // every wave's reads of the ring have returned
+    if (wave == 0) {
       // release in round order
-      while (ld_rlx(hm_a) != start) {
+      const uint64_t b_end = n ? lane64(pos, (uint32_t)n - 1) + lane64(sz, (uint32_t)n - 1) : 0;
+      bool stop = false;
+      while (uni64(ld_rlx(hm_a)) != start) {
         __builtin_amdgcn_s_sleep(1);
         if (w.expired()) {
-          s_stop = 1;
+          stop = true;
           break;
         }
       }
-      if (!s_stop) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        st_rlx(hb_a, s_bend);
-        st_rlx(hm_a, s_end);
-      }
+      if (!stop) st_pair(hm_a, start + n, b_end, lane == 0);
+      if (lane == 0) cast->late_stop = stop;
     }
     __syncthreads();
-    if (s_stop) break;
+    if (cast->late_stop) return;
     w.progress();
   }
-  __threadfence();
 }
 
 __global__ __launch_bounds__(kPumpBlock) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void pump_kernel(PumpArgs a) {
-  const DevRole role = a.roles[blockIdx.x];
-  const uint32_t tid = threadIdx.x;
-  __shared__ Seg s_pseg[4][2 * kProdBatch];
-  if (role.kind == 0) {
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform in the wave
-    if (wave < role.count) run_producer(a, a.roles[blockIdx.x].ids[wave], tid & 63, s_pseg[wave]);
-    __threadfence();
-  } else if (a.chans[role.ids[0]].mode == kModeMpscLock) {
-    run_lock_team(a, role.ids[0], tid);
-  } else {
-    run_consumer(a, role.ids[0], tid);
+  __shared__ Cast cast;
+  const DevRole role = table(&a.roles[blockIdx.x]);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform in the wave
+  switch (role.kind) {
+    case kRoleProducerWaves:
+      if (wave < role.count) run_producer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
+      break;
+    case kRoleProducerGroup:
+      run_producer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
+      break;
+    case kRoleConsumerWaves:
+      if (wave < role.count) run_consumer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
+      break;
+    case kRoleConsumerGroup:
+      run_consumer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
+      break;
+    default:
+      run_lock_team(a, role.ids[0], wave, lane, &cast);
   }
 }
 

@@ -32,13 +32,9 @@
 //      requests).  count_kernel sums the counts per slot in LDS first, so a
 //      slot named by many requests costs one device atomic per counter.
 #include "internal.h"
+#include "span.h"
 
 namespace hicr {
-
-typedef int32_t v4i __attribute__((ext_vector_type(4)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-// Global address space (1): plain global_load/global_store instead of flat.
-#define GLOBAL __attribute__((address_space(1)))
 
 // Cache policy of the body's buffer accesses (gfx950 bits: 1 = sc0, 2 = nt,
 // 16 = sc1).  Neither side is touched again by the copy, so the source is
@@ -48,26 +44,6 @@ constexpr int kLoadPolicy = 2;
 constexpr int kStorePolicy = 18;
 // Pieces of at most this many vector bytes take body_small.
 constexpr uint32_t kSmallPiece = 8192;
-
-// A buffer resource over [base, base + bytes): accesses at or past `bytes`
-// read zero and write nothing (the hardware's range check), which lets the
-// body run whole rounds without clamping its last one.  base and bytes are
-// the same in every lane; base may have any alignment (gfx950 runs the HSA
-// unaligned-access mode).
-__device__ __forceinline__ rsrc_t span_rsrc(uint64_t base, uint32_t bytes) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0,
-                                           (int)__builtin_amdgcn_readfirstlane(bytes),
-                                           0x00020000);
-}
-
-__device__ __forceinline__ v4i bload(rsrc_t r, uint32_t off) {
-  return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kLoadPolicy);
-}
-__device__ __forceinline__ void bstore(rsrc_t r, uint32_t off, v4i v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kStorePolicy);
-}
 
 // nb bytes (a multiple of 16) from rs to rd in rounds of U vector rows (1 KiB
 // per row), two rounds in flight: round k + 1 is loaded before round k is
@@ -79,16 +55,16 @@ __device__ __forceinline__ void body(rsrc_t rs, rsrc_t rd, uint32_t nb, uint32_t
   const uint32_t l16 = 16u * lane;
   v4i a[U], c[U];
 #pragma unroll
-  for (int k = 0; k < U; k++) a[k] = bload(rs, l16 + 1024u * k);
+  for (int k = 0; k < U; k++) a[k] = bload<kLoadPolicy>(rs, l16 + 1024u * k);
   for (uint32_t b = 0; b < nb; b += 2 * R) {
 #pragma unroll
-    for (int k = 0; k < U; k++) c[k] = bload(rs, b + R + l16 + 1024u * k);
+    for (int k = 0; k < U; k++) c[k] = bload<kLoadPolicy>(rs, b + R + l16 + 1024u * k);
 #pragma unroll
-    for (int k = 0; k < U; k++) bstore(rd, b + l16 + 1024u * k, a[k]);
+    for (int k = 0; k < U; k++) bstore<kStorePolicy>(rd, b + l16 + 1024u * k, a[k]);
 #pragma unroll
-    for (int k = 0; k < U; k++) a[k] = bload(rs, b + 2 * R + l16 + 1024u * k);
+    for (int k = 0; k < U; k++) a[k] = bload<kLoadPolicy>(rs, b + 2 * R + l16 + 1024u * k);
 #pragma unroll
-    for (int k = 0; k < U; k++) bstore(rd, b + R + l16 + 1024u * k, c[k]);
+    for (int k = 0; k < U; k++) bstore<kStorePolicy>(rd, b + R + l16 + 1024u * k, c[k]);
   }
 }
 

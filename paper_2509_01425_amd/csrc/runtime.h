@@ -6,6 +6,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <unordered_set>
 #include <vector>
 
 #include "hicr.h"
@@ -128,7 +129,7 @@ struct hicr_ctx_s {
   std::vector<hicr_desc> pending;
   hicr_sched def_sched{};
   hicr::SchedState *sched = nullptr;
-  std::vector<struct hicr_channel_s *> channels;
+  std::unordered_set<struct hicr_channel_s *> channels;
   std::vector<struct hicr_plan_s *> plans;
   std::map<uint64_t, hicr_dobj_handle> dobjs;  // published data objects by id
   uint64_t next_dobj_id = 1;
