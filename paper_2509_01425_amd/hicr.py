@@ -11,7 +11,9 @@ fallback: importing this module on a machine without the built library
 raises.
 """
 import ctypes
+import itertools
 import os
+import struct
 
 import numpy as np
 
@@ -66,6 +68,10 @@ class hicr_stream(ctypes.Structure):
     _fields_ = [("channel", ctypes.c_void_p), ("producer", ctypes.c_uint32),
                 ("src", ctypes.c_uint32), ("out", ctypes.c_uint32), ("pad", ctypes.c_uint32),
                 ("first_msg", ctypes.c_uint64), ("n_msgs", ctypes.c_uint64)]
+
+
+_STREAM = struct.Struct("=QIII4xQQ")  # a hicr_stream (native layout, padding zeroed)
+assert _STREAM.size == ctypes.sizeof(hicr_stream)
 
 
 class hicr_pump_io(ctypes.Structure):
@@ -382,9 +388,13 @@ def hicr_channel_pump(ctx, streams, msg_src_off, msg_size, trace_dev: int = 0, t
     """streams: sequence of (channel, producer, src_slot, out_slot, first_msg, n_msgs).
     msg_src_off / msg_size: host arrays, or device addresses (ints, with
     n_msgs given) for HICR_PUMP_DEVICE_TABLES."""
-    arr = (hicr_stream * max(len(streams), 1))()
-    for i, (ch, p, src, out, first, n) in enumerate(streams):
-        arr[i] = hicr_stream(ch, p, src, out, 0, first, n)
+    try:
+        packed = b"".join(itertools.starmap(_STREAM.pack, streams))
+        arr = ctypes.cast(packed, ctypes.POINTER(hicr_stream))
+    except struct.error:  # a value that only ctypes converts (None, a negative number)
+        arr = (hicr_stream * max(len(streams), 1))()
+        for i, (ch, p, src, out, first, n) in enumerate(streams):
+            arr[i] = hicr_stream(ch, p, src, out, 0, first, n)
     if isinstance(msg_src_off, int):
         io = hicr_pump_io(msg_src_off or None, msg_size or None, n_msgs, trace_dev or None,
                           ts_dev or None, timeout_ns, PUMP_DEVICE_TABLES, 0)
