@@ -15,16 +15,21 @@ static_assert(kMlpParams == 7052, "parameter count");
 
 // Activations and gradients of one mini-batch of B samples (device).
 struct MlpBufs {
-  float *a1, *h1, *a2, *h2, *z;  // pre-activations / activations / logits
-  float *dz, *d2, *d1;           // gradients w.r.t. z, a2, a1
-  float *loss;                   // per-sample loss
+  float *h1, *h2;       // activations
+  float *dz, *d2, *d1;  // gradients w.r.t. the logits and the two layers' pre-activations
+  float *loss;          // per-sample loss
 };
+constexpr size_t kMlpBufFloats = 4 * kMlpHidden + kMlpOut + 1;  // per sample
 
-hipError_t mlp_forward(const MlpBufs &m, const float *params, const float *X, int B,
-                       hipStream_t s);
-hipError_t mlp_backward(const MlpBufs &m, const float *params, const float *X, const int32_t *y,
-                        int B, float *grad, float *loss_mean, hipStream_t s);
-hipError_t mlp_adam(float *p, const float *g, float *m, float *v, float lr, int t, hipStream_t s);
+// logits z[B][12]
+hipError_t mlp_forward(const float *params, const float *X, uint32_t B, float *z, hipStream_t s);
+// gradient of the mean loss (and the mean loss, if loss_mean)
+hipError_t mlp_grad(const MlpBufs &m, const float *params, const float *X, const int32_t *y,
+                    uint32_t B, float *grad, float *loss_mean, hipStream_t s);
+// the t-th Adam step on that gradient (mo, ve: its moments)
+hipError_t mlp_step(const MlpBufs &m, float *params, float *mo, float *ve, const float *X,
+                    const int32_t *y, uint32_t B, float lr, int t, float *loss_mean,
+                    hipStream_t s);
 
 // Host mirror of the histogram feature: bin floor(log2 s) capped at 31,
 // size 0 in bin 0; feature log2(1 + count).

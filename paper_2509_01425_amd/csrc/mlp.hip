@@ -1,195 +1,253 @@
 // mlp.hip -- the schedule-predicting network on gfx950: 32 -> 64 -> 64 -> 12,
 // ReLU, softmax cross-entropy, Adam (Kingma & Ba 2015), all fp32.
 //
-// The network is tiny (7,052 parameters, ~14 kFLOP per sample): the forward,
-// input-gradient, loss and Adam kernels give one thread one output element,
-// the weight-gradient kernel one workgroup one output unit; every sum runs in
-// a fixed order, so the results are deterministic run to run.  Parameter layout (flat, row-major):
-// W1[64,32] b1[64] W2[64,64] b2[64] W3[12,64] b3[12].
+// The network is tiny (7,052 parameters, ~14 kFLOP per sample and direction),
+// so a step is bound by its launches and by the latency of each dependent
+// pass over memory, not by arithmetic: twelve launches (three layers, loss,
+// three weight gradients, two input gradients, mean loss, Adam, an event)
+// took 52 us a step at batch 256.  Now it is two: sample_kernel takes every
+// sample through the forward pass, the loss and the input gradients in one
+// wave with the weights in LDS, and weight_kernel sums each weight's gradient
+// over the batch and applies Adam to it: 16.5 us a step (5.8 and 5.5 us of
+// kernels).  Every sum runs in a fixed order, so the results are
+// deterministic run to run.  Parameter layout (flat, row-major): W1[64,32]
+// b1[64] W2[64,64] b2[64] W3[12,64] b3[12].
 //
 #include "internal.h"
 #include "mlp.h"
 
 namespace hicr {
 
-// Y[b,o] = bias[o] + sum_i W[o,i] X[b,i], summed from the bias in ascending
-// i (the host inference uses the same order); Yact gets the ReLU.  A
-// workgroup takes 256 / O samples and stages W transposed (rows padded to
-// O + 1, so neither the staging stores nor the loop's reads conflict in LDS)
-// and its samples' inputs: lanes then read consecutive W^T entries, where
-// reading row-major W directly was a stride-I access in every lane.
-constexpr int kFwdWords = kMlpHidden * (kMlpHidden + 1);
-constexpr int kFwdInputs = 2048;
-static_assert(kMlpIn * (kMlpHidden + 1) <= kFwdWords && kMlpHidden * (kMlpOut + 1) <= kFwdWords,
-              "every layer's W^T fits the LDS stage");
-static_assert((256 / kMlpHidden) * kMlpHidden <= kFwdInputs &&
-                  (256 / kMlpOut) * kMlpHidden <= kFwdInputs,
-              "every layer's sample inputs fit the LDS stage");
-__global__ __launch_bounds__(256) void dense_fwd_kernel(const float *X, const float *W,
-                                                        const float *bias, int I, int O, int B,
-                                                        float *Ypre, float *Yact) {
-  __shared__ float wt[kFwdWords];
-  __shared__ float xs[kFwdInputs];
-  const int t = threadIdx.x, S = 256 / O, P = O + 1;
-  const int b0 = blockIdx.x * S;
-  const int nS = B - b0 < S ? B - b0 : S;
-  for (int k = t; k < I * O; k += 256) wt[(k % I) * P + k / I] = W[k];
-  for (int k = t; k < nS * I; k += 256) xs[k] = X[b0 * I + k];
+constexpr int kB1 = kMlpHidden * kMlpIn, kW2 = kB1 + kMlpHidden,
+              kB2 = kW2 + kMlpHidden * kMlpHidden, kW3 = kB2 + kMlpHidden,
+              kB3 = kW3 + kMlpOut * kMlpHidden;
+static_assert(kB3 + kMlpOut == kMlpParams, "parameter layout");
+static_assert(kMlpHidden == 64 && kMlpIn <= 64 && kMlpOut <= 16, "one lane per unit of a layer");
+
+__device__ __forceinline__ float lane_of(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Stage W[O][I] transposed, row i of O + 1 floats: lanes that read one row
+// (the forward pass: lane = output) and lanes that read one column (the
+// backward pass: lane = input) then both hit every bank once.
+template <int I, int O>
+__device__ __forceinline__ void stage(float *t, const float *W) {
+  static_assert(I * O % 256 == 0, "whole rounds of the workgroup");
+#pragma unroll
+  for (int r = 0; r < I * O / 256; r++) {
+    const int k = r * 256 + threadIdx.x;
+    t[(k % I) * (O + 1) + k / I] = W[k];
+  }
+}
+
+// Output `lane` of a layer: bias + sum_i W[o,i] x_i, from the bias in
+// ascending i with fused multiply-adds (the host inference uses the same
+// order); x_i is lane i's x.
+template <int I, int O>
+__device__ __forceinline__ float dense(const float *t, float bias, float x, int o) {
+  float acc = bias;
+#pragma unroll
+  for (int i = 0; i < I; i++) acc = fmaf(t[i * (O + 1) + o], lane_of(x, i), acc);
+  return acc;
+}
+
+// Input gradient `lane`: sum_o dy_o W[o,i], ascending o.
+template <int O>
+__device__ __forceinline__ float dense_back(const float *t, float dy, int i) {
+  float acc = 0.f;
+#pragma unroll
+  for (int o = 0; o < O; o++) acc = fmaf(lane_of(dy, o), t[i * (O + 1) + o], acc);
+  return acc;
+}
+
+// One wave per sample, four samples to a workgroup, persistent over the
+// batch.  A workgroup stages the 28 KB of weights first (from the L2 after
+// the first few), which costs about as much as one sample's chain of
+// multiply-adds.  z gets the logits (forward only); with kTrain the
+// activations and gradients that weight_kernel needs, dZ = (p - onehot(y)) / B,
+// and the sample's cross-entropy log-sum-exp(z) - z_y.
+constexpr uint32_t kSampleGroups = 1024;
+template <bool kTrain>
+__global__ __launch_bounds__(256) void sample_kernel(const float *params, const float *X,
+                                                     const int32_t *y, uint32_t B, float *z_out,
+                                                     MlpBufs m) {
+  __shared__ float w1[kMlpIn * (kMlpHidden + 1)], w2[kMlpHidden * (kMlpHidden + 1)],
+      w3[kMlpHidden * (kMlpOut + 1)];
+  const int lane = threadIdx.x & 63;
+  const int lo = lane < kMlpOut ? lane : 0;  // the last layer has fewer units than lanes
+  const float b1 = params[kB1 + lane], b2 = params[kB2 + lane], b3 = params[kB3 + lo];
+  stage<kMlpIn, kMlpHidden>(w1, params);
+  stage<kMlpHidden, kMlpHidden>(w2, params + kW2);
+  stage<kMlpHidden, kMlpOut>(w3, params + kW3);
   __syncthreads();
-  const int sm = t / O, o = t % O;
-  if (sm >= nS) return;
-  float acc = bias[o];
-#pragma unroll 8
-  for (int i = 0; i < I; i++) acc = fmaf(wt[i * P + o], xs[sm * I + i], acc);
-  const int y = (b0 + sm) * O + o;
-  Ypre[y] = acc;
-  if (Yact) Yact[y] = acc > 0.f ? acc : 0.f;
-}
-
-// Per sample: softmax of the logits, dZ = (p - onehot(y)) / B, and the
-// sample's cross-entropy log-sum-exp(z) - z_y.
-__global__ __launch_bounds__(256) void softmax_xent_kernel(const float *Z, const int32_t *y,
-                                                           int B, float *dZ, float *loss) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= B) return;
-  const float *z = Z + b * kMlpOut;
-  float m = z[0];
-  for (int c = 1; c < kMlpOut; c++) m = fmaxf(m, z[c]);
-  float sum = 0.f;
-  for (int c = 0; c < kMlpOut; c++) sum += expf(z[c] - m);
-  // A label outside [0, kMlpOut) is never used as an index: the sample's loss
-  // is NaN (so a mean over the batch shows it) and it adds no gradient.
-  const int yb = y[b];
-  const bool valid = yb >= 0 && yb < kMlpOut;
-  for (int c = 0; c < kMlpOut; c++) {
-    const float p = expf(z[c] - m) / sum;
-    dZ[b * kMlpOut + c] = valid ? (p - (c == yb ? 1.f : 0.f)) / (float)B : 0.f;
+  for (size_t b = blockIdx.x * 4u + (threadIdx.x >> 6); b < B; b += gridDim.x * 4u) {
+    const float x = lane < kMlpIn ? X[b * kMlpIn + lane] : 0.f;
+    const float a1 = dense<kMlpIn, kMlpHidden>(w1, b1, x, lane);
+    const float h1 = a1 > 0.f ? a1 : 0.f;
+    const float a2 = dense<kMlpHidden, kMlpHidden>(w2, b2, h1, lane);
+    const float h2 = a2 > 0.f ? a2 : 0.f;
+    const float z = dense<kMlpHidden, kMlpOut>(w3, b3, h2, lo);
+    if (!kTrain) {
+      if (lane < kMlpOut) z_out[b * kMlpOut + lane] = z;
+      continue;
+    }
+    float mx = lane_of(z, 0), sum = 0.f;
+#pragma unroll
+    for (int c = 1; c < kMlpOut; c++) mx = fmaxf(mx, lane_of(z, c));
+    const float e = expf(z - mx);
+#pragma unroll
+    for (int c = 0; c < kMlpOut; c++) sum += lane_of(e, c);
+    // A label outside [0, kMlpOut) is never used as an index: the sample's loss
+    // is NaN (so a mean over the batch shows it) and it adds no gradient.
+    const int yb = y[b];
+    const bool valid = yb >= 0 && yb < kMlpOut;
+    const float dz = valid ? (e / sum - (lane == yb ? 1.f : 0.f)) / (float)(int)B : 0.f;
+    const float zy = __shfl(z, valid ? yb : 0);
+    const float d2 = a2 > 0.f ? dense_back<kMlpOut>(w3, dz, lane) : 0.f;
+    const float d1 = a1 > 0.f ? dense_back<kMlpHidden>(w2, d2, lane) : 0.f;
+    m.h1[b * kMlpHidden + lane] = h1;
+    m.h2[b * kMlpHidden + lane] = h2;
+    m.d1[b * kMlpHidden + lane] = d1;
+    m.d2[b * kMlpHidden + lane] = d2;
+    if (lane < kMlpOut) m.dz[b * kMlpOut + lane] = dz;
+    if (lane == 0) m.loss[b] = valid ? (mx + logf(sum)) - zy : __builtin_nanf("");
   }
-  if (loss) loss[b] = valid ? (m + logf(sum)) - z[yb] : __builtin_nanf("");
 }
 
-// dX[b,i] = (sum_o dY[b,o] W[o,i]) * [Xpre[b,i] > 0]
-__global__ __launch_bounds__(256) void dense_bwd_input_kernel(const float *dY, const float *W,
-                                                              const float *Xpre, int I, int O,
-                                                              int B, float *dX) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= B * I) return;
-  const int b = t / I, i = t % I;
-  float acc = 0.f;
-#pragma unroll 16
-  for (int o = 0; o < O; o++) acc = fmaf(dY[b * O + o], W[o * I + i], acc);
-  dX[t] = Xpre[t] > 0.f ? acc : 0.f;
-}
+struct WeightArgs {
+  const float *X;
+  MlpBufs m;
+  uint32_t B;
+  float *loss_mean;  // nullable
+  float *grad;       // gradients out, or (null) the Adam step below
+  float *p, *mo, *ve;
+  float lr, bc1, bc2;
+};
 
-// dW[o,i] = sum_b dY[b,o] X[b,i] and db[o] = sum_b dY[b,o], one workgroup
-// per output o (I <= 256).  256 / I threads share column i, each summing
-// every (256 / I)-th row, so a wavefront reads consecutive columns of a row
-// and every thread keeps many independent loads in flight (one thread per
-// weight walking all B rows left the kernel latency-bound on a few
-// workgroups).  Partial sums meet in LDS in a fixed order: the result does
-// not depend on timing.
-__global__ __launch_bounds__(256) void dense_bwd_weight_kernel(const float *dY, const float *X,
-                                                               int I, int O, int B, float *dW,
-                                                               float *db) {
-  __shared__ float part[256];
-  __shared__ float wsum[4];
-  const int o = blockIdx.x, t = threadIdx.x;
-  const int parts = 256 / I, i = t % I, p = t / I;
-  float acc = 0.f;
-  if (p < parts) {
-#pragma unroll 16
-    for (int b = p; b < B; b += parts) acc = fmaf(dY[b * O + o], X[b * I + i], acc);
+__device__ __forceinline__ void apply(const WeightArgs &a, int i, float g, float p, float mo,
+                                      float ve) {
+  if (a.grad) {
+    a.grad[i] = g;
+    return;
   }
+  constexpr float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  const float mi = b1 * mo + (1.f - b1) * g;
+  const float vi = b2 * ve + (1.f - b2) * g * g;
+  a.mo[i] = mi;
+  a.ve[i] = vi;
+  a.p[i] = p - a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + eps);
+}
+
+// Sum of v over the workgroup's 1,024 threads, in every thread; fixed order.
+__device__ __forceinline__ float group_sum(float v, float *wsum) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; w++) s += wsum[w];
+  return s;
+}
+
+// dW[o,i] = sum_b dY[b,o] X[b,i] and db[o] = sum_b dY[b,o] for one output o:
+// 1,024 / I threads share column i, each summing every (1,024 / I)-th sample,
+// so a wave reads consecutive columns and a thread's loads (16 at batch 256)
+// are all in flight at once; partial sums meet in LDS in a fixed order.
+template <int I, int O>
+__device__ __forceinline__ void weight_row(const WeightArgs &a, const float *dY, const float *X,
+                                           int w_base, int b_base, int o) {
+  __shared__ float part[1024];
+  __shared__ float wsum[16];
+  constexpr uint32_t kParts = 1024 / I;
+  const uint32_t t = threadIdx.x, i = t % I, q = t / I;
+  // threads 0..I-1 finish a weight each, thread I the bias
+  const int mine = t < I ? w_base + o * I + (int)t : b_base + o;
+  float p = 0.f, mo = 0.f, ve = 0.f;
+  if (!a.grad && t <= I) {
+    p = a.p[mine];
+    mo = a.mo[mine];
+    ve = a.ve[mine];
+  }
+  float acc = 0.f, bs = 0.f;
+#pragma unroll 16
+  for (size_t b = q; b < a.B; b += kParts) acc = fmaf(dY[b * O + o], X[b * I + i], acc);
+  for (size_t b = t; b < a.B; b += 1024) bs += dY[b * O + o];
   part[t] = acc;
-  float bs = 0.f;
-  for (int b = t; b < B; b += 256) bs += dY[b * O + o];
-  for (int off = 32; off > 0; off >>= 1) bs += __shfl_down(bs, off, 64);
-  if ((t & 63) == 0) wsum[t >> 6] = bs;
-  __syncthreads();
+  const float db = group_sum(bs, wsum);  // (its barrier also covers part[])
   if (t < I) {
     float sum = 0.f;
-    for (int q = 0; q < parts; q++) sum += part[q * I + t];
-    dW[o * I + t] = sum;
-  }
-  if (t == 0) db[o] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-}
-
-__global__ __launch_bounds__(256) void mean_kernel(const float *v, int n, float *out) {
-  __shared__ float part[256];
-  float acc = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) acc += v[i];
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < 256; i++) s += part[i];
-    *out = s / (float)n;
+#pragma unroll
+    for (uint32_t k = 0; k < kParts; k++) sum += part[k * I + t];
+    apply(a, mine, sum, p, mo, ve);
+  } else if (t == I) {
+    apply(a, mine, db, p, mo, ve);
   }
 }
 
-__global__ __launch_bounds__(256) void adam_kernel(float *p, const float *g, float *m, float *v,
-                                                   int n, float lr, float b1, float b2, float eps,
-                                                   float bc1, float bc2) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+// One workgroup per output unit of the three layers, and one for the mean loss.
+__global__ __launch_bounds__(1024) void weight_kernel(WeightArgs a) {
+  const int o = blockIdx.x;
+  if (o < kMlpHidden) {
+    weight_row<kMlpHidden, kMlpHidden>(a, a.m.d2, a.m.h1, kW2, kB2, o);
+  } else if (o < 2 * kMlpHidden) {
+    weight_row<kMlpIn, kMlpHidden>(a, a.m.d1, a.X, 0, kB1, o - kMlpHidden);
+  } else if (o < 2 * kMlpHidden + kMlpOut) {
+    weight_row<kMlpHidden, kMlpOut>(a, a.m.dz, a.m.h2, kW3, kB3, o - 2 * kMlpHidden);
+  } else {
+    __shared__ float wsum[16];
+    float acc = 0.f;
+    for (size_t b = threadIdx.x; b < a.B; b += 1024) acc += a.m.loss[b];
+    const float sum = group_sum(acc, wsum);
+    if (threadIdx.x == 0) *a.loss_mean = sum / (float)(int)a.B;
+  }
 }
 
-static_assert(kMlpIn <= 256 && kMlpHidden <= 256, "dense_bwd_weight_kernel spreads I columns over 256 threads");
+static inline uint32_t sample_groups(uint32_t B) {
+  return B / 4 >= kSampleGroups ? kSampleGroups : (B + 3) / 4;
+}
 
-static inline unsigned blocks(int n) { return (unsigned)((n + 255) / 256); }
-// workgroups of dense_fwd_kernel: 256 / O samples each
-static inline unsigned fwd_blocks(int B, int O) { return (unsigned)((B + 256 / O - 1) / (256 / O)); }
-
-hipError_t mlp_forward(const MlpBufs &m, const float *params, const float *X, int B,
-                       hipStream_t s) {
-  const float *W1 = params, *b1 = W1 + kMlpHidden * kMlpIn, *W2 = b1 + kMlpHidden,
-              *b2 = W2 + kMlpHidden * kMlpHidden, *W3 = b2 + kMlpHidden,
-              *b3 = W3 + kMlpOut * kMlpHidden;
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3(fwd_blocks(B, kMlpHidden)), dim3(256), 0, s, X, W1, b1,
-                     kMlpIn, kMlpHidden, B, m.a1, m.h1);
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3(fwd_blocks(B, kMlpHidden)), dim3(256), 0, s, m.h1, W2,
-                     b2, kMlpHidden, kMlpHidden, B, m.a2, m.h2);
-  hipLaunchKernelGGL(dense_fwd_kernel, dim3(fwd_blocks(B, kMlpOut)), dim3(256), 0, s, m.h2, W3, b3,
-                     kMlpHidden, kMlpOut, B, m.z, (float *)nullptr);
+hipError_t mlp_forward(const float *params, const float *X, uint32_t B, float *z, hipStream_t s) {
+  hipLaunchKernelGGL(sample_kernel<false>, dim3(sample_groups(B)), dim3(256), 0, s, params, X,
+                     (const int32_t *)nullptr, B, z, MlpBufs{});
   return hipGetLastError();
 }
 
-hipError_t mlp_backward(const MlpBufs &m, const float *params, const float *X, const int32_t *y,
-                        int B, float *grad, float *loss_mean, hipStream_t s) {
-  const float *W2 = params + kMlpHidden * kMlpIn + kMlpHidden;
-  const float *W3 = W2 + kMlpHidden * kMlpHidden + kMlpHidden;
-  float *gW1 = grad, *gb1 = gW1 + kMlpHidden * kMlpIn, *gW2 = gb1 + kMlpHidden,
-        *gb2 = gW2 + kMlpHidden * kMlpHidden, *gW3 = gb2 + kMlpHidden,
-        *gb3 = gW3 + kMlpOut * kMlpHidden;
-  hipLaunchKernelGGL(softmax_xent_kernel, dim3(blocks(B)), dim3(256), 0, s, m.z, y, B, m.dz,
-                     m.loss);
-  hipLaunchKernelGGL(dense_bwd_weight_kernel, dim3(kMlpOut), dim3(256),
-                     0, s, m.dz, m.h2, kMlpHidden, kMlpOut, B, gW3, gb3);
-  hipLaunchKernelGGL(dense_bwd_input_kernel, dim3(blocks(B * kMlpHidden)), dim3(256), 0, s, m.dz,
-                     W3, m.a2, kMlpHidden, kMlpOut, B, m.d2);
-  hipLaunchKernelGGL(dense_bwd_weight_kernel, dim3(kMlpHidden), dim3(256), 0, s, m.d2, m.h1,
-                     kMlpHidden, kMlpHidden, B, gW2, gb2);
-  hipLaunchKernelGGL(dense_bwd_input_kernel, dim3(blocks(B * kMlpHidden)), dim3(256), 0, s, m.d2,
-                     W2, m.a1, kMlpHidden, kMlpHidden, B, m.d1);
-  hipLaunchKernelGGL(dense_bwd_weight_kernel, dim3(kMlpHidden), dim3(256),
-                     0, s, m.d1, X, kMlpIn, kMlpHidden, B, gW1, gb1);
-  if (loss_mean) hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, s, m.loss, B, loss_mean);
+static hipError_t train(WeightArgs a, const float *params, const int32_t *y, hipStream_t s) {
+  hipLaunchKernelGGL(sample_kernel<true>, dim3(sample_groups(a.B)), dim3(256), 0, s, params, a.X,
+                     y, a.B, (float *)nullptr, a.m);
+  hipLaunchKernelGGL(weight_kernel, dim3(2 * kMlpHidden + kMlpOut + (a.loss_mean ? 1 : 0)),
+                     dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t mlp_adam(float *p, const float *g, float *mo, float *ve, float lr, int t,
+hipError_t mlp_grad(const MlpBufs &m, const float *params, const float *X, const int32_t *y,
+                    uint32_t B, float *grad, float *loss_mean, hipStream_t s) {
+  WeightArgs a{};
+  a.X = X;
+  a.m = m;
+  a.B = B;
+  a.loss_mean = loss_mean;
+  a.grad = grad;
+  return train(a, params, y, s);
+}
+
+hipError_t mlp_step(const MlpBufs &m, float *params, float *mo, float *ve, const float *X,
+                    const int32_t *y, uint32_t B, float lr, int t, float *loss_mean,
                     hipStream_t s) {
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float bc1 = 1.f - powf(b1, (float)t), bc2 = 1.f - powf(b2, (float)t);
-  hipLaunchKernelGGL(adam_kernel, dim3(blocks(kMlpParams)), dim3(256), 0, s, p, g, mo, ve,
-                     kMlpParams, lr, b1, b2, 1e-8f, bc1, bc2);
-  return hipGetLastError();
+  WeightArgs a{};
+  a.X = X;
+  a.m = m;
+  a.B = B;
+  a.loss_mean = loss_mean;
+  a.p = params;
+  a.mo = mo;
+  a.ve = ve;
+  a.lr = lr;
+  a.bc1 = 1.f - powf(0.9f, (float)t);
+  a.bc2 = 1.f - powf(0.999f, (float)t);
+  return train(a, params, y, s);
 }
 
 }  // namespace hicr

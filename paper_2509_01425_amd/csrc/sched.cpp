@@ -17,13 +17,13 @@
 namespace hicr {
 
 struct SchedState {
-  float *d_params = nullptr, *d_m = nullptr, *d_v = nullptr, *d_grad = nullptr;
-  float *d_loss = nullptr;
+  float *d_params = nullptr, *d_m = nullptr, *d_v = nullptr;
+  float *d_loss = nullptr;  // one mean loss, for a caller whose own place overlaps the inputs
   int step = 0;
   bool net_loaded = false;
   float *d_act = nullptr;  // activations of up to act_cap samples
-  float *d_x = nullptr;    // one feature, for the device inference of a plan's class
-  int act_cap = 0;
+  float *d_x = nullptr;    // one feature and its logits, for a plan's device inference
+  uint32_t act_cap = 0;
   MlpBufs bufs{};
   std::vector<std::array<float, kMlpIn>> feats;  // tuned table
   std::vector<uint32_t> cls;
@@ -62,8 +62,7 @@ static int state(hicr_ctx c, SchedState **out) {
     if (!s) return HICR_ENOMEM;
     const size_t pb = sizeof(float) * kMlpParams;
     bool ok = hipMalloc(&s->d_params, pb) == hipSuccess && hipMalloc(&s->d_m, pb) == hipSuccess &&
-              hipMalloc(&s->d_v, pb) == hipSuccess && hipMalloc(&s->d_grad, pb) == hipSuccess &&
-              hipMalloc(&s->d_loss, 64) == hipSuccess;
+              hipMalloc(&s->d_v, pb) == hipSuccess && hipMalloc(&s->d_loss, 64) == hipSuccess;
     c->sched = s;
     if (!ok) return fail(c, HICR_ENOMEM, "network state");
   }
@@ -71,27 +70,43 @@ static int state(hicr_ctx c, SchedState **out) {
   return HICR_OK;
 }
 
-static int ensure_act(hicr_ctx c, SchedState *s, int B) {
+static int ensure_act(hicr_ctx c, SchedState *s, uint32_t B) {
   if (B <= s->act_cap) return HICR_OK;
   if (s->d_act) (void)hipFree(s->d_act);
   s->d_act = nullptr;
   s->act_cap = 0;
-  const size_t per = 2 * kMlpHidden * 2 + kMlpOut * 2 + kMlpHidden * 2 + 1;  // floats/sample
-  if (hipMalloc(&s->d_act, sizeof(float) * per * B) != hipSuccess)
-    return fail(c, HICR_ENOMEM, "activations for %d samples", B);
+  if (hipMalloc(&s->d_act, sizeof(float) * kMlpBufFloats * B) != hipSuccess)
+    return fail(c, HICR_ENOMEM, "activations for %u samples", B);
   float *p = s->d_act;
   auto take = [&](int n) { float *q = p; p += (size_t)n * B; return q; };
-  s->bufs.a1 = take(kMlpHidden);
   s->bufs.h1 = take(kMlpHidden);
-  s->bufs.a2 = take(kMlpHidden);
   s->bufs.h2 = take(kMlpHidden);
-  s->bufs.z = take(kMlpOut);
   s->bufs.dz = take(kMlpOut);
   s->bufs.d2 = take(kMlpHidden);
   s->bufs.d1 = take(kMlpHidden);
   s->bufs.loss = take(1);
   s->act_cap = B;
   return HICR_OK;
+}
+
+static bool overlap(const void *p, size_t np, const void *q, size_t nq) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p), b = reinterpret_cast<uint64_t>(q);
+  return a < b + nq && b < a + np;
+}
+
+// Where a step's mean loss goes: straight to loss_dev, unless that lies in
+// memory the same launch reads or writes otherwise; then to d_loss, copied
+// from there once the launch has ended (put_loss).
+static float *loss_place(SchedState *s, float *loss_dev, const float *x, uint32_t B,
+                         const float *grad) {
+  if (!loss_dev) return nullptr;
+  const bool apart = !overlap(loss_dev, 4, x, sizeof(float) * kMlpIn * (size_t)B) &&
+                     !(grad && overlap(loss_dev, 4, grad, sizeof(float) * kMlpParams));
+  return apart ? loss_dev : s->d_loss;
+}
+static hipError_t put_loss(SchedState *s, const float *place, float *loss_dev, hipStream_t st) {
+  if (place != s->d_loss || !loss_dev) return hipSuccess;
+  return hipMemcpyAsync(loss_dev, s->d_loss, sizeof(float), hipMemcpyDeviceToDevice, st);
 }
 
 static double pivot_dist(const std::array<double, kMlpIn> &p, const float *f) {
@@ -203,18 +218,16 @@ static uint32_t net_class(const float *T, const float *x) {
 // parameters as they are on the device), read back and argmax-ed with ties to
 // the lowest class.
 static int device_class(hicr_ctx c, SchedState *s, const float *f, uint32_t *cls) {
-  int rc = ensure_act(c, s, 1);
-  if (rc != HICR_OK) return rc;
-  if (!s->d_x && hipMalloc(&s->d_x, sizeof(float) * kMlpIn) != hipSuccess) {
+  if (!s->d_x && hipMalloc(&s->d_x, sizeof(float) * (kMlpIn + kMlpOut)) != hipSuccess) {
     s->d_x = nullptr;
     return fail(c, HICR_ENOMEM, "network input");
   }
   static_assert(sizeof(float) * kMlpOut <= 64, "logits fit the read-back buffer");
   float *z = reinterpret_cast<float *>(c->h_read);
   hipError_t e = hipMemcpy(s->d_x, f, sizeof(float) * kMlpIn, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = mlp_forward(s->bufs, s->d_params, s->d_x, 1, c->stream);
+  if (e == hipSuccess) e = mlp_forward(s->d_params, s->d_x, 1, s->d_x + kMlpIn, c->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(z, s->bufs.z, sizeof(float) * kMlpOut, hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(z, s->d_x + kMlpIn, sizeof(float) * kMlpOut, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "network forward for a plan");
   uint32_t b = 0;
@@ -266,8 +279,8 @@ int choose_sched(hicr_ctx c, const hicr_desc *d, uint64_t n, uint32_t mode, hicr
 void destroy_sched(hicr_ctx c) {
   SchedState *s = c->sched;
   if (!s) return;
-  for (void *p : {(void *)s->d_params, (void *)s->d_m, (void *)s->d_v, (void *)s->d_grad,
-                  (void *)s->d_loss, (void *)s->d_act, (void *)s->d_x})
+  for (void *p : {(void *)s->d_params, (void *)s->d_m, (void *)s->d_v, (void *)s->d_loss,
+                  (void *)s->d_act, (void *)s->d_x})
     if (p) (void)hipFree(p);
   delete s;
   c->sched = nullptr;
@@ -337,12 +350,17 @@ int hicr_mlp_forward(hicr_ctx c, const float *x_dev, uint32_t batch, float *logi
     if (!c->sched || !c->sched->net_loaded) return fail(c, HICR_EINVAL, "no network loaded");
     (void)hipSetDevice(c->device);
     SchedState *s = c->sched;
-    int rc = ensure_act(c, s, (int)batch);
-    if (rc != HICR_OK) return rc;
-    hipError_t e = mlp_forward(s->bufs, s->d_params, x_dev, (int)batch, c->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(logits_dev, s->bufs.z, sizeof(float) * kMlpOut * batch,
-                         hipMemcpyDeviceToDevice, c->stream);
+    const size_t out = sizeof(float) * kMlpOut * batch;
+    float *z = logits_dev;
+    if (overlap(logits_dev, out, x_dev, sizeof(float) * kMlpIn * batch)) {
+      // logits over their own inputs: through a buffer
+      int rc = ensure_act(c, s, batch);
+      if (rc != HICR_OK) return rc;
+      z = s->bufs.h1;
+    }
+    hipError_t e = mlp_forward(s->d_params, x_dev, batch, z, c->stream);
+    if (e == hipSuccess && z != logits_dev)
+      e = hipMemcpyAsync(logits_dev, z, out, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? HICR_OK : hip_fail(c, e, "network forward");
   });
@@ -356,12 +374,11 @@ int hicr_mlp_grad(hicr_ctx c, const float *x_dev, const int32_t *y_dev, uint32_t
     if (!c->sched || !c->sched->net_loaded) return fail(c, HICR_EINVAL, "no network loaded");
     (void)hipSetDevice(c->device);
     SchedState *s = c->sched;
-    int rc = ensure_act(c, s, (int)batch);
+    int rc = ensure_act(c, s, batch);
     if (rc != HICR_OK) return rc;
-    hipError_t e = mlp_forward(s->bufs, s->d_params, x_dev, (int)batch, c->stream);
-    if (e == hipSuccess)
-      e = mlp_backward(s->bufs, s->d_params, x_dev, y_dev, (int)batch, grad_dev, loss_dev,
-                       c->stream);
+    float *loss = loss_place(s, loss_dev, x_dev, batch, grad_dev);
+    hipError_t e = mlp_grad(s->bufs, s->d_params, x_dev, y_dev, batch, grad_dev, loss, c->stream);
+    if (e == hipSuccess) e = put_loss(s, loss, loss_dev, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return e == hipSuccess ? HICR_OK : hip_fail(c, e, "network gradient");
   });
@@ -375,13 +392,13 @@ int hicr_mlp_train_step(hicr_ctx c, const float *x_dev, const int32_t *y_dev, ui
     if (!c->sched || !c->sched->net_loaded) return fail(c, HICR_EINVAL, "no network loaded");
     (void)hipSetDevice(c->device);
     SchedState *s = c->sched;
-    int rc = ensure_act(c, s, (int)batch);
+    int rc = ensure_act(c, s, batch);
     if (rc != HICR_OK) return rc;
-    hipError_t e = mlp_forward(s->bufs, s->d_params, x_dev, (int)batch, c->stream);
-    if (e == hipSuccess)
-      e = mlp_backward(s->bufs, s->d_params, x_dev, y_dev, (int)batch, s->d_grad, loss_dev,
-                       c->stream);
-    if (e == hipSuccess) e = mlp_adam(s->d_params, s->d_grad, s->d_m, s->d_v, lr, ++s->step, c->stream);
+    float *loss = loss_place(s, loss_dev, x_dev, batch, nullptr);
+    hipError_t e = mlp_step(s->bufs, s->d_params, s->d_m, s->d_v, x_dev, y_dev, batch, lr,
+                            s->step + 1, loss, c->stream);
+    if (e == hipSuccess) s->step++;
+    if (e == hipSuccess) e = put_loss(s, loss, loss_dev, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->push_ev, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "network training step");
     c->push_pending = true;
