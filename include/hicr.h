@@ -91,7 +91,11 @@ typedef struct {
  * request is spread over at least wgs_per_desc pieces (of at least 1 KiB)
  * when it is large enough; unroll sets the depth of the copy loop: a lane
  * moves rounds of 4 x unroll 16-byte vectors, two rounds in flight.  The
- * schedule never changes a byte of the result.
+ * schedule never changes a byte of the result.  (It sets how batches from
+ * about 256 MiB are copied; a smaller one of at most 4,096 requests into HBM
+ * is shared evenly among the wavefronts under every schedule, and launches
+ * over a scanned table use chunk_bytes and wgs_per_desc only to share out the
+ * batch.)
  * mode: HICR_SCHED_FIXED uses the fields as given; HICR_SCHED_TUNED looks the
  * batch up in the context's autotuned table; HICR_SCHED_LEARNED lets the
  * schedule network pick the class from the batch's size histogram: for a
@@ -131,8 +135,9 @@ int hicr_ctx_set_sched(hicr_ctx ctx, const hicr_sched *s);
  * CUs x this, capped by what fits).  0 (the default) picks by schedule: 4 for
  * chunks of 4 KiB or less, 1 for chunks above 16 KiB up to 32 KiB, otherwise
  * 2; at least 4 for a launch of more than 4,096 requests whose chunks are
- * 16 KiB or less or whose average request is under 16 KiB.  Never changes a
- * byte.
+ * 16 KiB or less or whose average request is under 16 KiB (but 64 KiB of the
+ * batch per workgroup); 1 for a batch that is shared evenly (see hicr_sched).
+ * Never changes a byte.
  * wgs_per_cu > 64 -> HICR_EINVAL. */
 int hicr_ctx_set_copy_grid(hicr_ctx ctx, uint32_t wgs_per_cu);
 /* Memory-space pairs memcpy accepts from now on (HICR_PAIR bits; default
@@ -169,10 +174,10 @@ int hicr_memcpy(hicr_ctx ctx, hicr_slot dst, uint64_t dst_off, hicr_slot src, ui
  * checked first; on the first invalid request nothing is enqueued, the code
  * of that request is returned and its index stored in *bad_index_or_null.
  * `descs` is copied before the call returns.  s_or_null NULL selects the
- * context default.  A batch of 8,192 requests or more is uploaded on a
- * private stream that `stream` waits for (so the upload overlaps earlier
- * copies); 16,384 or more are checked by several host threads.  A
- * submission stages through host memory and is not meant for HIP graph
+ * context default.  A batch of 8,192 requests or more behind others in
+ * flight is uploaded on a private stream that `stream` waits for (so the
+ * upload overlaps earlier copies); 16,384 or more are checked by several host
+ * threads.  A submission stages through host memory and is not meant for HIP graph
  * capture: persistent plans (below) are. */
 int hicr_memcpy_batch(hicr_ctx ctx, const hicr_desc *descs, uint64_t n,
                       const hicr_sched *s_or_null, void *stream, uint64_t *bad_index_or_null);

@@ -114,9 +114,9 @@ namespace hicr {
 
 int wait_extra(hicr_ctx c) {
   int rc = HICR_OK;
-  if (c->push_pending) {
-    hipError_t e = sync_event(c->push_ev);
-    c->push_pending = false;
+  if (c->push_done < c->push_seq) {
+    hipError_t e = wait_signal(c, c->push_sig);
+    c->push_done = c->push_seq;
     if (e != hipSuccess) rc = hip_fail(c, e, "waiting for channel pushes");
   }
   for (Extra &x : c->extra) {
@@ -130,11 +130,9 @@ int wait_extra(hicr_ctx c) {
 }
 
 bool extra_inflight(hicr_ctx c) {
-  if (c->push_pending) {
-    if (hipEventQuery(c->push_ev) == hipSuccess)
-      c->push_pending = false;
-    else
-      return true;
+  if (c->push_done < c->push_seq) {
+    if (!ended(c, c->push_sig)) return true;
+    c->push_done = c->push_seq;
   }
   for (Extra &x : c->extra)
     if (hipEventQuery(x.ev) != hipSuccess) return true;
@@ -145,8 +143,8 @@ void destroy_extra(hicr_ctx c) {
   wait_extra(c);
   for (hicr_channel ch : c->channels) free_channel(ch);
   c->channels.clear();
-  if (c->push_ev) (void)hipEventDestroy(c->push_ev);
-  c->push_ev = nullptr;
+  if (c->push_sig.ev) (void)hipEventDestroy(c->push_sig.ev);
+  c->push_sig.ev = nullptr;
 }
 
 }  // namespace hicr
@@ -284,9 +282,11 @@ int hicr_channel_push(hicr_channel ch, uint32_t producer, hicr_slot src, uint64_
     pa.publish = &ch->coord_dev[r].prod.w[0];
     pa.publish_value = h.tm + n_ent;
     hipError_t e = launch_push(pa, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->push_ev, c->stream);
+    if (e == hipSuccess) {
+      c->push_seq++;
+      e = mark(c, c->push_sig, c->stream);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "launching a channel push");
-    c->push_pending = true;
     for (uint64_t i = 0; i < n_ent; i++)
       h.ent[(h.tm + i) % ch->E] = ent_bytes | ((uint64_t)producer << 48);
     h.tm += n_ent;

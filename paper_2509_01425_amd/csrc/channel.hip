@@ -161,13 +161,6 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
   return ((uint64_t)__shfl((unsigned)(v >> 32), src) << 32) | (uint64_t)__shfl((unsigned)v, src);
 }
 
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ uint64_t uni64(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // A table entry that nothing writes while the kernel runs, at an index that
 // is the same in every lane: read through the scalar cache into scalar
 // registers (the compiler does so by itself only before the first store).
@@ -194,13 +187,6 @@ __device__ __forceinline__ uint64_t wave_scan(uint64_t v, uint32_t lane) {
   return v;
 }
 
-// Lane `lane` (uniform) of a 64-bit value held in every lane's registers.
-__device__ __forceinline__ uint64_t lane64(uint64_t v, uint32_t lane) {
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Store two words of one 16-byte unit with one access (lanes outside `on`
 // store nothing), so that whoever reads the first also finds the second.
 __device__ __forceinline__ void st_pair(uint64_t a, uint64_t w0, uint64_t w1, bool on) {
@@ -212,67 +198,10 @@ __device__ __forceinline__ void st_pair(uint64_t a, uint64_t w0, uint64_t w1, bo
   bstore<16>(span_rsrc(a, 16), on ? 0u : ~0u, v);
 }
 
-// Nothing the compiler sees moves across this point.
-__device__ __forceinline__ void order() { asm volatile("" ::: "memory"); }
-
-// Wait until this wave's memory accesses have completed: its agent-scope
-// stores are then visible to every other wave of the device.
-__device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// n bytes d <- s (uniform), at most kChunkBytes of destination lines.
-constexpr int kChunkRows = 4;  // 1 KiB rows
-constexpr uint32_t kChunkBytes = 1024u * kChunkRows;
-struct Chunk {
-  uint64_t d, s;
-  uint32_t n;
-};
-
-// Cache policies: ring accesses at agent scope (sc1), and nothing is used
-// again by the wave that touches it (nt).
 // Ring bytes are written without nt: the consumer reads most of them soon
 // after, and they then come from the memory-side cache (4.03 against 4.42 ms
 // a pass on the first configuration above; reading the ring without nt
 // 4.3-4.4 ms).
-constexpr int kAgent = 16;
-constexpr int kAgentStream = 18;
-constexpr int kReadStream = 2;
-
-// A chunk on its way: the 16-byte destination vectors of its rows, and in
-// lanes 0-15 the at most 15 bytes before the first, in lanes 16-31 the at
-// most 15 bytes after the last of them.  Loads and stores of what a chunk
-// does not have are out of the buffer resource's range: they read zero and
-// write nothing.  So a chunk costs the same instructions whatever its length
-// (also 0), and the compiler can count exactly which of them a store waits
-// for; with a branch around the loads it waits for all of them.
-template <int LP, int SP>
-struct Flight {
-  v4i v[kChunkRows];
-  uint32_t byte;
-  __device__ __forceinline__ static uint32_t head(const Chunk &c) {
-    const uint32_t h = (uint32_t)(-c.d) & 15u;
-    return h < c.n ? h : c.n;
-  }
-  // (lanes past the tail get offsets past the chunk by themselves)
-  __device__ __forceinline__ static uint32_t byte_off(const Chunk &c, uint32_t lane) {
-    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u);
-    const uint32_t h = lane < nh ? lane : ~0u;
-    return lane < 16 ? h : body + lane - 16;
-  }
-  __device__ __forceinline__ void load(const Chunk &c, uint32_t lane) {
-    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u), o = nh + 16 * lane;
-    const rsrc_t r = span_rsrc(c.s, body);
-    byte = bload8<LP>(span_rsrc(c.s, c.n), byte_off(c, lane));
-#pragma unroll
-    for (int k = 0; k < kChunkRows; k++) v[k] = bload<LP>(r, o + 1024u * k);
-  }
-  __device__ __forceinline__ void store(const Chunk &c, uint32_t lane) const {
-    const uint32_t nh = head(c), body = nh + ((c.n - nh) & ~15u), o = nh + 16 * lane;
-    const rsrc_t r = span_rsrc(c.d, body);
-#pragma unroll
-    for (int k = 0; k < kChunkRows; k++) bstore<SP>(r, o + 1024u * k, v[k]);
-    bstore8<SP>(span_rsrc(c.d, c.n), byte_off(c, lane), byte);
-  }
-};
 
 // j messages between a ring and other memory, as a sequence of chunks: lane l
 // holds message l's size, ring position (below P) and other address.  Chunks
@@ -314,28 +243,16 @@ struct Feed {
 // still be in flight.
 template <int WAVES, bool kToRing>
 __device__ __forceinline__ void move_feed(Feed<kToRing> f, uint32_t wave, uint32_t lane) {
-  typedef Flight<kToRing ? kReadStream : kAgentStream, kToRing ? kAgent : kAgentStream> F;
   f.l = 0;
   f.left = f.pos = f.addr = 0;
   if (WAVES > 1) f.skip(wave);
-  auto take = [&]() {
-    const Chunk c = f.next();
-    if (WAVES > 1) f.skip(WAVES - 1);
-    return c;
-  };
-  Chunk a = take();
-  if (a.n == 0) return;
-  F fa, fb;
-  fa.load(a, lane);
-  do {
-    const Chunk b = take();
-    fb.load(b, lane);
-    fa.store(a, lane);
-    a = take();
-    fa.load(a, lane);
-    fb.store(b, lane);
-  } while (a.n);
-  order();
+  move_chunks<kToRing ? kReadStream : kAgentStream, kToRing ? kAgent : kAgentStream>(
+      [&]() {
+        const Chunk c = f.next();
+        if (WAVES > 1) f.skip(WAVES - 1);
+        return c;
+      },
+      lane);
 }
 
 // What the first wave of a workgroup endpoint tells the others per batch.

@@ -1,36 +1,37 @@
 // copy.hip -- fused batched memcpy for gfx950 (CDNA4).
 //
-// One launch moves a batch of memcpy(dst, dstOff, src, srcOff, size)
-// requests (HiCR Sec. 3.1.4) with a persistent grid:
-//   1. the batch becomes one global index space of pieces: an inclusive
-//      prefix scan of the pieces per request.  A batch of at most 4,096
-//      requests is scanned by every workgroup into LDS (wavefront scans with
-//      __shfl_up, then a cross-wave carry); a larger one is scanned once, by
-//      scan_kernel, one workgroup per tile of 4,096 requests (the tile's
-//      prefix staged in LDS, written to device memory with the tile total),
-//      and every copy workgroup scans only the tile totals into LDS;
-//   2. every wavefront is an independent worker.  Against an LDS table,
-//      wave w of workgroup g takes pieces 4g + w, 4g + w + 4G, ... and finds
-//      each piece's request by a 64-ary ballot search (two ballots for 4,096
-//      requests).  Against the tiled table, every wavefront takes one
-//      contiguous range of pieces, searches once for its first request (tile,
-//      then request inside the tile) and walks forward request by request;
-//   3. a piece is copied by its wave with buffer loads (at whatever
-//      alignment the source has: gfx950 runs the HSA unaligned-access mode)
-//      and 16-byte destination-aligned buffer stores, both non-temporal;
-//      rounds of 4 x `unroll` 1 KiB rows, the next round's loads issued
-//      before the current round's stores (see copy_span); the at most 15
-//      bytes before the first and after the last aligned destination vector
-//      are copied byte by byte, so no store ever touches a byte outside the
-//      request;
-//   4. completion counting is a separate small kernel (count.hip) queued
-//      behind the copy launches of a submission on the same stream: the
-//      kernel boundary makes every copied byte visible before any counter
-//      rises, so the copy kernel needs no per-workgroup release (an
-//      agent-scope release writes back the whole L2 of the XCD, and one per
-//      workgroup cost more than the copy itself on batches of small
-//      requests).  count_kernel sums the counts per slot in LDS first, so a
-//      slot named by many requests costs one device atomic per counter.
+// One launch moves a batch of memcpy(dst, dstOff, src, srcOff, size) requests
+// (HiCR Sec. 3.1.4) with a persistent grid.  There are three, by the batch:
+//   stream_kernel    up to 4,096 requests and about 256 MiB: the host has cut
+//                    the batch into equal shares of bytes, one per wave;
+//   copy_kernel      up to 4,096 requests, larger: a global index space of
+//                    pieces, the inclusive prefix of the pieces per request
+//                    scanned by every workgroup into LDS (wavefront scans with
+//                    __shfl_up, then a cross-wave carry); wave w of workgroup
+//                    g takes pieces 4g + w, 4g + w + 4G, ... and finds each
+//                    piece's request by a 64-ary ballot search;
+//   copy_kernel_mem  more requests: the prefix is scanned once, by
+//                    scan_kernel, one workgroup per tile of 4,096 requests;
+//                    every wave takes one contiguous range of pieces, finds
+//                    where it starts and ends by the same search, and copies
+//                    it as a stream.
+// A piece of copy_kernel is copied with buffer loads (at whatever alignment
+// the source has: gfx950 runs the HSA unaligned-access mode) and 16-byte
+// destination-aligned buffer stores, both non-temporal, in rounds of
+// 4 x `unroll` 1 KiB rows, the next round's loads issued before the current
+// round's stores (see copy_span); a stream in chunks of 4 KiB of destination
+// lines (see Flight).  The at most 15 bytes before the first and after the
+// last aligned destination vector are copied byte by byte, so no store ever
+// touches a byte outside the request.
+//
+// Every store writes through to the device's coherence point (agent scope),
+// so a workgroup that has waited for its stores has nothing to write back and
+// can say that it has ended (signal_done): no counter kernel and no event
+// behind the copy.  (An agent-scope release in every workgroup, which stores
+// that stay in the L2 need, writes back the whole L2 of the XCD and cost more
+// than the copy itself on batches of small requests.)
+#include <algorithm>
+
 #include "internal.h"
 #include "span.h"
 
@@ -42,6 +43,11 @@ namespace hicr {
 // scope.
 constexpr int kLoadPolicy = 2;
 constexpr int kStorePolicy = 18;
+// Streamed ranges read with the plain policy: the rows of small or unaligned
+// requests share source lines with their neighbours, which the caches then
+// serve (halo exchange 145 us against 151 us read non-temporally; 8,192
+// requests of 256 B - 64 KiB 94-99 against 110 us a pass).
+constexpr int kPlainLoad = 0;
 // Pieces of at most this many vector bytes take body_small.
 constexpr uint32_t kSmallPiece = 8192;
 
@@ -68,26 +74,25 @@ __device__ __forceinline__ void body(rsrc_t rs, rsrc_t rd, uint32_t nb, uint32_t
   }
 }
 
-// Small pieces (a halo row, the tail of a request) with plain global
-// accesses: rounds of 4 vector rows, indices past the last vector clamped to
-// it (a repeated vector rewrites equal bytes), stores non-temporal.  On the
-// halo exchange (rows of 5,632 B) the buffer body took 159-168 us per
-// exchange against 154 us for this one.
+// Small pieces (the ends of large requests) with plain global loads: rounds of
+// 4 vector rows, indices past the last vector clamped to it (a repeated vector
+// rewrites equal bytes).
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef v4u v4u_any __attribute__((aligned(1)));  // 16 bytes at any alignment
 __device__ __forceinline__ void body_small(uint64_t d, uint64_t s, uint32_t nv, uint32_t lane) {
+  const rsrc_t rd = span_rsrc(d, 16 * nv);
   for (uint32_t b = 0; b < nv; b += 256) {
-    uint64_t o[4];
+    uint32_t o[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const uint32_t i = b + lane + 64u * k;
-      o[k] = 16ull * (i < nv ? i : nv - 1);
+      o[k] = 16 * (i < nv ? i : nv - 1);
     }
     v4u r[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) r[k] = *(const GLOBAL v4u_any *)(s + o[k]);
 #pragma unroll
-    for (int k = 0; k < 4; k++) __builtin_nontemporal_store(r[k], (GLOBAL v4u *)(d + o[k]));
+    for (int k = 0; k < 4; k++) bstore<kStorePolicy>(rd, o[k], (v4i)r[k]);
   }
 }
 
@@ -117,14 +122,22 @@ __device__ __forceinline__ void copy_span(uint64_t lo, uint64_t hi, uint64_t s, 
   // (lo and hi are the same in every lane: a piece without head or tail
   // bytes, such as an aligned row, skips the byte copy altogether)
   const bool bytes = (nh | nt) != 0;
-  unsigned char byte = 0;
+  uint32_t byte = 0;
   if (bytes) byte = *(const GLOBAL unsigned char *)(s + bo);
   const uint32_t nb = (uint32_t)(a1 - a0);
-  if (nb > kSmallPiece)
+  // (the empty asm takes the byte once per path: where the paths meet again
+  // the compiler would wait for everything in flight before it, the body's
+  // stores among it, which cost 1 % on a batch of 4,096 requests to 4 MiB)
+  if (nb > kSmallPiece) {
     body<U>(span_rsrc(s + nh, nb), span_rsrc(a0, nb), nb, lane);
-  else if (nb)
-    body_small(a0, s + nh, nb >> 4, lane);
-  if (bytes) *(GLOBAL unsigned char *)(lo + bo) = byte;
+    asm volatile("" : "+v"(byte));
+  } else {
+    if (nb) body_small(a0, s + nh, nb >> 4, lane);
+    asm volatile("" : "+v"(byte));
+  }
+  if (bytes)
+    __hip_atomic_store((GLOBAL unsigned char *)(lo + bo), (unsigned char)byte, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void copy_range(uint64_t lo, uint64_t hi, uint64_t s, uint32_t unroll,
@@ -202,7 +215,7 @@ __device__ __forceinline__ void block_scan(uint32_t *v, uint32_t m, uint32_t *ws
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kCopyBlock) void copy_kernel(DevBatch b, DevSched s) {
+__global__ __launch_bounds__(kCopyBlock) void copy_kernel(DevBatch b, DevSched s, Done done) {
   __shared__ uint32_t ends[kMaxLdsDescs];
   __shared__ uint32_t wsum[kCopyBlock / 64];
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -225,31 +238,47 @@ __global__ __launch_bounds__(kCopyBlock) void copy_kernel(DevBatch b, DevSched s
     const uint64_t dst = b.dst[i], src = b.src[i], size = b.size[i];
     copy_piece(dst, src, size, piece_len(dst, size, s.chunk, s.wgs), j, s.unroll, lane);
   }
+  signal_done(done);
 }
 
 // Table of a large batch, one workgroup per tile of kTile requests: the
 // tile's piece counts are loaded (all of a thread's loads in flight at
 // once), counted into LDS, scanned there, and written out as the tile's
 // inclusive prefix (relative to the tile's first piece) with the tile's
-// total in tile_tot[tile].
-__global__ __launch_bounds__(kScanBlock) void scan_kernel(DevBatch b, DevSched s, uint32_t *ends,
-                                                          uint32_t *tile_tot) {
+// total in tile_tot[tile].  With kStage the requests lie in pinned host
+// memory (`b`) and the kernel also moves them to device memory (`to`): the
+// same stream then needs no copy engine, whose start waits for a completion
+// signal of the kernel before it.
+template <bool kStage>
+__global__ __launch_bounds__(kScanBlock) void scan_kernel(DevBatch b, DevBatch to, DevSched s,
+                                                          uint32_t *ends, uint32_t *tile_tot) {
   constexpr int kPer = kTile / kScanBlock;
   __shared__ uint32_t cnt[kTile];
   __shared__ uint32_t wsum[kScanBlock / 64];
   const uint32_t tid = threadIdx.x;
   const uint32_t i0 = blockIdx.x * kTile, m = min(b.n - i0, kTile);
-  uint64_t dv[kPer], zv[kPer];
+  uint64_t dv[kPer], zv[kPer], sv[kPer], pv[kPer];
 #pragma unroll
   for (int r = 0; r < kPer; r++) {
     const uint32_t k = tid + r * kScanBlock;
     dv[r] = k < m ? b.dst[i0 + k] : 0;
     zv[r] = k < m ? b.size[i0 + k] : 0;
+    if (kStage) {
+      sv[r] = k < m ? b.src[i0 + k] : 0;
+      pv[r] = k < m ? b.slots[i0 + k] : 0;
+    }
   }
 #pragma unroll
   for (int r = 0; r < kPer; r++) {
     const uint32_t k = tid + r * kScanBlock;
-    if (k < m) cnt[k] = (uint32_t)piece_count(dv[r], zv[r], s.chunk, s.wgs);
+    if (k >= m) continue;
+    cnt[k] = (uint32_t)piece_count(dv[r], zv[r], s.chunk, s.wgs);
+    if (kStage) {
+      const_cast<uint64_t *>(to.dst)[i0 + k] = dv[r];
+      const_cast<uint64_t *>(to.src)[i0 + k] = sv[r];
+      const_cast<uint64_t *>(to.size)[i0 + k] = zv[r];
+      const_cast<uint64_t *>(to.slots)[i0 + k] = pv[r];
+    }
   }
   __syncthreads();
   block_scan<kScanBlock>(cnt, m, wsum);
@@ -257,85 +286,163 @@ __global__ __launch_bounds__(kScanBlock) void scan_kernel(DevBatch b, DevSched s
   if (tid == 0) tile_tot[blockIdx.x] = cnt[m - 1];
 }
 
+// Move `words` 8-byte words of pinned host memory to device memory.
+__global__ __launch_bounds__(kCopyBlock) void upload_kernel(const uint64_t *h, uint64_t *d,
+                                                            uint64_t words) {
+  for (uint64_t i = blockIdx.x * kCopyBlock + threadIdx.x; i < words; i += gridDim.x * kCopyBlock)
+    d[i] = h[i];
+}
+
+// Copy, with one wave, what the batch holds from byte `off` of request
+// `first` up to byte `end` of request `last` (0 of request n: to its end), as
+// one sequence of chunks: lane l holds request base + l, and the chunk
+// pipeline runs on from one request into the next.
+__device__ __forceinline__ void stream_range(const DevBatch &b, uint64_t first, uint64_t off,
+                                             uint64_t last, uint64_t end, uint32_t lane) {
+  for (uint64_t base = first; base <= last && base < b.n; base += 64) {
+    const uint64_t i = base + lane;
+    uint64_t v_d = 0, v_s = 0, v_n = 0;
+    if (i <= last && i < b.n) {
+      const uint64_t lo = i == first ? off : 0;
+      v_n = (i == last ? end : b.size[i]) - lo;
+      v_d = b.dst[i] + lo;
+      v_s = b.src[i] + lo;
+    }
+    const uint32_t j = (uint32_t)min(last + 1 - base, (uint64_t)64);
+    uint32_t l = 0;
+    uint64_t d = 0, s = 0, left = 0;
+    move_chunks<kPlainLoad, kStorePolicy>(
+        [&]() {
+          while (left == 0 && l < j) {
+            left = lane64(v_n, l);
+            d = lane64(v_d, l);
+            s = lane64(v_s, l);
+            l++;
+          }
+          const uint64_t line = kChunkBytes - (d & (kLineBytes - 1));
+          const Chunk c = {d, s,
+                           (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)min(line, left))};
+          left -= c.n;
+          d += c.n;
+          s += c.n;
+          return c;
+        },
+        lane);
+  }
+}
+
 // Copy against the tiled table in device memory.  Every workgroup first
 // scans the tile totals into LDS (at most kMaxTiles of them), so piece q's
 // global index is tile_base(tile) + local prefix.  Wavefront w of the W in
-// the grid takes pieces [total * w / W, total * (w + 1) / W), finds the
-// request of its first piece (64-ary search over the tile bases, then over
-// that tile's prefix) and walks forward from there: every request has at
-// least one piece, so the walk advances one request at a time, and the next
-// request's descriptor is loaded before the current piece is copied.
+// the grid takes pieces [total * w / W, total * (w + 1) / W): it finds the
+// request and byte where its first piece and the next wavefront's first piece
+// start (64-ary search over the tile bases, then over that tile's prefix) and
+// copies what lies between.
+__device__ __forceinline__ StreamStart piece_start(const DevBatch &b, const DevSched &s,
+                                                   const GLOBAL uint32_t *ends,
+                                                   const uint32_t *tiles, uint32_t nt, uint32_t q,
+                                                   uint32_t total, uint32_t lane) {
+  if (q >= total) return StreamStart{0, b.n};
+  const uint32_t t = __builtin_amdgcn_readfirstlane(find_piece_owner(tiles, nt, q, lane));
+  const uint32_t tb = t ? tiles[t - 1] : 0u, t0 = t * kTile;
+  const uint32_t i = t0 + __builtin_amdgcn_readfirstlane(find_piece_owner(
+                              ends + t0, min(b.n - t0, kTile), q - tb, lane));
+  const uint32_t j = q - (tb + (i > t0 ? ends[i - 1] : 0u));
+  const uint64_t dst = b.dst[i], size = b.size[i];
+  const uint64_t lo = (dst & ~(uint64_t)(kLineBytes - 1)) + j * piece_len(dst, size, s.chunk, s.wgs);
+  return StreamStart{j ? min(lo - dst, size) : 0, i};
+}
+
 __global__ __launch_bounds__(kCopyBlock) void copy_kernel_mem(DevBatch b, DevSched s,
                                                               const uint32_t *ends_in,
-                                                              const uint32_t *tile_tot) {
+                                                              const uint32_t *tile_tot, Done done) {
   __shared__ uint32_t tiles[kMaxTiles];
   __shared__ uint32_t wsum[kCopyBlock / 64];
   const GLOBAL uint32_t *ends = (const GLOBAL uint32_t *)ends_in;
   constexpr uint32_t kWaves = kCopyBlock / 64;
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t n = b.n, nt = (n + kTile - 1) / kTile;
+  const uint32_t nt = (b.n + kTile - 1) / kTile;
   for (uint32_t k = threadIdx.x; k < nt; k += kCopyBlock) tiles[k] = tile_tot[k];
   __syncthreads();
   block_scan<kCopyBlock>(tiles, nt, wsum);
   const uint64_t total = tiles[nt - 1];
   const uint64_t W = (uint64_t)gridDim.x * kWaves;
   const uint64_t gw = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
-  uint32_t q = (uint32_t)(total * gw / W);
-  const uint32_t q1 = (uint32_t)(total * (gw + 1) / W);
-  if (q >= q1) return;
-  const uint32_t t = __builtin_amdgcn_readfirstlane(find_piece_owner(tiles, nt, q, lane));
-  const uint32_t tb = t ? tiles[t - 1] : 0u, t0 = t * kTile;
-  uint32_t i = t0 + __builtin_amdgcn_readfirstlane(
-                        find_piece_owner(ends + t0, min(n - t0, kTile), q - tb, lane));
-  uint32_t start = tb + (i > t0 ? ends[i - 1] : 0u), end = tb + ends[i];
-  uint64_t dst = b.dst[i], src = b.src[i], size = b.size[i];
-  for (; q < q1; q++) {
-    // piece q + 1 in this range belongs to request i + 1 (< n, since
-    // q + 1 < total; checked anyway, so that no table content can send a
-    // wavefront past the batch): load its descriptor before copying piece q
-    const bool next = q + 1 < q1 && q + 1 >= end && i + 1 < n;
-    uint32_t nend = 0;
-    uint64_t ndst = 0, nsrc = 0, nsize = 0;
-    if (next) {
-      const uint32_t nt1 = (i + 1) / kTile;
-      nend = (nt1 ? tiles[nt1 - 1] : 0u) + ends[i + 1];
-      ndst = b.dst[i + 1];
-      nsrc = b.src[i + 1];
-      nsize = b.size[i + 1];
-    }
-    copy_piece(dst, src, size, piece_len(dst, size, s.chunk, s.wgs), q - start, s.unroll, lane);
-    if (next) {
-      i++;
-      start = end;
-      end = nend;
-      dst = ndst;
-      src = nsrc;
-      size = nsize;
-    }
+  const uint32_t q = (uint32_t)(total * gw / W), q1 = (uint32_t)(total * (gw + 1) / W);
+  if (q < q1) {
+    const StreamStart at = piece_start(b, s, ends, tiles, nt, q, (uint32_t)total, lane);
+    const StreamStart to = piece_start(b, s, ends, tiles, nt, q1, (uint32_t)total, lane);
+    stream_range(b, uni64(at.req), uni64(at.off), uni64(to.req), uni64(to.off), lane);
   }
+  signal_done(done);
 }
 
-hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, hipStream_t stream) {
-  if (b.n > kMaxLdsDescs || grid == 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyBlock), 0, stream, b, s);
+// A batch small enough not to need the piece kernels' order (stream_waves says
+// which) copied as one stream of bytes in equal shares, one per wave.  The
+// host has cut the shares, so nothing is scanned or searched here, and the
+// requests are read where they are: for a submission in pinned host memory,
+// each wave its own few, over the host link, which takes less than queuing an
+// upload in front (with upload, copy and counter kernels and an event: a
+// single 16 KiB request submit to fence 16.5 us, 256 requests to 8 KiB 19.4,
+// 512 requests to 1 MiB 57; now 10.7, 14.8 and 35 = 3.6 TB/s, its kernel
+// 26 us = 4.9 TB/s).  Bound: launch, host link and memory latencies below a
+// few MiB, HBM above.
+__global__ __launch_bounds__(kCopyBlock) void stream_kernel(DevBatch b, const StreamStart *starts,
+                                                            uint32_t waves, Done done) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t w =
+      __builtin_amdgcn_readfirstlane(blockIdx.x * (kCopyBlock / 64) + (threadIdx.x >> 6));
+  if (w < waves)
+    stream_range(b, uni64(starts[w].req), uni64(starts[w].off), uni64(starts[w + 1].req),
+                 uni64(starts[w + 1].off), lane);
+  signal_done(done);
+}
+
+hipError_t launch_stream(const DevBatch &b, const StreamStart *starts, uint32_t waves, Done done,
+                         hipStream_t stream) {
+  if (!waves || !starts) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(stream_kernel, dim3(stream_grid(waves)), dim3(kCopyBlock), 0, stream, b,
+                     starts, waves, done);
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const DevBatch &b, DevSched s, uint32_t *ends, uint32_t *tile_tot,
+hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, Done done,
                        hipStream_t stream) {
-  if (b.n == 0 || !ends || !tile_tot || (b.n + kTile - 1) / kTile > kMaxTiles)
+  if (b.n > kMaxLdsDescs || grid == 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyBlock), 0, stream, b, s, done);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan(const DevBatch *staged, const DevBatch &b, DevSched s, uint32_t *ends,
+                       uint32_t *tile_tot, hipStream_t stream) {
+  const uint32_t tiles = (b.n + kTile - 1) / kTile;
+  if (b.n == 0 || !ends || !tile_tot || tiles > kMaxTiles || (staged && staged->n != b.n))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(scan_kernel, dim3((b.n + kTile - 1) / kTile), dim3(kScanBlock), 0, stream, b,
-                     s, ends, tile_tot);
+  if (staged)
+    hipLaunchKernelGGL(scan_kernel<true>, dim3(tiles), dim3(kScanBlock), 0, stream, *staged, b, s,
+                       ends, tile_tot);
+  else
+    hipLaunchKernelGGL(scan_kernel<false>, dim3(tiles), dim3(kScanBlock), 0, stream, b, b, s, ends,
+                       tile_tot);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const void *h_dev, void *d, uint64_t bytes, hipStream_t stream) {
+  const uint64_t words = bytes / 8;
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(64, (words + kCopyBlock - 1) / kCopyBlock);
+  if (!words || bytes % 8) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(upload_kernel, dim3(grid), dim3(kCopyBlock), 0, stream,
+                     static_cast<const uint64_t *>(h_dev), static_cast<uint64_t *>(d), words);
   return hipGetLastError();
 }
 
 hipError_t launch_copy_mem(const DevBatch &b, DevSched s, const uint32_t *ends,
-                           const uint32_t *tile_tot, uint32_t grid, hipStream_t stream) {
+                           const uint32_t *tile_tot, uint32_t grid, Done done,
+                           hipStream_t stream) {
   if (b.n == 0 || !ends || !tile_tot || grid == 0 || (b.n + kTile - 1) / kTile > kMaxTiles)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(copy_kernel_mem, dim3(grid), dim3(kCopyBlock), 0, stream, b, s, ends,
-                     tile_tot);
+                     tile_tot, done);
   return hipGetLastError();
 }
 

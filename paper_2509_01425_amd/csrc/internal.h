@@ -5,11 +5,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "stream_plan.h"
+
 namespace hicr {
 
 constexpr int kCopyBlock = 256;         // threads per copy workgroup (4 waves)
 constexpr int kScanBlock = 1024;        // threads of the one scan workgroup
 constexpr uint32_t kMaxLdsDescs = 4096; // requests scanned into LDS by every copy workgroup
+static_assert(kMaxLdsDescs == kStreamMaxReqs, "a batch of more requests has its table in memory");
 constexpr uint32_t kTile = 4096;        // requests per tile of a scanned table
 constexpr uint32_t kMaxTiles = 4096;    // tiles per launch over a scanned table
 constexpr uint32_t kLineBytes = 128;    // interior piece boundaries are line aligned
@@ -24,6 +27,20 @@ struct DevBatch {
   const uint64_t *slots; // [n] dst_slot | (uint64_t)src_slot << 32
   uint32_t n;
 };
+
+// How a copy launch tells the host that it has ended.  Every workgroup waits
+// for its own stores, which write through to the device's coherence point;
+// then a launch of at most kDoneWords workgroups stores seq to one word of
+// pinned host memory per workgroup, and a larger one counts its workgroups in
+// *arrive (device memory, zero before and after every launch), the last of
+// them storing to words[0].  words null: no signal.
+constexpr uint32_t kDoneWords = 64;
+struct Done {
+  uint64_t *words = nullptr;
+  uint32_t *arrive = nullptr;
+  uint64_t seq = 0;
+};
+inline uint32_t done_words(uint32_t grid) { return grid <= kDoneWords ? grid : 1; }
 
 // Schedule as the kernel sees it.
 struct DevSched {
@@ -63,21 +80,31 @@ __host__ __device__ inline uint64_t piece_count(uint64_t dst, uint64_t size, uin
 
 // Launch the fused copy kernel over one sub-batch (n <= kMaxLdsDescs), piece
 // table scanned in LDS by every workgroup.
-hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, hipStream_t stream);
+hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, Done done, hipStream_t stream);
 // Scan the pieces of a batch (1 <= n <= kTile * kMaxTiles, fewer than 2^31
 // pieces) into a tiled table: ends[0, n) holds each tile's inclusive prefix
-// relative to the tile, tile_tot[0, ceil(n / kTile)) the tile totals.
-hipError_t launch_scan(const DevBatch &b, DevSched s, uint32_t *ends, uint32_t *tile_tot,
-                       hipStream_t stream);
+// relative to the tile, tile_tot[0, ceil(n / kTile)) the tile totals.  staged:
+// the requests lie there in pinned host memory, and are moved to b first.
+hipError_t launch_scan(const DevBatch *staged, const DevBatch &b, DevSched s, uint32_t *ends,
+                       uint32_t *tile_tot, hipStream_t stream);
+// Move bytes (a multiple of 8) of pinned host memory to device memory.
+hipError_t launch_upload(const void *h_dev, void *d, uint64_t bytes, hipStream_t stream);
 // Launch the copy kernel over a batch whose table launch_scan has written.
 hipError_t launch_copy_mem(const DevBatch &b, DevSched s, const uint32_t *ends,
-                           const uint32_t *tile_tot, uint32_t grid, hipStream_t stream);
+                           const uint32_t *tile_tot, uint32_t grid, Done done,
+                           hipStream_t stream);
+// Copy requests [0, n) as one stream of bytes shared evenly by `waves`
+// wavefronts: wave w moves what lies between starts[w] and starts[w + 1]
+// (starts[waves] = {0, n}).  dst, src, size and starts may lie in pinned host
+// memory.
+inline uint32_t stream_grid(uint32_t waves) { return (waves + kCopyBlock / 64 - 1) / (kCopyBlock / 64); }
+hipError_t launch_stream(const DevBatch &b, const StreamStart *starts, uint32_t waves, Done done,
+                         hipStream_t stream);
 // Raise the slot counters of n requests (slots[i] = dst | src << 32); queued
-// after the copy launches of the same requests on the same stream.  When the
-// launch is a single workgroup (n <= 1,024) and done is not null, the kernel
-// ends by storing seq to *done (pinned host memory) and *armed is set.
-hipError_t launch_count(const uint64_t *slots, uint64_t n, uint64_t *counters, hipStream_t stream,
-                        uint64_t *done = nullptr, uint64_t seq = 0, bool *armed = nullptr);
+// after the copy launches of the same requests on the same stream.
+inline uint32_t count_grid(uint64_t n) { return (uint32_t)((n + 1023) / 1024); }
+hipError_t launch_count(const uint64_t *slots, uint64_t n, uint64_t *counters, Done done,
+                        hipStream_t stream);
 // Workgroups of the copy kernel that one CU holds at once.
 int copy_occupancy(int *wgs_per_cu);
 

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -23,21 +24,26 @@ using namespace hicr;
 struct hicr_plan_s {
   hicr_ctx c = nullptr;
   uint64_t n = 0;
-  void *d = nullptr;          // device SoA {dst, src, size, slot pair} + piece tables, 40 B per request
+  // device: kHead bytes of head (the arrival counter), the SoA {dst, src, size,
+  // slot pair} (32 B per request), then the piece tables (8 B per request) or
+  // the stream kernel's starts
+  void *d = nullptr;
+  uint64_t *batch() const { return d ? static_cast<uint64_t *>(d) + kHead / 8 : nullptr; }
+  static constexpr size_t kHead = 128;
   std::vector<Seg> segs;      // copy launches of one replay
+  uint32_t waves = 0;         // waves of the stream kernel (0: the piece kernels)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;  // HICR_PLAN_GRAPH
   DevSched ds{};
-  hipEvent_t ev = nullptr;    // end of the last replay
+  Signal sig;                 // end of the last replay; seq counts the replays
   hipStream_t last = nullptr; // stream of the last replay
   bool launched = false;
   std::vector<hicr_slot> slots;  // distinct slots the requests name
-  // direct replays of a plan that writes device memory only and has one
-  // counter group: the pinned word their counter kernel stores the replay's
-  // number to, the number of the last replay, and whether it will be stored
-  uint64_t *h_done = nullptr;
-  uint64_t done_seq = 0;
-  bool done_armed = false;
+  // direct replays of a plan that writes device memory only: their copy
+  // launch raises sig's words, and a replay is counted in the slots here
+  // (sent and received per entry of `slots`)
+  bool host_count = false;
+  std::vector<uint64_t> n_sent, n_recv;
 };
 
 namespace {
@@ -45,20 +51,53 @@ namespace {
 void free_plan(hicr_plan p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
-  if (p->ev) (void)hipEventDestroy(p->ev);
+  if (p->sig.ev) (void)hipEventDestroy(p->sig.ev);
   if (p->d) (void)hipFree(p->d);
-  if (p->h_done) (void)hipHostFree(p->h_done);
+  if (p->sig.words) p->c->plan_words.push_back(p->sig.words);
   for (hicr_slot s : p->slots) p->c->slots[s].plan_refs--;
   delete p;
 }
 
+// Done words of a plan (pinned), from blocks the context keeps.
+hipError_t take_words(hicr_ctx c, uint64_t **out) {
+  if (c->plan_words.empty()) {
+    constexpr int kPlans = 16;
+    void *b = nullptr;
+    hipError_t e = hipHostMalloc(&b, 8 * kDoneWords * kPlans, hipHostMallocDefault);
+    if (e != hipSuccess) return e;
+    c->plan_blocks.push_back(b);
+    for (int i = 0; i < kPlans; i++)
+      c->plan_words.push_back(static_cast<uint64_t *>(b) + kDoneWords * i);
+  }
+  *out = c->plan_words.back();
+  c->plan_words.pop_back();
+  std::memset(*out, 0, 8 * kDoneWords);
+  return hipSuccess;
+}
+
+// The slots that requests name, each once, in ascending order.
+std::vector<hicr_slot> distinct_slots(hicr_ctx c, const hicr_desc *d, uint64_t n) {
+  std::vector<hicr_slot> sl;
+  if (c->slots.size() <= 16 * n) {  // few slots: mark them (no sort of 2 n ids)
+    std::vector<char> used(c->slots.size(), 0);
+    for (uint64_t i = 0; i < n; i++) used[d[i].dst_slot] = used[d[i].src_slot] = 1;
+    for (hicr_slot x = 0; x < used.size(); x++)
+      if (used[x]) sl.push_back(x);
+    return sl;
+  }
+  sl.reserve(2 * n);
+  for (uint64_t i = 0; i < n; i++) {
+    sl.push_back(d[i].dst_slot);
+    sl.push_back(d[i].src_slot);
+  }
+  std::sort(sl.begin(), sl.end());
+  sl.erase(std::unique(sl.begin(), sl.end()), sl.end());
+  return sl;
+}
+
 int wait_plan(hicr_ctx c, hicr_plan p) {
   if (!p->launched) return HICR_OK;
-  if (p->done_armed && wait_done(p->h_done, p->done_seq)) {
-    p->launched = false;
-    return HICR_OK;
-  }
-  hipError_t e = sync_event(p->ev);
+  hipError_t e = wait_signal(c, p->sig);
   p->launched = false;
   return e == hipSuccess ? HICR_OK : hip_fail(c, e, "waiting for a plan replay");
 }
@@ -79,13 +118,25 @@ int wait_plans(hicr_ctx c) {
 bool plans_inflight(hicr_ctx c) {
   for (hicr_plan p : c->plans) {
     if (!p->launched) continue;
-    if ((p->done_armed && __atomic_load_n(p->h_done, __ATOMIC_ACQUIRE) == p->done_seq) ||
-        hipEventQuery(p->ev) == hipSuccess)
-      p->launched = false;
-    else
-      return true;
+    if (!ended(c, p->sig)) return true;
+    p->launched = false;
   }
   return false;
+}
+
+void plans_unfinished(hicr_ctx c, uint32_t slot, uint64_t *sent, uint64_t *recv) {
+  for (hicr_plan p : c->plans) {
+    if (!p->host_count || !p->launched || ended(c, p->sig)) continue;
+    // replays run one after another and each raises the same words to its
+    // number, so the lowest word is the number of replays that have ended
+    uint64_t done = ~0ull;
+    for (uint32_t i = 0; i < p->sig.n_words; i++)
+      done = std::min(done, __atomic_load_n(&p->sig.words[i], __ATOMIC_ACQUIRE));
+    const size_t k = std::lower_bound(p->slots.begin(), p->slots.end(), slot) - p->slots.begin();
+    if (k == p->slots.size() || p->slots[k] != slot) continue;
+    *sent -= (p->sig.seq - done) * p->n_sent[k];
+    *recv -= (p->sig.seq - done) * p->n_recv[k];
+  }
 }
 
 void destroy_plans(hicr_ctx c) {
@@ -94,6 +145,9 @@ void destroy_plans(hicr_ctx c) {
     free_plan(p);
   }
   c->plans.clear();
+  for (void *b : c->plan_blocks) (void)hipHostFree(b);
+  c->plan_blocks.clear();
+  c->plan_words.clear();
 }
 
 }  // namespace hicr
@@ -130,45 +184,63 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
     if (!p) return HICR_ENOMEM;
     p->c = c;
     p->n = n;
-    std::vector<hicr_slot> sl;
-    sl.reserve(2 * n);
-    for (uint64_t i = 0; i < n; i++) {
-      sl.push_back(d[i].dst_slot);
-      sl.push_back(d[i].src_slot);
-    }
-    std::sort(sl.begin(), sl.end());
-    sl.erase(std::unique(sl.begin(), sl.end()), sl.end());
-    for (hicr_slot x : sl) c->slots[x].plan_refs++;
-    p->slots = sl;
+    p->slots = distinct_slots(c, d, n);
+    for (hicr_slot x : p->slots) c->slots[x].plan_refs++;
 
-    std::vector<uint64_t> h(4 * std::max<uint64_t>(n, 1));
-    pack_batch(c, d, n, h.data());
+    constexpr size_t kHeadWords = hicr_plan_s::kHead / 8;
+    std::vector<uint64_t> up(kHeadWords + 4 * n, 0);  // what goes to the device
+    uint64_t *h = up.data() + kHeadWords;
+    pack_batch(c, d, n, h);
     DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};
     p->ds = ds;
-    rc = split_batch(c, h.data(), h.data() + 2 * n, n, ds, p->segs);
+    rc = split_batch(c, h, h + 2 * n, n, ds, p->segs);
     if (rc != HICR_OK) {
       free_plan(p);
       return rc;
     }
+    // (a captured launch cannot number its replays: graphs count on the device)
+    p->host_count = n && !(flags & HICR_PLAN_GRAPH) && writes_device_only(c, d, n);
     hipStream_t cs = nullptr;
-    hipError_t e = hipEventCreateWithFlags(&p->ev, hipEventDisableTiming);
-    if (e == hipSuccess && n && n <= 1024 && !(flags & HICR_PLAN_GRAPH) &&
-        writes_device_only(c, d, n)) {
-      e = hipHostMalloc(&p->h_done, 64, hipHostMallocDefault);
-      if (e == hipSuccess) *p->h_done = 0;
+    hipError_t e = hipEventCreateWithFlags(&p->sig.ev, hipEventDisableTiming);
+    if (p->host_count) {
+      p->n_sent.assign(p->slots.size(), 0);
+      p->n_recv.assign(p->slots.size(), 0);
+      uint64_t bytes = 0;
+      for (uint64_t i = 0; i < n; i++) {
+        c->slots[d[i].src_slot].tmp_sent++;
+        c->slots[d[i].dst_slot].tmp_recv++;
+        bytes += d[i].size;
+      }
+      for (size_t k = 0; k < p->slots.size(); k++) {
+        Slot &x = c->slots[p->slots[k]];
+        p->n_sent[k] = x.tmp_sent;
+        p->n_recv[k] = x.tmp_recv;
+        x.tmp_sent = x.tmp_recv = 0;
+      }
+      p->waves = stream_waves(n, bytes, c->n_cu, c->grid_per_cu);
+      if (p->waves) {
+        static_assert(sizeof(StreamStart) == 16, "two words");
+        up.resize(up.size() + 2 * (p->waves + 1));
+        h = up.data() + kHeadWords;
+        stream_starts(h, h + 2 * n, n, bytes, p->waves, kLineBytes,
+                      reinterpret_cast<StreamStart *>(h + 4 * n));
+      }
+      if (e == hipSuccess) e = take_words(c, &p->sig.words);
     }
-    if (e == hipSuccess && n) e = hipMalloc(&p->d, batch_bytes(n));
-    if (e == hipSuccess && n) e = hipMemcpy(p->d, h.data(), n * 32, hipMemcpyHostToDevice);
+    if (e == hipSuccess && n)
+      e = hipMalloc(&p->d, std::max(hicr_plan_s::kHead + batch_bytes(n), up.size() * 8));
+    if (e == hipSuccess && n) e = hipMemcpy(p->d, up.data(), up.size() * 8, hipMemcpyHostToDevice);
+    p->sig.arrive = static_cast<uint32_t *>(p->d);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e != hipSuccess) {
       if (cs) (void)hipStreamDestroy(cs);
       free_plan(p);
       return hip_fail(c, e, "allocating a plan");
     }
-    const uint64_t *dd = static_cast<const uint64_t *>(p->d);
-    uint32_t *tables = n ? batch_tables(p->d, n) : nullptr;
+    const uint64_t *dd = p->batch();
+    uint32_t *tables = n ? batch_tables(p->batch(), n) : nullptr;
     // the piece tables are scanned once; every replay reads them
-    rc = launch_scans(c, dd, n, p->segs, ds, tables, cs);
+    if (!p->waves) rc = launch_scans(c, nullptr, dd, n, p->segs, ds, tables, cs);
     if (rc == HICR_OK) {
       e = hipStreamSynchronize(cs);
       if (e != hipSuccess) rc = hip_fail(c, e, "scanning a plan");
@@ -213,26 +285,33 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
     (void)hipSetDevice(c->device);
     hipStream_t s = stream ? static_cast<hipStream_t>(stream) : c->stream;
     hipError_t e = hipSuccess;
-    if (p->launched && s != p->last) e = hipStreamWaitEvent(s, p->ev, 0);
+    if (p->launched && s != p->last) {
+      e = ensure_event(c, p->sig);
+      if (e == hipSuccess) e = hipStreamWaitEvent(s, p->sig.ev, 0);
+    }
+    const uint64_t *dd = p->batch();
     if (e == hipSuccess && p->exec) {
       e = hipGraphLaunch(p->exec, s);
+      c->dev_counted = true;
+    } else if (e == hipSuccess && p->waves) {
+      const DevBatch b{dd, dd + p->n, dd + 2 * p->n, dd + 3 * p->n, (uint32_t)p->n};
+      e = launch_stream(b, reinterpret_cast<const StreamStart *>(dd + 4 * p->n), p->waves,
+                        arm(p->sig, stream_grid(p->waves)), s);
     } else if (e == hipSuccess && p->n) {
-      const uint64_t *dd = static_cast<const uint64_t *>(p->d);
-      // replays are ordered (same stream, or the wait above), so the word's
+      // replays are ordered (same stream, or the wait above), so the words'
       // last value is the last replay's
-      const uint64_t seq = p->done_seq + 1;
-      bool armed = false;
-      p->done_armed = false;
-      int rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->d, p->n), c->d_counters,
-                             s, p->h_done, seq, &armed);
+      if (!p->host_count) c->dev_counted = true;
+      int rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->batch(), p->n),
+                             p->host_count ? nullptr : c->d_counters, s,
+                             p->host_count ? &p->sig : nullptr);
       if (rc != HICR_OK) return rc;
-      if (armed) {
-        p->done_seq = seq;
-        p->done_armed = true;
-      }
     }
-    if (e == hipSuccess) e = hipEventRecord(p->ev, s);
+    if (e == hipSuccess) e = mark(c, p->sig, s);
     if (e != hipSuccess) return hip_fail(c, e, "launching a plan");
+    for (size_t k = 0; k < p->n_sent.size(); k++) {
+      c->slots[p->slots[k]].sent += p->n_sent[k];
+      c->slots[p->slots[k]].recv += p->n_recv[k];
+    }
     p->launched = true;
     p->last = s;
     return HICR_OK;

@@ -2,13 +2,16 @@
 // slot table, request validation, fused-batch submission and fences.
 //
 // Slots (HiCR Sec. 3.1.3) live in a host table; requests are validated on
-// the host and resolved to absolute device addresses, packed as a structure
-// of arrays into pinned staging, uploaded with one asynchronous copy and
-// moved by one fused copy launch per (at most 4,096-request) sub-batch.
-// Per-slot counters live in device memory and are raised by the copy kernel.
+// the host, resolved to absolute device addresses and packed as a structure
+// of arrays into pinned staging.  A small batch is copied by one launch that
+// reads them there; a larger one is moved to device memory by a kernel in
+// front and copied by one fused launch.  The last launch raises words in
+// pinned memory that the fence polls, and the requests are counted in the host
+// table (many-request batches: by a counter kernel, in device memory).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <functional>
@@ -74,8 +77,10 @@ int check_desc(hicr_ctx c, const hicr_desc &d) {
   return HICR_OK;
 }
 
-static uint64_t *sub_done_word(hicr_ctx c, const Sub &s) {
-  return c->h_done + 8 * (uint64_t)(&s - c->subs);
+// A submission has ended: so has what was queued on its stream before it.
+static void sub_ended(hicr_ctx c, Sub &s) {
+  s.inflight = false;
+  c->push_done = std::max(c->push_done, s.push_seq);
 }
 
 bool any_inflight(hicr_ctx c) {
@@ -85,15 +90,12 @@ bool any_inflight(hicr_ctx c) {
     else
       return true;
   }
+  bool any = false;
   for (Sub &s : c->subs) {
-    if (!s.inflight) continue;
-    if ((s.done_seq && __atomic_load_n(sub_done_word(c, s), __ATOMIC_ACQUIRE) == s.done_seq) ||
-        hipEventQuery(s.ev) == hipSuccess)
-      s.inflight = false;
-    else
-      return true;
+    if (s.inflight && ended(c, s.sig)) sub_ended(c, s);
+    any = any || s.inflight;
   }
-  return false;
+  return any;
 }
 
 hipError_t sync_event(hipEvent_t e) {
@@ -109,13 +111,41 @@ hipError_t sync_event(hipEvent_t e) {
   return hipEventSynchronize(e);
 }
 
-bool wait_done(const uint64_t *w, uint64_t seq) {
-  const auto t0 = std::chrono::steady_clock::now();
-  for (uint32_t k = 0;; k++) {
-    if (__atomic_load_n(w, __ATOMIC_ACQUIRE) == seq) return true;
-    if ((k & 63) == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200))
-      return false;
+hipError_t mark(hicr_ctx c, Signal &sig, hipStream_t s) {
+  sig.recorded = !(c->own_stream && s == c->stream);
+  return sig.recorded ? hipEventRecord(sig.ev, s) : hipSuccess;
+}
+
+hipError_t ensure_event(hicr_ctx c, Signal &sig) {
+  if (sig.recorded) return hipSuccess;
+  const hipError_t e = hipEventRecord(sig.ev, c->stream);
+  if (e == hipSuccess) sig.recorded = true;
+  return e;
+}
+
+static bool raised(const Signal &sig) {
+  for (uint32_t i = 0; i < sig.n_words; i++)
+    if (__atomic_load_n(&sig.words[i], __ATOMIC_ACQUIRE) != sig.seq) return false;
+  return sig.n_words != 0;
+}
+
+bool ended(hicr_ctx c, Signal &sig) {
+  if (raised(sig)) return true;
+  if (sig.n_words && !sig.recorded) return false;
+  return ensure_event(c, sig) == hipSuccess && hipEventQuery(sig.ev) == hipSuccess;
+}
+
+hipError_t wait_signal(hicr_ctx c, Signal &sig) {
+  if (sig.n_words) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t k = 0;; k++) {
+      if (raised(sig)) return hipSuccess;
+      if ((k & 15) == 15 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200))
+        break;
+    }
   }
+  const hipError_t e = ensure_event(c, sig);
+  return e == hipSuccess ? sync_event(sig.ev) : e;
 }
 
 bool writes_device_only(hicr_ctx c, const hicr_desc *d, uint64_t n) {
@@ -124,17 +154,10 @@ bool writes_device_only(hicr_ctx c, const hicr_desc *d, uint64_t n) {
   return true;
 }
 
-// A submission that raises a done word has ended once the word holds its
-// value (the event completes ~5 us later on gfx950 with ROCm 7); otherwise,
-// or if the word is late, the event decides.
 int wait_sub(hicr_ctx c, Sub &s) {
   if (!s.inflight) return HICR_OK;
-  if (s.done_seq && wait_done(sub_done_word(c, s), s.done_seq)) {
-    s.inflight = false;
-    return HICR_OK;
-  }
-  hipError_t e = sync_event(s.ev);
-  s.inflight = false;
+  hipError_t e = wait_signal(c, s.sig);
+  sub_ended(c, s);
   if (e != hipSuccess) return hip_fail(c, e, "waiting for a batch");
   return HICR_OK;
 }
@@ -158,29 +181,48 @@ int wait_all(hicr_ctx c) {
   return rc;
 }
 
-static int ensure_capacity(hicr_ctx c, Sub &s, uint64_t n) {
-  if (n <= s.cap) return HICR_OK;
-  uint64_t cap = std::max<uint64_t>(n, std::max<uint64_t>(2 * s.cap, 4096));
-  if (s.h) (void)hipHostFree(s.h);
-  if (s.d) (void)hipFree(s.d);
+// Room for n requests in a submission buffer's staging, and on the device
+// (for the piece kernels).
+static uint64_t grown(uint64_t cap, uint64_t n) {
+  return std::max<uint64_t>(n, std::max<uint64_t>(2 * cap, 4096));
+}
+static int ensure_staging(hicr_ctx c, Sub &s, uint64_t n) {
+  if (n <= s.h_cap) return HICR_OK;
+  const uint64_t cap = grown(s.h_cap, n);
+  if (s.h && s.h_cap > kStageReqs) (void)hipHostFree(s.h);
   s.h = nullptr;
-  s.d = nullptr;
-  s.cap = 0;
-  hipError_t e = hipHostMalloc(&s.h, cap * 32, hipHostMallocDefault);
+  s.h_cap = 0;
+  hipError_t e = hipHostMalloc(&s.h, stage_bytes(cap), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(&s.h_dev, s.h, 0);
   if (e != hipSuccess) return fail(c, HICR_ENOMEM, "pinned staging of %llu requests", (unsigned long long)cap);
-  e = hipMalloc(&s.d, batch_bytes(cap));
-  if (e != hipSuccess) return fail(c, HICR_ENOMEM, "device batch buffer of %llu requests", (unsigned long long)cap);
-  s.cap = cap;
+  s.h_cap = cap;
+  return HICR_OK;
+}
+static int ensure_device(hicr_ctx c, Sub &s, uint64_t n) {
+  if (n <= s.d_cap) return HICR_OK;
+  const uint64_t cap = grown(s.d_cap, n);
+  if (s.d) (void)hipFree(s.d);
+  s.d = nullptr;
+  s.d_cap = 0;
+  if (hipMalloc(&s.d, batch_bytes(cap)) != hipSuccess) {
+    s.d = nullptr;
+    return fail(c, HICR_ENOMEM, "device batch buffer of %llu requests", (unsigned long long)cap);
+  }
+  s.d_cap = cap;
   return HICR_OK;
 }
 
 // The counter table is allocated once, for kMaxSlots slots (16 MiB), so its
-// address never changes: captured plans keep a valid pointer to it.
+// address never changes: captured plans keep a valid pointer to it.  The
+// submission buffers' arrival counters lie behind it.
 static int alloc_counters(hicr_ctx c) {
-  hipError_t e = hipMalloc(&c->d_counters, (size_t)kMaxSlots * 16);
-  if (e == hipSuccess) e = hipMemset(c->d_counters, 0, (size_t)kMaxSlots * 16);
+  const size_t bytes = (size_t)kMaxSlots * 16 + 128 * kNumSubs;
+  hipError_t e = hipMalloc(&c->d_counters, bytes);
+  if (e == hipSuccess) e = hipMemset(c->d_counters, 0, bytes);
   if (e != hipSuccess) return hip_fail(c, e, "allocating the counter table");
   c->counter_cap = kMaxSlots;
+  for (int i = 0; i < kNumSubs; i++)
+    c->subs[i].sig.arrive = reinterpret_cast<uint32_t *>(c->d_counters + 2 * (size_t)kMaxSlots) + 32 * i;
   return HICR_OK;
 }
 
@@ -250,66 +292,74 @@ static DevBatch seg_batch(const uint64_t *dd, uint64_t n, const Seg &g) {
                   (uint32_t)(g.i1 - g.i0)};
 }
 
-int launch_scans(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
-                 DevSched ds, uint32_t *tables, hipStream_t stream) {
+int launch_scans(hicr_ctx c, const uint64_t *staged, const uint64_t *dd, uint64_t n,
+                 const std::vector<Seg> &segs, DevSched ds, uint32_t *tables, hipStream_t stream) {
   for (const Seg &g : segs) {
     if (g.lds) continue;
-    hipError_t e = launch_scan(seg_batch(dd, n, g), ds, tables + g.i0, tables + n + g.i0, stream);
+    DevBatch from;
+    if (staged) from = seg_batch(staged, n, g);
+    hipError_t e = launch_scan(staged ? &from : nullptr, seg_batch(dd, n, g), ds, tables + g.i0,
+                               tables + n + g.i0, stream);
     if (e != hipSuccess) return hip_fail(c, e, "launching the scan kernel");
   }
   return HICR_OK;
 }
 
+static int launch_counts(hicr_ctx c, const uint64_t *dd, uint64_t n, uint64_t *counters,
+                         hipStream_t stream, Signal *sig) {
+  if (!counters || !n) return HICR_OK;
+  Done done;
+  if (sig) done = arm(*sig, count_grid(n));
+  hipError_t e = launch_count(dd + 3 * n, n, counters, done, stream);
+  return e == hipSuccess ? HICR_OK : hip_fail(c, e, "launching the counter kernel");
+}
+
 int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
                   DevSched ds, const uint32_t *tables, uint64_t *counters, hipStream_t stream,
-                  uint64_t *done, uint64_t seq, bool *armed) {
-  if (armed) *armed = false;
+                  Signal *sig) {
   const int per_cu_class = c->grid_per_cu > 0 ? c->grid_per_cu : default_grid_per_cu(ds);
   for (const Seg &g : segs) {
     // A launch over a scanned table whose pieces average under 16 KiB (a
-    // halo exchange's rows) is latency-bound: four groups per CU measured
-    // 1.45x faster than one at unroll 4.  (With an LDS table every group
-    // re-scans the batch, so more groups cost more there.)
+    // halo exchange's rows) takes four groups per CU: 151.6 us an exchange
+    // against 153.4 with two, 149.6 with eight.  (With an LDS table every
+    // group re-scans the batch, so more groups cost more there.)
     int per_cu = per_cu_class;
     if (c->grid_per_cu == 0 && !g.lds &&
         (ds.chunk <= (16u << 10) || g.bytes < (g.i1 - g.i0) * (16u << 10)))
       per_cu = std::max(per_cu, 4);
-    per_cu = std::min(per_cu, c->occ);
-    const uint64_t cap_grid = (uint64_t)c->n_cu * (uint64_t)per_cu;
+    if (g.lds) per_cu = std::min(per_cu, c->occ);
+    uint64_t cap_grid = (uint64_t)c->n_cu * (uint64_t)per_cu;
+    // ... of at least 16 KiB a wavefront (7,744 rows of 2,816 B: 19 us a replay
+    // that way, 24 us with four groups per CU)
+    if (c->grid_per_cu == 0 && !g.lds) cap_grid = std::min(cap_grid, std::max<uint64_t>(1, g.bytes >> 16));
     // every wavefront of a workgroup copies its own pieces
     const uint64_t want = (g.pieces + kCopyBlock / 64 - 1) / (kCopyBlock / 64);
     const uint32_t grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 1), cap_grid);
-    hipError_t e = g.lds ? launch_copy(seg_batch(dd, n, g), ds, grid, stream)
+    // the last launch of the submission tells of its end (the launches of one
+    // stream run one after another)
+    Done done;
+    if (sig && !counters && &g == &segs.back()) done = arm(*sig, grid);
+    hipError_t e = g.lds ? launch_copy(seg_batch(dd, n, g), ds, grid, done, stream)
                          : launch_copy_mem(seg_batch(dd, n, g), ds, tables + g.i0,
-                                           tables + n + g.i0, grid, stream);
+                                           tables + n + g.i0, grid, done, stream);
     if (e != hipSuccess) return hip_fail(c, e, "launching the copy kernel");
   }
-  if (counters && n) {
-    hipError_t e = launch_count(dd + 3 * n, n, counters, stream, done, seq, armed);
-    if (e != hipSuccess) return hip_fail(c, e, "launching the counter kernel");
-  }
-  return HICR_OK;
-}
-
-void pack_batch(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t *h) {
-  uint64_t *hd = h, *hs = h + n, *hz = h + 2 * n, *hp = h + 3 * n;
-  for (uint64_t i = 0; i < n; i++) {
-    hd[i] = c->slots[d[i].dst_slot].base + d[i].dst_off;
-    hs[i] = c->slots[d[i].src_slot].base + d[i].src_off;
-    hz[i] = d[i].size;
-    hp[i] = (uint64_t)d[i].dst_slot | ((uint64_t)d[i].src_slot << 32);
-  }
+  return launch_counts(c, dd, n, counters, stream, sig);
 }
 
 // Host threads for batches large enough that validating and packing them on
 // one core would take longer than their copy (a halo exchange: 61,952
-// requests, ~186 us on one core).  run(f) calls f(part) for every part in
-// [0, size()), part 0 on the calling thread, and returns when all are done.
+// requests, 130 us on one core).  run(blocks, f) calls f(block) for every block
+// in [0, blocks) and returns when all are done.  The calling thread takes
+// blocks from the start; a pool thread joins in once it is awake (50-100 us
+// after it is called) and is not waited for if nothing is left by then:
+// the halo exchange 326 us a pass with three threads waited for, 307 with three
+// that join in, 257 with seven, 336 without any.
 class HostPool {
  public:
   explicit HostPool(int extra) {
     try {
-      for (int i = 0; i < extra; i++) th_.emplace_back([this, i] { loop(i + 1); });
+      for (int i = 0; i < extra; i++) th_.emplace_back([this] { loop(); });
     } catch (...) {
       stop();  // join the threads already started, then report the failure
       throw;
@@ -317,18 +367,19 @@ class HostPool {
   }
   ~HostPool() { stop(); }
   int size() const { return (int)th_.size() + 1; }
-  void run(const std::function<void(int)> &f) {
+  void run(uint32_t blocks, const std::function<void(uint32_t)> &f) {
     {
       std::lock_guard<std::mutex> g(m_);
       f_ = &f;
-      left_ = (int)th_.size();
+      blocks_ = blocks;
+      next_ = 0;
       gen_++;
     }
     cv_.notify_all();
-    f(0);
+    work(f, blocks);
     std::unique_lock<std::mutex> g(m_);
-    done_.wait(g, [&] { return left_ == 0; });
-    f_ = nullptr;
+    f_ = nullptr;  // who wakes up from here on finds nothing to do
+    done_.wait(g, [&] { return active_ == 0; });
   }
 
  private:
@@ -341,28 +392,34 @@ class HostPool {
     for (std::thread &t : th_)
       if (t.joinable()) t.join();
   }
-  void loop(int part) {
+  void work(const std::function<void(uint32_t)> &f, uint32_t blocks) {
+    for (uint32_t b; (b = next_.fetch_add(1, std::memory_order_relaxed)) < blocks;) f(b);
+  }
+  void loop() {
     uint64_t seen = 0;
+    std::unique_lock<std::mutex> g(m_);
     for (;;) {
-      const std::function<void(int)> *f;
-      {
-        std::unique_lock<std::mutex> g(m_);
-        cv_.wait(g, [&] { return quit_ || gen_ != seen; });
-        if (quit_) return;
-        seen = gen_;
-        f = f_;
-      }
-      (*f)(part);
-      std::lock_guard<std::mutex> g(m_);
-      if (--left_ == 0) done_.notify_one();
+      cv_.wait(g, [&] { return quit_ || gen_ != seen; });
+      if (quit_) return;
+      seen = gen_;
+      if (!f_) continue;
+      const std::function<void(uint32_t)> &f = *f_;
+      const uint32_t blocks = blocks_;
+      active_++;
+      g.unlock();
+      work(f, blocks);
+      g.lock();
+      if (--active_ == 0) done_.notify_one();
     }
   }
   std::vector<std::thread> th_;
   std::mutex m_;
   std::condition_variable cv_, done_;
-  const std::function<void(int)> *f_ = nullptr;
+  const std::function<void(uint32_t)> *f_ = nullptr;
+  std::atomic<uint32_t> next_{0};
+  uint32_t blocks_ = 0;
   uint64_t gen_ = 0;
-  int left_ = 0;
+  int active_ = 0;
   bool quit_ = false;
 };
 
@@ -372,27 +429,82 @@ void destroy_pool(hicr_ctx c) {
 }
 
 constexpr uint64_t kPoolMin = 16384;        // requests that make a batch large
+constexpr uint64_t kPackBlock = 2048;       // requests a host thread takes at once
+constexpr int kPoolThreads = 7;             // beside the calling one
 constexpr uint64_t kUploadStream = 256 << 10;  // upload bytes that go on their own stream
 
-// Validate and pack requests [i0, i1); the index of the first rejected one
-// (and its code), or i1.
-static uint64_t pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0, uint64_t i1,
-                           uint64_t *h, int *rc_out) {
+// What pack_range found: the first rejected request (i1 if none) and its
+// code, the bytes of all, and whether one writes host memory.
+struct Packed {
+  uint64_t bad = 0;
+  int rc = HICR_OK;
+  uint64_t bytes = 0;
+  bool host_dst = false;
+};
+
+// Validate requests [i0, i1) of n and resolve them to the structure of arrays
+// {dst, src, size, slot pair}.
+static Packed pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0, uint64_t i1,
+                         uint64_t *h) {
   uint64_t *hd = h, *hs = h + n, *hz = h + 2 * n, *hp = h + 3 * n;
   const Slot *sl = c->slots.data();
+  Packed p;
+  p.bad = i1;
   for (uint64_t i = i0; i < i1; i++) {
     const hicr_desc &x = d[i];
-    const int rc = check_desc(c, x);
-    if (rc != HICR_OK) {
-      *rc_out = rc;
-      return i;
+    p.rc = check_desc(c, x);
+    if (p.rc != HICR_OK) {
+      p.bad = i;
+      return p;
     }
     hd[i] = sl[x.dst_slot].base + x.dst_off;
     hs[i] = sl[x.src_slot].base + x.src_off;
     hz[i] = x.size;
     hp[i] = (uint64_t)x.dst_slot | ((uint64_t)x.src_slot << 32);
+    p.bytes += x.size;
+    p.host_dst |= sl[x.dst_slot].space != HICR_MEM_HBM;
   }
-  return i1;
+  return p;
+}
+
+void pack_batch(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t *h) {
+  (void)pack_range(c, d, n, 0, n, h);
+}
+
+// The same for the whole batch, split over host threads when it is large.
+static Packed pack_all(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t *h) {
+  if (n < kPoolMin || !c->pool || c->pool->size() == 1) return pack_range(c, d, n, 0, n, h);
+  const uint32_t blocks = (uint32_t)((n + kPackBlock - 1) / kPackBlock);
+  std::vector<Packed> part(blocks);
+  c->pool->run(blocks, [&](uint32_t p) {
+    part[p] = pack_range(c, d, n, p * kPackBlock, std::min(n, (p + 1) * kPackBlock), h);
+  });
+  Packed k;
+  k.bad = n;
+  for (uint32_t p = blocks; p-- > 0;) {
+    k.bytes += part[p].bytes;
+    k.host_dst |= part[p].host_dst;
+    if (part[p].rc != HICR_OK) {
+      k.bad = part[p].bad;
+      k.rc = part[p].rc;
+    }
+  }
+  return k;
+}
+
+// Start the pool behind a context's first large batch, while that one is on
+// the GPU (starting seven threads takes longer than packing it alone).
+static void start_pool(hicr_ctx c, uint64_t n) {
+  if (n < kPoolMin || c->pool || c->pool_failed) return;
+  // no exception crosses the C ABI: a pool that cannot start its threads
+  // leaves the work on the calling thread
+  try {
+    const int hw = (int)std::thread::hardware_concurrency();
+    c->pool = new HostPool(std::max(0, std::min(kPoolThreads, hw - 1)));
+  } catch (...) {
+    c->pool = nullptr;
+    c->pool_failed = true;
+  }
 }
 
 // Validate, pack and launch n requests as one submission.
@@ -404,88 +516,88 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   c->next_sub = (c->next_sub + 1) % kNumSubs;
   int rc = wait_sub(c, s);
   if (rc != HICR_OK) return rc;
-  rc = ensure_capacity(c, s, n);
+  rc = ensure_staging(c, s, n);
   if (rc != HICR_OK) return rc;
-  // validate and pack in one pass (split over host threads for a large
-  // batch); nothing is queued unless every request passes and the batch
-  // splits into launches
   uint64_t *h = static_cast<uint64_t *>(s.h);
-  uint64_t first_bad = n;
-  int bad_rc = HICR_OK;
-  if (n >= kPoolMin && !c->pool && !c->pool_failed) {
-    // no exception crosses the C ABI: a pool that cannot start its threads
-    // leaves the checks on the calling thread
-    try {
-      const int hw = (int)std::thread::hardware_concurrency();
-      c->pool = new HostPool(std::max(0, std::min(3, hw - 1)));
-    } catch (...) {
-      c->pool = nullptr;
-      c->pool_failed = true;
+  const uint64_t *hv = static_cast<const uint64_t *>(s.h_dev);  // the same, as the device sees it
+  // nothing is queued unless every request passes
+  const Packed k = pack_all(c, d, n, h);
+  if (k.rc != HICR_OK) {
+    if (bad) *bad = k.bad;
+    return fail(c, k.rc, "request %llu rejected", (unsigned long long)k.bad);
+  }
+  // How the end is seen and the requests are counted.  A batch into HBM of at
+  // most kMaxLdsDescs requests is counted here, in its slots, and its last
+  // copy launch raises the submission's words; a larger one is counted on the
+  // device by a kernel that raises them (a host core takes ~2 ns a request);
+  // bytes in host memory are only visible after the runtime's completion
+  // signal, so there the event tells.
+  const bool no_count = opt && opt->no_count;
+  const bool host_count = !no_count && !k.host_dst && n <= kMaxLdsDescs;
+  uint64_t *counters = no_count || host_count ? nullptr : c->d_counters;
+  Signal *sig = k.host_dst || opt ? nullptr : &s.sig;
+  const uint32_t waves = host_count && !opt ? stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu) : 0;
+  s.sig.n_words = 0;
+  s.host_counted = 0;
+  hipError_t e = hipSuccess;
+  if (waves) {
+    // small enough that the kernel reads the requests where they are
+    StreamStart *starts = reinterpret_cast<StreamStart *>(h + 4 * n);
+    stream_starts(h, h + 2 * n, n, k.bytes, waves, kLineBytes, starts);
+    const DevBatch b{hv, hv + n, hv + 2 * n, hv + 3 * n, (uint32_t)n};
+    e = launch_stream(b, reinterpret_cast<const StreamStart *>(hv + 4 * n), waves,
+                      arm(*sig, stream_grid(waves)), stream);
+    if (e != hipSuccess) rc = hip_fail(c, e, "launching the stream kernel");
+  } else {
+    const DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};
+    rc = ensure_device(c, s, n);
+    if (rc == HICR_OK) rc = split_batch(c, h, h + 2 * n, n, ds, c->segs);
+    if (rc != HICR_OK) return rc;
+    const uint64_t *dd = static_cast<const uint64_t *>(s.d);
+    uint32_t *tables = batch_tables(s.d, n);
+    const bool lds = c->segs[0].lds;  // all of them, or none
+    // A large batch behind others still in flight is uploaded on a stream of
+    // its own, so the upload overlaps their copies.  Otherwise a kernel in
+    // front of the copy reads the staging (the scan kernel, when there is a
+    // table to scan): a copy engine first waits for the signal of the kernel
+    // before it, and the copy kernel then for the engine's.
+    const bool behind = n * 32 >= kUploadStream && any_inflight(c);
+    if (behind) {
+      e = hipMemcpyAsync(s.d, s.h, n * 32, hipMemcpyHostToDevice, c->up);
+      if (e == hipSuccess) e = hipEventRecord(s.up_ev, c->up);
+      if (e == hipSuccess) e = hipStreamWaitEvent(stream, s.up_ev, 0);
+    } else if (lds) {
+      e = launch_upload(s.h_dev, s.d, n * (counters ? 32 : 24), stream);
+    }
+    if (e != hipSuccess) return hip_fail(c, e, "uploading a batch");
+    if (opt && opt->t0) {
+      e = hipEventRecord(opt->t0, stream);
+      if (e != hipSuccess) return hip_fail(c, e, "recording a timing event");
+    }
+    rc = launch_scans(c, behind || lds ? nullptr : hv, dd, n, c->segs, ds, tables, stream);
+    if (rc == HICR_OK) rc = launch_copies(c, dd, n, c->segs, ds, tables, counters, stream, sig);
+    if (rc == HICR_OK && opt && opt->t1) {
+      e = hipEventRecord(opt->t1, stream);
+      if (e != hipSuccess) rc = hip_fail(c, e, "recording a timing event");
     }
   }
-  if (n >= kPoolMin && c->pool && c->pool->size() > 1) {
-    const int parts = c->pool->size();
-    std::vector<uint64_t> pb(parts, n);
-    std::vector<int> prc(parts, HICR_OK);
-    c->pool->run([&](int p) {
-      const uint64_t i0 = n * p / parts, i1 = n * (p + 1) / parts;
-      const uint64_t b = pack_range(c, d, n, i0, i1, h, &prc[p]);
-      if (b < i1) pb[p] = b;
-    });
-    for (int p = 0; p < parts; p++)
-      if (pb[p] < first_bad) {
-        first_bad = pb[p];
-        bad_rc = prc[p];
-      }
-  } else {
-    first_bad = pack_range(c, d, n, 0, n, h, &bad_rc);
-  }
-  if (first_bad < n) {
-    if (bad) *bad = first_bad;
-    return fail(c, bad_rc, "request %llu rejected", (unsigned long long)first_bad);
-  }
-  DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};
-  rc = split_batch(c, h, h + 2 * n, n, ds, c->segs);
-  if (rc != HICR_OK) return rc;
-  // a large upload runs on its own stream, so it overlaps the copies queued
-  // before it; the copy stream waits for it
-  hipError_t e;
-  if (n * 32 >= kUploadStream) {
-    e = hipMemcpyAsync(s.d, s.h, n * 32, hipMemcpyHostToDevice, c->up);
-    if (e == hipSuccess) e = hipEventRecord(s.up_ev, c->up);
-    if (e == hipSuccess) e = hipStreamWaitEvent(stream, s.up_ev, 0);
-  } else {
-    e = hipMemcpyAsync(s.d, s.h, n * 32, hipMemcpyHostToDevice, stream);
-  }
-  if (e != hipSuccess) return hip_fail(c, e, "uploading a batch");
-  const uint64_t *dd = static_cast<const uint64_t *>(s.d);
-  uint64_t *counters = (opt && opt->no_count) ? nullptr : c->d_counters;
-  if (opt && opt->t0) {
-    e = hipEventRecord(opt->t0, stream);
-    if (e != hipSuccess) return hip_fail(c, e, "recording a timing event");
-  }
-  uint32_t *tables = batch_tables(s.d, n);
-  // a batch small enough for one counter group that writes device memory
-  // only announces its end in the buffer's done word
-  uint64_t *done = nullptr, seq = 0;
-  if (counters && n <= 1024 && writes_device_only(c, d, n)) {
-    done = sub_done_word(c, s);
-    seq = ++c->done_next;
-  }
-  bool armed = false;
-  s.done_seq = 0;
-  rc = launch_scans(c, dd, n, c->segs, ds, tables, stream);
-  if (rc == HICR_OK)
-    rc = launch_copies(c, dd, n, c->segs, ds, tables, counters, stream, done, seq, &armed);
-  if (rc == HICR_OK && armed) s.done_seq = seq;
-  if (rc == HICR_OK && opt && opt->t1) {
-    e = hipEventRecord(opt->t1, stream);
-    if (e != hipSuccess) rc = hip_fail(c, e, "recording a timing event");
-  }
-  // the staging buffer is in use from the upload on, whatever failed after it
-  e = hipEventRecord(s.ev, stream);
+  if (counters) c->dev_counted = true;
+  // the staging buffer is in use from the first launch on, whatever failed
+  // after it (then only the event tells when it is free again)
+  if (rc != HICR_OK) s.sig.n_words = 0;
+  e = mark(c, s.sig, stream);
+  s.push_seq = stream == c->stream ? c->push_seq : 0;
   if (e == hipSuccess) s.inflight = true;
+  start_pool(c, n);
   if (rc != HICR_OK) return rc;
+  if (host_count) {
+    const uint64_t *hp = h + 3 * n;
+    for (uint64_t i = 0; i < n; i++) {
+      c->slots[hp[i] & 0xffffffffull].recv++;
+      c->slots[hp[i] >> 32].sent++;
+    }
+    s.host_counted = n;
+  }
   if (e != hipSuccess) return hip_fail(c, e, "recording a batch event");
   return HICR_OK;
 }
@@ -569,13 +681,30 @@ int hicr_ctx_create(int device, void *stream, hicr_ctx *out) {
     }
     bool ok = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipHostMalloc(&c->h_read, 64, hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipHostMalloc(&c->h_done, 64 * kNumSubs, hipHostMallocDefault) == hipSuccess;
-    if (ok) std::memset(c->h_done, 0, 64 * kNumSubs);
-    ok = ok && hipEventCreateWithFlags(&c->push_ev, hipEventDisableTiming) == hipSuccess;
+    // pinned, in one block: the submission buffers' done words, their staging
+    // for kStageReqs requests each (larger submissions allocate their own),
+    // and the staging of hicr_memcpy_batch_noalloc
+    constexpr size_t done_bytes = 4096, na_bytes = kNoAllocMaxReqs * 32;
+    static_assert(8 * kDoneWords * kNumSubs <= done_bytes, "one page of words");
+    void *pinned = nullptr, *pinned_dev = nullptr;
+    ok = ok && hipHostMalloc(&pinned, done_bytes + kNumSubs * stage_bytes(kStageReqs) + na_bytes,
+                             hipHostMallocDefault) == hipSuccess;
+    c->h_done = static_cast<uint64_t *>(pinned);
+    ok = ok && hipHostGetDevicePointer(&pinned_dev, pinned, 0) == hipSuccess;
+    if (ok) std::memset(c->h_done, 0, done_bytes);
+    for (int i = 0; ok && i < kNumSubs; i++) {
+      const size_t off = done_bytes + i * stage_bytes(kStageReqs);
+      c->subs[i].h = static_cast<char *>(pinned) + off;
+      c->subs[i].h_dev = static_cast<char *>(pinned_dev) + off;
+      c->subs[i].h_cap = kStageReqs;
+    }
+    if (ok) c->na_h = static_cast<char *>(pinned) + done_bytes + kNumSubs * stage_bytes(kStageReqs);
+    ok = ok && hipEventCreateWithFlags(&c->push_sig.ev, hipEventDisableTiming) == hipSuccess;
     if (ok && (pump_occupancy(&c->pump_occ) != 0 || c->pump_occ < 1)) c->pump_occ = 1;
     ok = ok && hipStreamCreateWithFlags(&c->up, hipStreamNonBlocking) == hipSuccess;
     for (int i = 0; ok && i < kNumSubs; i++) {
-      ok = hipEventCreateWithFlags(&c->subs[i].ev, hipEventDisableTiming) == hipSuccess;
+      c->subs[i].sig.words = c->h_done + kDoneWords * i;
+      ok = hipEventCreateWithFlags(&c->subs[i].sig.ev, hipEventDisableTiming) == hipSuccess;
       ok = ok && hipEventCreateWithFlags(&c->subs[i].up_ev, hipEventDisableTiming) == hipSuccess;
     }
     c->def_sched = hicr_sched{64u << 10, 1, 2, HICR_SCHED_FIXED};
@@ -583,7 +712,6 @@ int hicr_ctx_create(int device, void *stream, hicr_ctx *out) {
     // workspace's address, pinned staging, its events, and room for its
     // launch list and error messages (so that no call of it allocates)
     ok = ok && noalloc_scratch(device, &c->na_scratch) == hipSuccess;
-    ok = ok && hipHostMalloc(&c->na_h, kNoAllocMaxReqs * 32, hipHostMallocDefault) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&c->na_up_ev, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&c->na_ev, hipEventDisableTiming) == hipSuccess;
     if (ok) {
@@ -610,15 +738,14 @@ int hicr_ctx_destroy(hicr_ctx c) {
     destroy_sched(c);
     destroy_pool(c);
     for (Sub &s : c->subs) {
-      if (s.h) (void)hipHostFree(s.h);
+      if (s.h && s.h_cap > kStageReqs) (void)hipHostFree(s.h);
       if (s.d) (void)hipFree(s.d);
-      if (s.ev) (void)hipEventDestroy(s.ev);
+      if (s.sig.ev) (void)hipEventDestroy(s.sig.ev);
       if (s.up_ev) (void)hipEventDestroy(s.up_ev);
     }
     if (c->d_counters) (void)hipFree(c->d_counters);
     if (c->h_read) (void)hipHostFree(c->h_read);
     if (c->h_done) (void)hipHostFree(c->h_done);
-    if (c->na_h) (void)hipHostFree(c->na_h);
     if (c->na_up_ev) (void)hipEventDestroy(c->na_up_ev);
     if (c->na_ev) (void)hipEventDestroy(c->na_ev);
     if (c->aux) (void)hipStreamDestroy(c->aux);
@@ -745,12 +872,29 @@ int hicr_slot_counters(hicr_ctx c, hicr_slot slot, uint64_t *sent, uint64_t *rec
     std::lock_guard<std::mutex> g(c->mu);
     if (slot >= c->slots.size() || !c->slots[slot].live) return fail(c, HICR_EBADSLOT, "bad slot");
     (void)hipSetDevice(c->device);
-    hipError_t e = hipMemcpyAsync(c->h_read, c->d_counters + 2 * slot, 16, hipMemcpyDeviceToHost,
-                                  c->aux);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->aux);
-    if (e != hipSuccess) return hip_fail(c, e, "reading counters");
-    if (sent) *sent = c->h_read[0];
-    if (recv) *recv = c->h_read[1];
+    // transfers counted in the slot, less those of submissions and replays
+    // still in flight, plus what launches have counted on the device
+    uint64_t n_sent = c->slots[slot].sent, n_recv = c->slots[slot].recv;
+    (void)any_inflight(c);
+    for (const Sub &s : c->subs) {
+      if (!s.inflight) continue;
+      const uint64_t *hp = static_cast<const uint64_t *>(s.h) + 3 * s.host_counted;
+      for (uint64_t i = 0; i < s.host_counted; i++) {
+        n_recv -= (hp[i] & 0xffffffffull) == slot;
+        n_sent -= (hp[i] >> 32) == slot;
+      }
+    }
+    plans_unfinished(c, slot, &n_sent, &n_recv);
+    if (c->dev_counted) {
+      hipError_t e = hipMemcpyAsync(c->h_read, c->d_counters + 2 * slot, 16, hipMemcpyDeviceToHost,
+                                    c->aux);
+      if (e == hipSuccess) e = hipStreamSynchronize(c->aux);
+      if (e != hipSuccess) return hip_fail(c, e, "reading counters");
+      n_sent += c->h_read[0];
+      n_recv += c->h_read[1];
+    }
+    if (sent) *sent = n_sent;
+    if (recv) *recv = n_recv;
     return HICR_OK;
   });
 }
@@ -817,17 +961,14 @@ int hicr_memcpy_batch_noalloc(hicr_ctx c, const hicr_desc *descs, uint64_t n, co
       c->na_up_pending = false;
     }
     uint64_t *h = static_cast<uint64_t *>(c->na_h);
-    int bad_rc = HICR_OK;
-    const uint64_t first_bad = pack_range(c, descs, n, 0, n, h, &bad_rc);
-    if (first_bad < n) {
-      if (bad) *bad = first_bad;
-      return fail(c, bad_rc, "request %llu rejected", (unsigned long long)first_bad);
+    const Packed k = pack_range(c, descs, n, 0, n, h);
+    if (k.rc != HICR_OK) {
+      if (bad) *bad = k.bad;
+      return fail(c, k.rc, "request %llu rejected", (unsigned long long)k.bad);
     }
-    uint64_t bytes = 0;
-    for (uint64_t i = 0; i < n; i++) bytes += h[2 * n + i];
-    if (bytes >= kNoAllocMaxBytes)
+    if (k.bytes >= kNoAllocMaxBytes)
       return fail(c, HICR_EINVAL, "%llu bytes: the no-allocation path moves less than 2^38 per call",
-                  (unsigned long long)bytes);
+                  (unsigned long long)k.bytes);
     const DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};
     rc = split_batch(c, h, h + 2 * n, n, ds, c->segs);
     if (rc != HICR_OK) return rc;
@@ -843,7 +984,8 @@ int hicr_memcpy_batch_noalloc(hicr_ctx c, const hicr_desc *descs, uint64_t n, co
     c->na_up_pending = true;
     const uint64_t *dd = static_cast<const uint64_t *>(c->na_scratch);
     uint32_t *tables = batch_tables(c->na_scratch, n);
-    rc = launch_scans(c, dd, n, c->segs, ds, tables, st);
+    c->dev_counted = true;
+    rc = launch_scans(c, nullptr, dd, n, c->segs, ds, tables, st);
     if (rc == HICR_OK) rc = launch_copies(c, dd, n, c->segs, ds, tables, c->d_counters, st);
     e = hipEventRecord(c->na_ev, st);
     if (e == hipSuccess) c->na_inflight = true;

@@ -24,19 +24,39 @@ struct Slot {
   uint32_t plan_refs = 0;  // plans whose requests name this slot
   uint32_t dobj_refs = 0;  // published data objects inside this slot
   bool live = false;
+  // transfers accepted by submissions whose end the host sees itself (Done):
+  // the slot's counters are these, less what is still in flight, plus the
+  // device's
+  uint64_t sent = 0, recv = 0;
+  uint64_t tmp_sent = 0, tmp_recv = 0;  // while a plan is made: its transfers of this slot
 };
 
-// One submission buffer: pinned staging, its device copy, the event that
-// marks the end of the submission, and the value its counter kernel stores
-// to the buffer's word of the context's done array when it ends.
+// The words of pinned host memory a launch raises when it ends (Done), and
+// the launch's event.  On the context's own stream the event is recorded only
+// once somebody has to wait for it: recording one after every launch cost
+// the stream ~8 us each, and nobody else can queue work there behind the
+// library's.
+struct Signal {
+  uint64_t *words = nullptr;  // kDoneWords of them
+  uint32_t *arrive = nullptr;
+  uint64_t seq = 0;           // value of the last launch's words
+  uint32_t n_words = 0;       // words the last launch raises (0: only the event tells)
+  hipEvent_t ev = nullptr;
+  bool recorded = false;      // ev has been recorded behind the last launch
+};
+
+// One submission buffer: pinned staging, its device copy, and how the
+// submission's end is seen.
 struct Sub {
-  void *h = nullptr;
+  void *h = nullptr;      // staging (the context's own block up to kStageReqs requests)
+  void *h_dev = nullptr;  // its device address
   void *d = nullptr;
-  uint64_t cap = 0;
-  hipEvent_t ev = nullptr;     // end of the submission's last launch
+  uint64_t h_cap = 0, d_cap = 0;  // requests they have room for
   hipEvent_t up_ev = nullptr;  // end of its upload, when that ran on the upload stream
+  Signal sig;
   bool inflight = false;
-  uint64_t done_seq = 0;       // 0: the submission raises no done word
+  uint64_t host_counted = 0;   // its first requests counted in the slots (all, or none)
+  uint64_t push_seq = 0;       // host-API pushes and network steps queued before it on its stream
 };
 
 class HostPool;  // host threads that validate and pack large batches (runtime.cpp)
@@ -58,6 +78,11 @@ struct SubmitOpts {
 };
 
 constexpr int kNumSubs = 4;
+constexpr uint64_t kStageReqs = 1024;   // staged by a submission buffer from the start
+// Staging of n requests: 32 bytes each, then the stream kernel's starts.
+constexpr size_t stage_bytes(uint64_t n) {
+  return (n * 32 + (kMaxStreamWaves + 1) * sizeof(StreamStart) + 4095) & ~(size_t)4095;
+}
 constexpr uint32_t kMaxSlots = 1u << 20;  // slots per context (fixed counter table)
 
 struct SchedState;  // autotuned table and device-resident network (sched.cpp)
@@ -112,11 +137,8 @@ struct hicr_ctx_s {
   uint64_t *h_read = nullptr;  // pinned read-back buffer
   hicr::Sub subs[hicr::kNumSubs];
   int next_sub = 0;
-  // pinned words that one-group counter launches raise when a submission
-  // ends (word 8 i for subs[i], one 64-byte line each), and the last value
-  // handed out
-  uint64_t *h_done = nullptr;
-  uint64_t done_next = 0;
+  uint64_t *h_done = nullptr;    // the submission buffers' done words; heads the context's pinned block
+  bool dev_counted = false;      // some launch has counted its requests on the device
   // hicr_memcpy_batch_noalloc: this device's fixed workspace, pinned staging
   // allocated with the context, and the events of the last such submission
   void *na_scratch = nullptr;
@@ -131,14 +153,18 @@ struct hicr_ctx_s {
   hicr::SchedState *sched = nullptr;
   std::unordered_set<struct hicr_channel_s *> channels;
   std::vector<struct hicr_plan_s *> plans;
+  std::vector<void *> plan_blocks;      // pinned blocks of plans' done words,
+  std::vector<uint64_t *> plan_words;   // and the words in them that are free
   std::map<uint64_t, hicr_dobj_handle> dobjs;  // published data objects by id
   uint64_t next_dobj_id = 1;
   std::vector<hicr::Extra> extra;
   std::vector<hicr::PumpBuf> pump_free;  // finished pumps' buffers, for reuse
   std::vector<hicr::PumpLive> pump_live;  // pumps launched and not yet finished
   int pump_occ = 0;  // pump workgroups per CU
-  hipEvent_t push_ev = nullptr;  // last host-API channel push or network step
-  bool push_pending = false;
+  // host-API channel pushes and network steps queued on `stream`: how many,
+  // how many of them are known to have ended, and the event of the last
+  uint64_t push_seq = 0, push_done = 0;
+  hicr::Signal push_sig;
   std::mutex abort_mu;  // guards abort_words; never held while waiting on the GPU
   std::vector<uint32_t *> abort_words;  // running pumps' pinned abort words
   std::string err;
@@ -153,11 +179,22 @@ int check_sched(hicr_ctx c, const hicr_sched &s);
 bool any_inflight(hicr_ctx c);
 // Wait for an event: poll briefly, then block.
 hipError_t sync_event(hipEvent_t e);
-// Poll a done word (pinned host memory a counter kernel stores to) for up
-// to 200 us; true once it holds seq.
-bool wait_done(const uint64_t *w, uint64_t seq);
+// The next launch of `grid` workgroups raises sig's words.
+inline Done arm(Signal &sig, uint32_t grid) {
+  sig.n_words = done_words(grid);
+  return Done{sig.words, sig.arrive, ++sig.seq};
+}
+// Queue what marks the end of everything launched on `s` so far: the event,
+// unless `s` is the context's own stream.
+hipError_t mark(hicr_ctx c, Signal &sig, hipStream_t s);
+// Whether the marked launch has ended / wait until it has (its words are
+// polled for up to 200 us, then the event is waited for).
+bool ended(hicr_ctx c, Signal &sig);
+hipError_t wait_signal(hicr_ctx c, Signal &sig);
+// The event behind the marked launch, recorded now if it is not yet.
+hipError_t ensure_event(hicr_ctx c, Signal &sig);
 // Whether every request of a batch writes device memory (HBM slots): only
-// then may a done word stand for the end of the batch, since the runtime's
+// then may done words stand for the end of the batch, since the runtime's
 // completion signal is what makes bytes written to host memory visible.
 bool writes_device_only(hicr_ctx c, const hicr_desc *d, uint64_t n);
 int wait_all(hicr_ctx c);
@@ -173,15 +210,15 @@ void pack_batch(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t *h);
 int split_batch(hicr_ctx c, const uint64_t *hd, const uint64_t *hz, uint64_t n, const DevSched &ds,
                 std::vector<Seg> &out);
 // Queue the scan kernel for every launch that reads a table (tables: the
-// batch_tables() region beside the uploaded batch dd).
-int launch_scans(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
-                 DevSched ds, uint32_t *tables, hipStream_t stream);
-// Queue the copy launches, then (counters != null) the counter kernel; with
-// done != null a one-group counter launch ends by storing seq to *done, and
-// *armed says whether it will.
+// batch_tables() region beside the batch dd).  staged: the batch lies there,
+// in pinned host memory, and the kernel moves it to dd.
+int launch_scans(hicr_ctx c, const uint64_t *staged, const uint64_t *dd, uint64_t n, 
+                 const std::vector<Seg> &segs, DevSched ds, uint32_t *tables, hipStream_t stream);
+// Queue the copy launches, then (counters != null) the counter kernel.  With
+// sig != null and a single copy launch, that launch raises sig's words.
 int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
                   DevSched ds, const uint32_t *tables, uint64_t *counters, hipStream_t stream,
-                  uint64_t *done = nullptr, uint64_t seq = 0, bool *armed = nullptr);
+                  Signal *sig = nullptr);
 // Bytes of device memory an uploaded batch of n requests takes: the packed
 // requests (32 B each), then the piece tables: per-request prefixes (4 B
 // each) and tile totals (a launch over requests [i0, i1) keeps its tiles at
@@ -195,6 +232,8 @@ inline uint32_t *batch_tables(void *d, uint64_t n) {
 int wait_plans(hicr_ctx c);
 bool plans_inflight(hicr_ctx c);
 void destroy_plans(hicr_ctx c);
+// Take what the plans' replays in flight will count on `slot` off the counts.
+void plans_unfinished(hicr_ctx c, uint32_t slot, uint64_t *sent, uint64_t *recv);
 
 // Schedule selection (sched.cpp): the class for a batch under mode TUNED
 // (nearest tuned-table entry) or LEARNED (the network: on the host, in the

@@ -399,9 +399,11 @@ int hicr_mlp_train_step(hicr_ctx c, const float *x_dev, const int32_t *y_dev, ui
                             s->step + 1, loss, c->stream);
     if (e == hipSuccess) s->step++;
     if (e == hipSuccess) e = put_loss(s, loss, loss_dev, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->push_ev, c->stream);
+    if (e == hipSuccess) {
+      c->push_seq++;
+      e = mark(c, c->push_sig, c->stream);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "network training step");
-    c->push_pending = true;
     s->h_stale = true;
     return HICR_OK;
   });
