@@ -486,7 +486,7 @@ int hicr_channel_device_view(hicr_channel ch, uint32_t ring, hicr_dev_ring *out)
  * pushes `buf` into B.  rtt_ticks[i * reps + k] receives round trip k of size
  * i in 100 MHz device-clock ticks.  All five slots: HBM, 16-byte aligned, at
  * least max(sizes) bytes.  wgs_per_endpoint 0 picks max(1, min(256,
- * size / 64 KiB)).  Synchronous. */
+ * size / 16 KiB)).  Synchronous. */
 int hicr_pingpong(hicr_ctx ctx, hicr_slot src, hicr_slot dst, hicr_slot ring_a, hicr_slot ring_b,
                   hicr_slot buf, const uint64_t *sizes, uint32_t n_sizes, uint32_t reps,
                   uint32_t wgs_per_endpoint, uint64_t *rtt_ticks);

@@ -744,6 +744,8 @@ int hicr_ctx_destroy(hicr_ctx c) {
       if (s.up_ev) (void)hipEventDestroy(s.up_ev);
     }
     if (c->d_counters) (void)hipFree(c->d_counters);
+    if (c->pp_d) (void)hipFree(c->pp_d);
+    if (c->pp_h) (void)hipHostFree(c->pp_h);
     if (c->h_read) (void)hipHostFree(c->h_read);
     if (c->h_done) (void)hipHostFree(c->h_done);
     if (c->na_up_ev) (void)hipEventDestroy(c->na_up_ev);

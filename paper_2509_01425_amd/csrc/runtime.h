@@ -165,6 +165,9 @@ struct hicr_ctx_s {
   // how many of them are known to have ended, and the event of the last
   uint64_t push_seq = 0, push_done = 0;
   hicr::Signal push_sig;
+  // words of hicr_pingpong launches and their copy on the host (pinned)
+  uint64_t *pp_d = nullptr, *pp_h = nullptr;
+  size_t pp_words = 0;
   std::mutex abort_mu;  // guards abort_words; never held while waiting on the GPU
   std::vector<uint32_t *> abort_words;  // running pumps' pinned abort words
   std::string err;
