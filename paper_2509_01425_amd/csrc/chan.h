@@ -17,6 +17,7 @@ constexpr uint64_t kEntrySizeMask = (1ull << 48) - 1;
 constexpr uint32_t kMaxProducers = 64;
 constexpr int kPumpBlock = 256;
 constexpr uint32_t kMaxTeam = 16;  // consumer workgroups of one locking MPSC ring
+constexpr uint32_t kMaxSplit = 8;  // workgroups of each end of a ring with one producer
 
 // One 128-byte line per writer so producer and consumer never share a line.
 struct alignas(128) CoordLine {
@@ -69,7 +70,12 @@ struct DevChannel {
   uint64_t trace_base;  // first trace slot (locking MPSC)
   uint32_t prod_stream_base;  // index into stream_of_prod: K entries
   uint32_t pad;
-  uint64_t claim;   // locking team: device address of the round claim counter
+  // locking team: device address of the round claim counter.  A ring whose
+  // ends are split: of the words its members share (zero at the start): the
+  // ring's byte counter at the start of the pump + 1, told by the first
+  // member, and from byte 64 on, one per producer member and, from the next
+  // multiple of 64 on, one per consumer member, the groups it has finished
+  uint64_t claim;
   uint64_t rounds;  // locking team: device address of the round table
 };
 
@@ -90,14 +96,17 @@ struct DevStream {
 
 // Per-workgroup role: up to four waves that are producers (ids = streams) or
 // consumers (ids = units) on their own, or a whole workgroup as the producer
-// of stream ids[0], the consumer of unit ids[0] or a locking team's member
-// (unit ids[0]).
+// of stream ids[0], the consumer of unit ids[0], a locking team's member
+// (unit ids[0]), or member ids[1] of those that produce stream ids[0] or
+// consume unit ids[0], in ids[2] teams of ids[3].
 enum : uint32_t {
   kRoleProducerWaves = 0,
   kRoleProducerGroup = 1,
   kRoleConsumerWaves = 2,
   kRoleConsumerGroup = 3,
   kRoleLockMember = 4,
+  kRoleProducerSplit = 5,
+  kRoleConsumerSplit = 6,
 };
 struct DevRole {
   uint32_t kind;
@@ -137,7 +146,7 @@ struct PushArgs {
 
 enum : uint32_t { kErrTimeout = 1, kErrAbort = 2, kErrCorrupt = 4 };
 
-hipError_t launch_pump(const PumpArgs &a, uint32_t n_wgs, hipStream_t stream);
+hipError_t launch_pump(const PumpArgs &a, bool split, uint32_t n_wgs, hipStream_t stream);
 hipError_t launch_push(const PushArgs &a, hipStream_t stream);
 int pump_occupancy(int *wgs_per_cu);
 

@@ -514,7 +514,12 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   std::vector<uint64_t> want;
   for (uint32_t k : lock_chans)
     want.push_back(std::min<uint64_t>(kMaxTeam, (chan_bytes[k] + per_unit - 1) / per_unit));
-  const PumpPlan plan = plan_endpoints(cap, n - indep.size(), indep.size(), want, kMaxProducers);
+  // (an end of a ring is split no further than four messages to a member)
+  uint64_t most_msgs = 0;
+  for (uint32_t sid : indep) most_msgs = std::max(most_msgs, st[sid].n_msgs);
+  const PumpPlan plan =
+      plan_endpoints(cap, n - indep.size(), indep.size(), want, kMaxProducers, (uint64_t)c->n_cu,
+                     std::min<uint64_t>(kMaxSplit, most_msgs / 4));
   if (!plan.fits)
     return fail(c, HICR_EINVAL, "%llu workgroups do not fit the device at once (%d x %d)",
                 (unsigned long long)plan.need, c->n_cu, c->pump_occ);
@@ -607,6 +612,7 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
       unit_of[sid] = (uint32_t)dch.size();
       ring_of[sid] = (uint32_t)rings.size();
       rings.push_back(dev_ring(ch, r));
+      rings.back().base_m = ch->dev_msgs[r];
       sop.push_back(sid);
       d.total_msgs += st[sid].n_msgs;
     }
@@ -652,17 +658,28 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
     if (st[i].channel->cfg.mode == HICR_CH_MPSC_LOCK)
       (plan.lock_groups ? lock_prods : prods).push_back(i);
   add_roles(true, kRoleProducerGroup, kRoleProducerWaves, lock_prods);
-  add_roles(plan.ind_groups, kRoleProducerGroup, kRoleProducerWaves, prods);
-  add_roles(plan.ind_groups, kRoleConsumerGroup, kRoleConsumerWaves, units);
+  if (plan.split > 1) {
+    // (a locking ring's producers are workgroups too then)
+    const uint32_t B = plan.share, A = plan.split / B;
+    for (uint32_t t = 0; t < plan.split; t++) {
+      for (uint32_t sid : indep) roles.push_back(DevRole{kRoleProducerSplit, 1, {sid, t, A, B}});
+      for (uint32_t u : units) roles.push_back(DevRole{kRoleConsumerSplit, 1, {u, t, A, B}});
+    }
+  } else {
+    add_roles(plan.ind_groups, kRoleProducerGroup, kRoleProducerWaves, prods);
+    add_roles(plan.ind_groups, kRoleConsumerGroup, kRoleConsumerWaves, units);
+  }
   add_roles(true, kRoleLockMember, kRoleLockMember, members);
   const uint32_t n_wgs = (uint32_t)roles.size();
-  // one upload: [err words | rings | channels | streams | sop | roles | msg_off | msg_size],
-  // then the locking teams' device scratch (not uploaded; its head is zeroed)
+  // one upload: [err words | rings | channels | streams | sop | roles | split rings' words (zero) |
+  // msg_off | msg_size], then the locking teams' device scratch (not uploaded; its head is zeroed)
   auto align = [](uint64_t x) { return (x + 255) & ~(uint64_t)255; };
+  const uint64_t word_bytes = 64 + 2 * ((8 * (uint64_t)plan.split + 63) & ~(uint64_t)63);
   uint64_t o_err = 0, o_ring = 256, o_ch = align(o_ring + rings.size() * sizeof(DevRing)),
            o_st = align(o_ch + dch.size() * sizeof(DevChannel)),
            o_sop = align(o_st + ds.size() * sizeof(DevStream)),
-           o_role = align(o_sop + sop.size() * 4), o_off = align(o_role + roles.size() * sizeof(DevRole)),
+           o_role = align(o_sop + sop.size() * 4), o_word = align(o_role + roles.size() * sizeof(DevRole)),
+           o_off = align(o_word + (plan.split > 1 ? word_bytes * n_indep_units : 0)),
            n_up = dev_tables ? 0 : n_msgs,  // message tables uploaded from the host
            o_size = align(o_off + n_up * 8), upload = align(o_size + n_up * 8),
            o_team = upload, total = align(o_team + team_bytes);
@@ -682,9 +699,13 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
         dch[u0 + m].rounds = dbase + lock_claim_off[t] + 8;
       }
     }
+    if (plan.split > 1)
+      for (uint32_t u = 0; u < n_indep_units; u++)
+        dch[members.size() + u].claim = reinterpret_cast<uint64_t>(x.d_buf) + o_word + word_bytes * u;
   }
   char *h = static_cast<char *>(x.h_buf);
   std::memset(h, 0, 256);
+  std::memset(h + o_word, 0, o_off - o_word);
   // the host's abort request: a word of the pinned staging's zeroed head,
   // which nothing else writes while the pump runs; its address goes up with
   // the error words (err[4..5])
@@ -735,7 +756,7 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   }
   if (e == hipSuccess) e = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, s);
   if (e == hipSuccess && team_zero_bytes) e = hipMemsetAsync(d + o_team, 0, team_zero_bytes, s);
-  if (e == hipSuccess) e = launch_pump(a, n_wgs, s);
+  if (e == hipSuccess) e = launch_pump(a, plan.split > 1, n_wgs, s);
   // error words come back into the (no longer needed) head of the staging
   if (e == hipSuccess) e = hipMemcpyAsync(h, d, 8, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&x.ev, hipEventDisableTiming);

@@ -30,7 +30,8 @@
 // pump_kernel is persistent: an endpoint (the producer of one stream, the
 // consumer of one or more single-producer rings) is either one wave, four of
 // them to a workgroup, or a whole workgroup when the device holds one for
-// every endpoint (few streams: the copy rate of one wave would bound each).
+// every endpoint (few streams: the copy rate of one wave would bound each), or
+// several workgroups while there are compute units to spare.
 // Either way its messages are cut into chunks of kChunkRows KiB that the
 // endpoint's waves take in turn, with the next chunk's loads issued before
 // the current chunk's stores.  A single-producer ring's messages lie back to
@@ -203,15 +204,16 @@ __device__ __forceinline__ void st_pair(uint64_t a, uint64_t w0, uint64_t w1, bo
 // a pass on the first configuration above; reading the ring without nt
 // 4.3-4.4 ms).
 
-// j messages between a ring and other memory, as a sequence of chunks: lane l
-// holds message l's size, ring position (below P) and other address.  Chunks
-// end at destination line boundaries, message ends and the ring end.
+// Messages l to j - 1 between a ring and other memory, as a sequence of
+// chunks: lane l holds message l's size, ring position (below P) and other
+// address.  Chunks end at destination line boundaries, message ends and the
+// ring end.
 template <bool kToRing>
 struct Feed {
   uint64_t payload, P;
   uint64_t v_size, v_pos, v_addr;
-  uint32_t j, l;
-  uint64_t left, pos, addr;
+  uint32_t j, l = 0;
+  uint64_t left = 0, pos = 0, addr = 0;
   __device__ __forceinline__ Chunk next() {
     while (left == 0 && l < j) {
       left = lane64(v_size, l);
@@ -243,8 +245,6 @@ struct Feed {
 // still be in flight.
 template <int WAVES, bool kToRing>
 __device__ __forceinline__ void move_feed(Feed<kToRing> f, uint32_t wave, uint32_t lane) {
-  f.l = 0;
-  f.left = f.pos = f.addr = 0;
   if (WAVES > 1) f.skip(wave);
   move_chunks<kToRing ? kReadStream : kAgentStream, kToRing ? kAgent : kAgentStream>(
       [&]() {
@@ -692,27 +692,304 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave,
   }
 }
 
+// A ring with one producer whose two ends are each split over workgroups.
+// The stream's messages are cut into groups of consecutive ones: up to
+// kSplitMost, and up to an eighth of the ring's bytes unless the first is
+// larger.  Every member finds the same groups in the size table (the
+// consumers check the entries against it).  Group g belongs to team g mod A;
+// the B workgroups of a team move a share of its bytes each.  Where a message
+// lies in the ring and in the output follows from the sizes before it, so a
+// producer member waits for nothing but room, a consumer member for nothing
+// but the group's publication; the first member of the team publishes the
+// group (or releases its room) once the others have told it of their shares
+// and the groups before have been published (released).  No wait is
+// circular: the first group that is not published waits for room only, every
+// group before it is published, and so its room is released in time.
+constexpr uint32_t kSplitMost = 16;
+
+struct Groups {
+  const uint64_t *sizes;  // of the stream's messages
+  uint64_t n, P, lim;
+  uint32_t most;
+  uint64_t first = 0;     // message of lane 0
+  uint64_t run = 0;       // bytes of the messages before it
+  uint64_t size = 0, incl = 0;
+  uint32_t lo = 0, hi = 0;  // lanes of the current group
+  bool bad = false;         // a size up to the current group's end is impossible
+  __device__ __forceinline__ Groups(const PumpArgs &a, const DevStream &st, const DevRing &r,
+                                    uint32_t teams, uint32_t lane)
+      : sizes(a.msg_size + st.first_msg), n(st.n_msgs), P(r.P), lim(r.P / (teams + 2)),
+        most(r.E < kSplitMost ? (uint32_t)r.E : kSplitMost) {
+    load(lane);
+  }
+  __device__ __forceinline__ uint32_t held() const { return n - first < 64 ? n - first : 64; }
+  __device__ __forceinline__ void load(uint32_t lane) {
+    size = lane < held() ? sizes[first + lane] : 0;
+    incl = wave_scan(size, lane);
+  }
+  // the next group (empty past the last)
+  __device__ __forceinline__ void next(uint32_t lane) {
+    lo = hi;
+    if (lo + most > 64 && first + 64 < n) {
+      run += lane64(incl, lo - 1);
+      first += lo;
+      lo = 0;
+      load(lane);
+    }
+    const bool in = lane >= lo && lane < held() && lane < lo + most &&
+                    (lane == lo || incl - before() <= lim);
+    hi = lo + (uint32_t)__popcll(__ballot(in));  // leading lanes: incl never decreases
+    bad |= __ballot(lane < hi && size > P) != 0;
+  }
+  // bytes of the messages between lane 0 and the group, and of the group
+  __device__ __forceinline__ uint64_t before() const { return lo ? lane64(incl, lo - 1) : 0; }
+  __device__ __forceinline__ uint64_t bytes() const { return lane64(incl, hi - 1) - before(); }
+  // group number `by` from here
+  __device__ __forceinline__ void skip(uint32_t by, uint32_t lane) {
+    for (uint32_t i = 0; i < by && (i == 0 || hi > lo); i++) next(lane);
+  }
+};
+
+// Member t's words beside the ring's base word (DevChannel::claim).
+__device__ __forceinline__ uint64_t split_word(uint64_t base_a, uint32_t members, uint32_t end,
+                                               uint32_t t) {
+  return base_a + 64 + end * ((8 * members + 63) & ~63u) + 8 * t;
+}
+
+// The share of a member of a group's bytes: member b's starts at b shares.
+// A member without one (the first always takes part) leaves the group alone:
+// nobody waits for it, so the group may be published, consumed and its room
+// given to later messages before it gets there.
+__device__ __forceinline__ uint64_t split_part(uint64_t bytes, uint32_t B) {
+  const uint64_t part = (bytes + B - 1) / B;
+  return part < kChunkBytes ? kChunkBytes : part;
+}
+template <bool kToRing>
+__device__ __forceinline__ void split_move(const Groups &g, const DevRing &r, uint64_t base_b,
+                                           uint64_t addr, uint32_t b, uint32_t B, uint32_t wave,
+                                           uint32_t lane) {
+  const uint64_t before = g.before(), part = split_part(g.bytes(), B);
+  // this lane's message, clipped to the share
+  const uint64_t x0 = before + b * part, x1 = x0 + part, m0 = g.incl - g.size;
+  const uint64_t c0 = m0 < x0 ? x0 : m0, c1 = g.incl < x1 ? g.incl : x1;
+  Feed<kToRing> f;
+  f.payload = r.payload;
+  f.P = r.P;
+  f.v_size = c1 > c0 ? c1 - c0 : 0;
+  f.v_pos = (base_b + g.run + c0) % r.P;
+  f.v_addr = addr + (c0 - m0);
+  f.l = g.lo;
+  f.j = g.hi;
+  move_feed<kPumpBlock / 64, kToRing>(f, wave, lane);
+}
+
+// The first member of a team waits until the others have moved their shares
+// of group number `no`.  False when the pump must stop.
+__device__ __forceinline__ bool split_gather(uint64_t words, uint64_t bytes, uint32_t B,
+                                             uint64_t no, uint32_t lane, Watch &w) {
+  const uint64_t part = split_part(bytes, B);
+  const bool on = lane > 0 && lane < B && lane * part < bytes;
+  while (__ballot(on && ld_rlx(words + 8 * lane) < no + 1)) {
+    if (w.expired()) return false;
+  }
+  return true;
+}
+
+__device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint32_t wave,
+                                   uint32_t lane, Cast *cast) {
+  const uint32_t A = role.ids[2], B = role.ids[3], t = role.ids[1], team = t / B, b = t - team * B;
+  const DevStream st = table(&a.streams[role.ids[0]]);
+  const DevRing r = table(&a.rings[st.ring]);
+  const uint64_t base_a = table(&a.chans[st.channel].claim);
+  const uint64_t words = split_word(base_a, A * B, 0, team * B);
+  const uint64_t tm_a = r.coord + offsetof(RingCoord, prod),
+                 hm_a = r.coord + offsetof(RingCoord, cons), hb_a = hm_a + 8;
+  if (st.n_msgs == 0) return;
+  Watch w{0, a.timeout_ticks, a.err, 0};
+  w.progress();
+  Groups g(a, st, r, A, lane);
+  // the ring's byte counter when the pump starts: nothing is published before
+  // the first member has read it
+  if (wave == 0) {
+    uint64_t v = 0;
+    bool stop = false;
+    if (t == 0) {
+      v = uni64(ld_rlx(hb_a)) + 1;
+      if (lane == 0) st_rlx(base_a, v);
+      if (uni64(ld_rlx(tm_a)) != r.base_m) {  // not what the host planned for
+        stop = true;
+        if (lane == 0)
+          __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    } else {
+      while ((v = uni64(ld_rlx(base_a))) == 0 && !stop) stop = w.expired();
+    }
+    if (lane == 0) {
+      cast->w[0] = v - 1;
+      cast->stop = stop;
+    }
+  }
+  __syncthreads();
+  const uint64_t base_b = uni64(cast->w[0]);
+  if (cast->stop) return;
+  uint64_t no = team;             // group number
+  uint64_t pub_m = 0, pub_b = 0;  // the counters that publish the last group
+  uint64_t last_bytes = 0;
+  uint32_t last_j = 0;            // its messages
+  for (g.skip(team + 1, lane);; g.skip(A, lane)) {
+    const bool mine = lane >= g.lo && lane < g.hi, more = g.hi > g.lo;
+    const uint64_t idx = g.first + lane;
+    const uint64_t off = mine ? a.msg_off[st.first_msg + idx] : 0;
+    // publish the group before this one: its payload and entries are in
+    // place once the stores of every wave of the team have completed
+    drain();
+    __syncthreads();
+    bool stop = false;
+    if (wave == 0 && last_j) {
+      if (b) {
+        if (lane == 0) st_rlx(words + 8 * b, no - A + 1);
+      } else {
+        stop = !split_gather(words, last_bytes, B, no - A, lane, w);
+        while (!stop && uni64(ld_rlx(tm_a)) != pub_m - last_j) stop = w.expired();
+        order();
+        if (!stop) {
+          if (a.ts_push && lane < last_j)
+            a.ts_push[st.first_msg + (pub_m - r.base_m) - last_j + lane] = wall_clock64();
+          if (lane == 0) {
+            st_rlx(tm_a + 8, pub_b);
+            st_rlx(tm_a, pub_m);
+          }
+        }
+      }
+    }
+    w.progress();
+    if (!more) return;
+    last_bytes = g.bytes();
+    last_j = 0;
+    no += A;
+    if (b && b * split_part(last_bytes, B) >= last_bytes) continue;
+    const bool bad = mine && (off > st.src_bytes || g.size > st.src_bytes - off ||
+                              g.run + g.incl > st.out_bytes);
+    if (g.bad || __ballot(bad)) {  // the same in every wave, before a byte of the group moves
+      if (wave == 0 && lane == 0)
+        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    const uint64_t end_m = r.base_m + g.first + g.hi;
+    const uint64_t end_b = base_b + g.run + lane64(g.incl, g.hi - 1);
+    if (wave == 0) {
+      while (!stop) {
+        const uint64_t hm = uni64(ld_rlx(hm_a)), hb = uni64(ld_rlx(hb_a));
+        if (end_m - hm <= r.E && end_b - hb <= r.P) break;
+        __builtin_amdgcn_s_sleep(1);
+        stop = w.expired();
+      }
+      order();
+      if (lane == 0) cast->stop = stop;
+    }
+    __syncthreads();
+    if (cast->stop) return;
+    if (b == 0 && wave == 0 && mine)
+      st_rlx(r.entries + 8 * ((r.base_m + idx) % r.E), g.size | ((uint64_t)st.producer << 48));
+    split_move<true>(g, r, base_b, st.src_base + off, b, B, wave, lane);
+    last_j = g.hi - g.lo;
+    pub_m = end_m;
+    pub_b = end_b;
+  }
+}
+
+__device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint32_t wave,
+                                   uint32_t lane, Cast *cast) {
+  const uint32_t A = role.ids[2], B = role.ids[3], t = role.ids[1], team = t / B, b = t - team * B;
+  const DevChannel u = table(&a.chans[role.ids[0]]);
+  const DevRing r = table(&a.rings[u.first_ring]);
+  const uint32_t sid = table(&a.stream_of_prod[u.prod_stream_base]);
+  const DevStream st = table(&a.streams[sid]);
+  const uint64_t words = split_word(u.claim, A * B, 1, team * B);
+  const uint64_t tm_a = r.coord + offsetof(RingCoord, prod),
+                 hm_a = r.coord + offsetof(RingCoord, cons);
+  if (st.n_msgs == 0) return;
+  Watch w{0, a.timeout_ticks, a.err, 0};
+  w.progress();
+  Groups g(a, st, r, A, lane);
+  uint64_t no = team;
+  for (g.skip(team + 1, lane); g.hi > g.lo; g.skip(A, lane), no += A) {
+    const bool mine = lane >= g.lo && lane < g.hi;
+    const uint64_t idx = g.first + lane, end_m = r.base_m + g.first + g.hi, bytes = g.bytes();
+    if (b && b * split_part(bytes, B) >= bytes) continue;
+    if (wave == 0) {
+      bool stop = false;
+      while (!stop && (int64_t)(uni64(ld_rlx(tm_a)) - end_m) < 0) {
+        __builtin_amdgcn_s_sleep(1);
+        stop = w.expired();
+      }
+      order();
+      if (lane == 0) cast->stop = stop;
+    }
+    __syncthreads();
+    if (cast->stop) return;
+    // (the ring's byte counter was there before anything was published)
+    const uint64_t base_b = uni64(ld_rlx(u.claim)) - 1;
+    const uint64_t e = mine ? ld_rlx(r.entries + 8 * ((r.base_m + idx) % r.E)) : 0;
+    // entries are checked against the plan before any byte moves
+    const bool bad = mine && ((e & kEntrySizeMask) != g.size || (e >> 48) != st.producer ||
+                              g.run + g.incl > st.out_bytes);
+    if (g.bad || __ballot(bad)) {  // the same in every wave
+      if (lane == 0)
+        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (b == 0 && wave == 0 && mine) {
+      if (a.trace) a.trace[st.trace_base + idx] = sid;
+      if (a.ts_pop) a.ts_pop[st.first_msg + idx] = wall_clock64();
+    }
+    split_move<false>(g, r, base_b, st.out_base + g.run + g.incl - g.size, b, B, wave, lane);
+    __syncthreads();  // every wave's reads of the ring have returned
+    if (wave == 0) {
+      bool stop = false;
+      if (b) {
+        if (lane == 0) st_rlx(words + 8 * b, no + 1);
+      } else {
+        const uint64_t start = end_m - (g.hi - g.lo);
+        stop = !split_gather(words, bytes, B, no, lane, w);
+        while (!stop && uni64(ld_rlx(hm_a)) != start) stop = w.expired();
+        order();
+        if (!stop)
+          st_pair(hm_a, end_m, base_b + g.run + lane64(g.incl, g.hi - 1), lane == 0);
+      }
+      if (lane == 0) cast->late_stop = stop;
+    }
+    __syncthreads();
+    if (cast->late_stop) return;
+    w.progress();
+  }
+}
+
+// kSplit: the rings that have one producer are split (no endpoint is a wave
+// or a workgroup of its own but a locking ring's); the forms are two kernels
+// because one with all of them spills registers.
+template <bool kSplit>
 __global__ __launch_bounds__(kPumpBlock) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void pump_kernel(PumpArgs a) {
   __shared__ Cast cast;
   const DevRole role = table(&a.roles[blockIdx.x]);
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform in the wave
-  switch (role.kind) {
-    case kRoleProducerWaves:
-      if (wave < role.count) run_producer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
-      break;
-    case kRoleProducerGroup:
-      run_producer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
-      break;
-    case kRoleConsumerWaves:
-      if (wave < role.count) run_consumer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
-      break;
-    case kRoleConsumerGroup:
-      run_consumer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
-      break;
-    default:
-      run_lock_team(a, role.ids[0], wave, lane, &cast);
+  if (role.kind == kRoleLockMember) {
+    run_lock_team(a, role.ids[0], wave, lane, &cast);
+  } else if (role.kind == kRoleProducerGroup) {
+    run_producer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
+  } else if constexpr (kSplit) {
+    if (role.kind == kRoleProducerSplit)
+      run_split_producer(a, role, wave, lane, &cast);
+    else
+      run_split_consumer(a, role, wave, lane, &cast);
+  } else if (role.kind == kRoleProducerWaves) {
+    if (wave < role.count) run_producer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
+  } else if (role.kind == kRoleConsumerWaves) {
+    if (wave < role.count) run_consumer<1>(a, a.roles[blockIdx.x].ids[wave], 0, lane, nullptr);
+  } else {
+    run_consumer<kPumpBlock / 64>(a, role.ids[0], wave, lane, &cast);
   }
 }
 
@@ -731,8 +1008,8 @@ __global__ __launch_bounds__(256) void push_kernel(PushArgs a) {
     __hip_atomic_store(a.publish, a.publish_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t launch_pump(const PumpArgs &a, uint32_t n_wgs, hipStream_t stream) {
-  hipLaunchKernelGGL(pump_kernel, dim3(n_wgs), dim3(kPumpBlock), 0, stream, a);
+hipError_t launch_pump(const PumpArgs &a, bool split, uint32_t n_wgs, hipStream_t stream) {
+  hipLaunchKernelGGL(split ? pump_kernel<true> : pump_kernel<false>, dim3(n_wgs), dim3(kPumpBlock), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -741,8 +1018,15 @@ hipError_t launch_push(const PushArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// (both forms may be in flight together)
 int pump_occupancy(int *wgs_per_cu) {
-  return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(wgs_per_cu, pump_kernel, kPumpBlock, 0);
+  int split = 0;
+  int e = (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(wgs_per_cu, pump_kernel<false>,
+                                                            kPumpBlock, 0);
+  if (e == 0)
+    e = (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(&split, pump_kernel<true>, kPumpBlock, 0);
+  if (split < *wgs_per_cu) *wgs_per_cu = split;
+  return e;
 }
 
 }  // namespace hicr

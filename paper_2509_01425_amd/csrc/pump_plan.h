@@ -21,12 +21,15 @@ struct PumpPlan {
   bool ind_groups = false;     // so are the other producers and their consumers
   std::vector<uint32_t> team;  // workgroups that drain each locking ring
   uint64_t ind_units = 0;      // consumers of the other rings
+  uint32_t split = 1;          // workgroups of each of their ends,
+  uint32_t share = 1;          // this many to a team that shares a group of messages
   uint64_t wgs = 0;            // workgroups in all
 };
 
-// cap workgroups; n_lock producers on locking rings that want teams of `want`
+// cap workgroups, on n_cu compute units; n_lock producers on locking rings that want teams of `want`
 // workgroups (at least 1 each), n_ind producers on rings of their own; a
-// consumer holds at most `max_rings` rings.
+// consumer holds at most `max_rings` rings; an end of a ring of its own may
+// be split over `max_split` workgroups.
 //
 // Groups or waves.  A producer that is one wave has 8 KiB in flight, so a few
 // streams are bound by it (serving 16 bursts of up to 256 messages to
@@ -37,8 +40,20 @@ struct PumpPlan {
 // locking ring keeps a team of two; then, if all of it fits, the other
 // producers and consumers.  Rings share a consumer wave only when there are
 // more of them than waves.
+//
+// Splits.  One compute unit copies 20-26 GB/s however many waves it runs (a
+// pump of 16 such bursts took 471 us with blocks of 256 threads, 497 with
+// 1,024), so while a pump leaves compute units unused both ends of its rings
+// are split: those 16 bursts 509 -> 203 us, two streams 454 -> 175, 60 streams
+// (split in two) 540 -> 398, 16 streams of 4,096 messages to 64 B 1,570 -> 875;
+// 100 streams are as before (640).  From four workgroups on two share each
+// group of messages, since the largest message otherwise sets the time of its
+// turn (16 bursts: 1 workgroup to a group 256 us, 2: 207, 4: 248).  One
+// workgroup per compute unit is the limit, which leaves other pumps room
+// beside this one.
 inline PumpPlan plan_endpoints(uint64_t cap, uint64_t n_lock, uint64_t n_ind,
-                               const std::vector<uint64_t> &want, uint64_t max_rings) {
+                               const std::vector<uint64_t> &want, uint64_t max_rings,
+                               uint64_t n_cu = 0, uint64_t max_split = 1) {
   PumpPlan p;
   const uint64_t prod = (n_lock + n_ind + 3) / 4, rings = want.size();
   const uint64_t min_units = (n_ind + max_rings - 1) / max_rings;
@@ -70,6 +85,13 @@ inline PumpPlan plan_endpoints(uint64_t cap, uint64_t n_lock, uint64_t n_ind,
                                             : prod;
   p.ind_units = p.ind_groups ? n_ind : std::min(n_ind, 4 * (cap - prod_wgs - total));
   p.wgs = prod_wgs + total + (p.ind_groups ? n_ind : (p.ind_units + 3) / 4);
+  const uint64_t room = std::min(cap, n_cu);
+  if (p.ind_groups && n_ind && max_split > 1 && p.wgs < room) {
+    p.split = (uint32_t)std::min(max_split, (room - n_lock - total) / (2 * n_ind));
+    if (p.split >= 4) p.share = 2;
+    p.split -= p.split % p.share;
+    p.wgs += 2 * n_ind * (p.split - 1);
+  }
   return p;
 }
 

@@ -750,6 +750,7 @@ int hicr_ctx_destroy(hicr_ctx c) {
     if (c->h_done) (void)hipHostFree(c->h_done);
     if (c->na_up_ev) (void)hipEventDestroy(c->na_up_ev);
     if (c->na_ev) (void)hipEventDestroy(c->na_ev);
+    for (hipStream_t s : c->serve_streams) (void)hipStreamDestroy(s);
     if (c->aux) (void)hipStreamDestroy(c->aux);
     if (c->up) (void)hipStreamDestroy(c->up);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

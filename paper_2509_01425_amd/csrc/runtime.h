@@ -161,6 +161,7 @@ struct hicr_ctx_s {
   std::vector<hicr::PumpBuf> pump_free;  // finished pumps' buffers, for reuse
   std::vector<hicr::PumpLive> pump_live;  // pumps launched and not yet finished
   int pump_occ = 0;  // pump workgroups per CU
+  std::vector<hipStream_t> serve_streams;  // of hicr_serve, kept for its next call
   // host-API channel pushes and network steps queued on `stream`: how many,
   // how many of them are known to have ended, and the event of the last
   uint64_t push_seq = 0, push_done = 0;
