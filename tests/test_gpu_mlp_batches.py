@@ -1,6 +1,6 @@
 """The training kernels at the batch sizes where their work split changes: a
-single sample, fewer samples than a workgroup's four waves, remainders, one
-more round than the persistent grid, against the fp64 oracle.
+single sample, the most that have a workgroup each, fewer than a workgroup's
+four waves leave over, one more round than the persistent grid, against the fp64 oracle.
 
 Tolerances: a logit is three chained sums of at most 64 products, so its
 rounding error is a few tens of fp32 epsilons (6e-8) of its terms; gradients
@@ -17,7 +17,7 @@ from workloads.mlp_init import he_uniform
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B", [1, 3, 5, 31, 257, 1025, 4099])
+@pytest.mark.parametrize("B", [1, 3, 5, 31, 257, 512, 513, 1025, 4099])
 def test_mlp_batch_sizes(B):
     import torch
     from paper_2509_01425_amd import hicr as H
