@@ -297,6 +297,26 @@ __global__ __launch_bounds__(kCopyBlock) void upload_kernel(const uint64_t *h, u
 // `first` up to byte `end` of request `last` (0 of request n: to its end), as
 // one sequence of chunks: lane l holds request base + l, and the chunk
 // pipeline runs on from one request into the next.
+__device__ __forceinline__ void stream_lanes(uint64_t v_d, uint64_t v_s, uint64_t v_n, uint32_t l,
+                                             uint32_t j, uint32_t lane) {
+  uint64_t d = 0, s = 0, left = 0;
+  move_chunks<kPlainLoad, kStorePolicy>(
+      [&]() {
+        while (left == 0 && l < j) {
+          left = lane64(v_n, l);
+          d = lane64(v_d, l);
+          s = lane64(v_s, l);
+          l++;
+        }
+        const uint64_t line = kChunkBytes - (d & (kLineBytes - 1));
+        const Chunk c = {d, s, (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)min(line, left))};
+        left -= c.n;
+        d += c.n;
+        s += c.n;
+        return c;
+      },
+      lane);
+}
 __device__ __forceinline__ void stream_range(const DevBatch &b, uint64_t first, uint64_t off,
                                              uint64_t last, uint64_t end, uint32_t lane) {
   for (uint64_t base = first; base <= last && base < b.n; base += 64) {
@@ -308,26 +328,7 @@ __device__ __forceinline__ void stream_range(const DevBatch &b, uint64_t first, 
       v_d = b.dst[i] + lo;
       v_s = b.src[i] + lo;
     }
-    const uint32_t j = (uint32_t)min(last + 1 - base, (uint64_t)64);
-    uint32_t l = 0;
-    uint64_t d = 0, s = 0, left = 0;
-    move_chunks<kPlainLoad, kStorePolicy>(
-        [&]() {
-          while (left == 0 && l < j) {
-            left = lane64(v_n, l);
-            d = lane64(v_d, l);
-            s = lane64(v_s, l);
-            l++;
-          }
-          const uint64_t line = kChunkBytes - (d & (kLineBytes - 1));
-          const Chunk c = {d, s,
-                           (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)min(line, left))};
-          left -= c.n;
-          d += c.n;
-          s += c.n;
-          return c;
-        },
-        lane);
+    stream_lanes(v_d, v_s, v_n, 0, (uint32_t)min(last + 1 - base, (uint64_t)64), lane);
   }
 }
 
@@ -382,9 +383,8 @@ __global__ __launch_bounds__(kCopyBlock) void copy_kernel_mem(DevBatch b, DevSch
 // host has cut the shares, so nothing is scanned or searched here, and the
 // requests are read where they are: for a submission in pinned host memory,
 // each wave its own few, over the host link, which takes less than queuing an
-// upload in front (with upload, copy and counter kernels and an event: a
-// single 16 KiB request submit to fence 16.5 us, 256 requests to 8 KiB 19.4,
-// 512 requests to 1 MiB 57; now 10.7, 14.8 and 35 = 3.6 TB/s, its kernel
+// upload in front (with upload, copy and counter kernels and an event: 512
+// requests to 1 MiB submit to fence 57 us; now 35 = 3.6 TB/s, its kernel
 // 26 us = 4.9 TB/s).  Bound: launch, host link and memory latencies below a
 // few MiB, HBM above.
 __global__ __launch_bounds__(kCopyBlock) void stream_kernel(DevBatch b, const StreamStart *starts,
@@ -396,6 +396,130 @@ __global__ __launch_bounds__(kCopyBlock) void stream_kernel(DevBatch b, const St
     stream_range(b, uni64(starts[w].req), uni64(starts[w].off), uni64(starts[w + 1].req),
                  uni64(starts[w + 1].off), lane);
   signal_done(done);
+}
+
+// The same for up to N requests, held in the kernel's arguments: in pinned
+// memory it takes a wave two trips over the host link, to its share and to its
+// requests, before its first load (submit to fence of one request of 4 KiB
+// 11.6 -> 9.5 us, 64 to 8 KiB 13.3 -> 11.3, 256 to 8 KiB 14.4 -> 13.2, 256 to
+// 256 KiB 23.2 -> 20.9; a plan's requests lie in device memory, which is
+// nearer than arguments: a replay of 16 to 4 KiB 9.2 us that way, 9.6 with
+// arguments).  4 KiB of arguments hold no more.  Addresses are held as
+// 32-bit distances from the lowest of the batch, sizes as the bytes up to the
+// end of the request, from which every wave finds its share: what lies
+// between w and w + 1 times `share` bytes, cut at lines of the destinations.
+template <uint32_t N>
+struct ArgBatch {
+  Done done;
+  uint64_t dst, src;
+  uint32_t n, waves, share, bytes;
+  uint32_t end[N], d[N], s[N];  // end: ~0 past the last request
+};
+template <uint32_t N>
+__global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) {
+  using Args = ArgBatch<N>;
+  constexpr uint32_t K = N / 64;
+  // (arrays in arguments are read by address, or they would be copied to
+  // scratch memory first)
+  const GLOBAL uint32_t *t = (const GLOBAL uint32_t *)(
+      (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(Args, end));
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t w =
+      __builtin_amdgcn_readfirstlane(blockIdx.x * (kCopyBlock / 64) + (threadIdx.x >> 6));
+  if (w < a.waves) {
+    // every wave reads them all, so that only one trip to memory comes before
+    // its first load: lane l holds requests l, l + 64, ...
+    uint32_t e[K], f[K], d[K], s[K];  // f: where it starts
+#pragma unroll
+    for (uint32_t k = 0; k < K; k++) {
+      const uint32_t i = lane + 64 * k;
+      e[k] = t[i];
+      f[k] = t[i ? i - 1 : 0];
+      d[k] = t[N + i];
+      s[k] = t[2 * N + i];
+    }
+    if (lane == 0) f[0] = 0;
+    // the request where the share starts and ends (n: past the last), and the
+    // byte of it
+    uint32_t i[2];
+    uint64_t off[2];
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const uint64_t x = (uint64_t)(w + j) * a.share;
+      uint32_t c = 0, r = 0, from = 0, to = 0, upto = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < K; k++) c += (uint32_t)__popcll(__ballot(e[k] <= x));
+      r = min(c, a.n - 1);
+#pragma unroll
+      for (uint32_t k = 0; k < K; k++)
+        if (r / 64 == k) {
+          from = __builtin_amdgcn_readlane(f[k], r % 64);
+          upto = __builtin_amdgcn_readlane(e[k], r % 64);
+          to = __builtin_amdgcn_readlane(d[k], r % 64);
+        }
+      const uint64_t dst = a.dst + to, at = x - from;
+      off[j] = min(((dst + at + kLineBytes - 1) & ~(uint64_t)(kLineBytes - 1)) - dst,
+                   (uint64_t)(upto - from));
+      if (at == 0 || x >= a.bytes) off[j] = 0;
+      i[j] = x >= a.bytes ? a.n : c;
+    }
+    if (w == 0) i[0] = 0;  // (leading empty requests)
+    for (uint32_t k = i[0] / 64; k < K && 64 * k <= i[1]; k++) {
+      uint32_t ek = e[0], fk = f[0], dk = d[0], sk = s[0];
+#pragma unroll
+      for (uint32_t m = 1; m < K; m++)
+        if (k == m) ek = e[m], fk = f[m], dk = d[m], sk = s[m];
+      const uint32_t r = lane + 64 * k;
+      const uint64_t lo = r == i[0] ? off[0] : 0, hi = r == i[1] ? off[1] : ek - fk;
+      stream_lanes(a.dst + dk + lo, a.src + sk + lo, r >= i[0] && r <= i[1] && r < a.n ? hi - lo : 0,
+                   max(i[0], 64 * k) - 64 * k, min(i[1] + 1 - 64 * k, 64u), lane);
+    }
+  }
+  signal_done(a.done);
+}
+
+template <uint32_t N>
+static void launch_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src, uint64_t bytes,
+                        uint32_t waves, Done done, hipStream_t stream) {
+  ArgBatch<N> a;
+  static_assert(sizeof(a) <= 4096, "kernel arguments");
+  static_assert(N % 64 == 0 && offsetof(ArgBatch<N>, s) == offsetof(ArgBatch<N>, end) + 8 * N,
+                "three arrays of N");
+  a.done = done;
+  a.dst = dst;
+  a.src = src;
+  a.n = n;
+  a.waves = waves;
+  a.share = (uint32_t)((bytes + waves - 1) / waves);
+  a.bytes = (uint32_t)bytes;
+  uint32_t end = 0;
+  for (uint32_t i = 0; i < n; i++) {
+    a.end[i] = end += (uint32_t)h[2 * n + i];
+    a.d[i] = (uint32_t)(h[i] - dst);
+    a.s[i] = (uint32_t)(h[n + i] - src);
+  }
+  std::fill(a.end + n, a.end + N, ~0u);
+  hipLaunchKernelGGL(stream_args_kernel<N>, dim3(stream_grid(waves)), dim3(kCopyBlock), 0, stream,
+                     a);
+}
+
+bool args_fit(const uint64_t *h, uint64_t n, uint64_t bytes, uint64_t *dst, uint64_t *src) {
+  constexpr uint64_t kSpan = 0xffffffffull;  // (~0 marks the end)
+  if (!n || n > kArgReqs || bytes >= kSpan) return false;
+  const auto d = std::minmax_element(h, h + n), s = std::minmax_element(h + n, h + 2 * n);
+  *dst = *d.first;
+  *src = *s.first;
+  return *d.second - *dst <= kSpan && *s.second - *src <= kSpan;
+}
+
+hipError_t launch_stream_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src,
+                              uint64_t bytes, uint32_t waves, Done done, hipStream_t stream) {
+  if (!n || n > kArgReqs || !waves) return hipErrorInvalidValue;
+  if (n <= 64)
+    launch_args<64>(h, n, dst, src, bytes, waves, done, stream);
+  else
+    launch_args<kArgReqs>(h, n, dst, src, bytes, waves, done, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_stream(const DevBatch &b, const StreamStart *starts, uint32_t waves, Done done,

@@ -541,12 +541,17 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   s.host_counted = 0;
   hipError_t e = hipSuccess;
   if (waves) {
-    // small enough that the kernel reads the requests where they are
-    StreamStart *starts = reinterpret_cast<StreamStart *>(h + 4 * n);
-    stream_starts(h, h + 2 * n, n, k.bytes, waves, kLineBytes, starts);
-    const DevBatch b{hv, hv + n, hv + 2 * n, hv + 3 * n, (uint32_t)n};
-    e = launch_stream(b, reinterpret_cast<const StreamStart *>(hv + 4 * n), waves,
-                      arm(*sig, stream_grid(waves)), stream);
+    const Done done = arm(*sig, stream_grid(waves));
+    uint64_t dst, src;
+    if (args_fit(h, n, k.bytes, &dst, &src)) {
+      e = launch_stream_args(h, (uint32_t)n, dst, src, k.bytes, waves, done, stream);
+    } else {
+      // small enough that the kernel reads the requests where they are
+      StreamStart *starts = reinterpret_cast<StreamStart *>(h + 4 * n);
+      stream_starts(h, h + 2 * n, n, k.bytes, waves, kLineBytes, starts);
+      const DevBatch b{hv, hv + n, hv + 2 * n, hv + 3 * n, (uint32_t)n};
+      e = launch_stream(b, reinterpret_cast<const StreamStart *>(hv + 4 * n), waves, done, stream);
+    }
     if (e != hipSuccess) rc = hip_fail(c, e, "launching the stream kernel");
   } else {
     const DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};

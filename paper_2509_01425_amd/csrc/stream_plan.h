@@ -40,18 +40,26 @@ inline uint32_t stream_waves(uint64_t n, uint64_t bytes, uint64_t n_cu, uint64_t
   return (uint32_t)std::min(most, std::max<uint64_t>(1, (bytes + kStreamShare - 1) / kStreamShare));
 }
 
-// Equal shares of the batch's bytes, cut at `line`-byte lines of the
-// destinations: wave w copies what lies between out[w] and out[w + 1]
-// (out[waves] is the end of the batch).
+// Equal shares of the batch's bytes, cut at `line`-byte lines (a power of two)
+// of the destinations: wave w copies what lies between out[w] and out[w + 1]
+// (out[waves] is the end of the batch).  A division per wave would cost 2 us of
+// host time for 1,024 waves.
 inline void stream_starts(const uint64_t *dst, const uint64_t *size, uint64_t n, uint64_t bytes,
                           uint32_t waves, uint64_t line, StreamStart *out) {
+  const uint64_t share = bytes / waves, rest = bytes % waves;
   uint64_t i = 0, before = 0;  // bytes of the requests before i
+  uint64_t at = 0, part = 0;   // bytes * w / waves, and the remainder
   for (uint32_t w = 0; w < waves; w++) {
-    const uint64_t at = bytes * w / waves;
     while (i < n && before + size[i] <= at) before += size[i++];
     uint64_t off = i < n ? at - before : 0;
-    if (off) off = std::min((dst[i] + off + line - 1) / line * line - dst[i], size[i]);
+    if (off) off = std::min(((dst[i] + off + line - 1) & ~(line - 1)) - dst[i], size[i]);
     out[w] = StreamStart{off, i};
+    at += share;
+    part += rest;
+    if (part >= waves) {
+      part -= waves;
+      at++;
+    }
   }
   out[waves] = StreamStart{0, n};
 }

@@ -25,7 +25,7 @@ def gpu():
 
 
 @pytest.mark.parametrize("n,sizes", [(1, [s]) for s in EDGES + [16384, (1 << 20) + 3]] + [
-    (2, EDGES), (63, EDGES), (64, EDGES), (65, EDGES), (129, [0]), (300, EDGES), (4096, EDGES),
+    (2, EDGES), (63, EDGES), (64, EDGES), (65, EDGES), (129, [0]), (256, [1, 17, 128, 3000]), (257, [1, 17, 128, 3000]), (255, EDGES), (300, EDGES), (4096, EDGES),
     (4097, EDGES), (20000, [1, 16, 200, 5632])])
 def test_batch_sizes(gpu, n, sizes):
     torch, H, wd = gpu
@@ -89,3 +89,38 @@ def test_batch_sizes(gpu, n, sizes):
                                                             "src_off", "size"))) == H.OK
         check(1)
     assert H.hicr_ctx_destroy(ctx) == H.OK
+
+
+@pytest.mark.parametrize("far", ["dst", "src"])
+def test_small_batch_across_4_gib(gpu, far):
+    """Few requests whose addresses lie 2^32 - 1, 2^32 and more bytes apart:
+    kernel arguments hold them as 32-bit distances, or they go the other way."""
+    torch, H, wd = gpu
+    span = 1 << 32
+    pool = torch.empty(span + (1 << 20), dtype=torch.uint8, device="cuda")
+    small = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+    small.copy_(torch.arange(1 << 20, device="cuda").remainder(251))
+    for last in (span - 1, span, span + 4321):
+        print("far apart", far, last, flush=True)
+        rc, ctx = H.hicr_ctx_create(0, 0)
+        assert rc == H.OK
+        a = H.hicr_slot_register(ctx, pool.data_ptr(), pool.numel())[1]
+        b = H.hicr_slot_register(ctx, small.data_ptr(), small.numel())[1]
+        at, size = [0, 7777, last], 3000
+        d = np.zeros(3, dtype=H.DESC_DTYPE)
+        for i, o in enumerate(at):
+            pool[o:o + size] = 255
+            if far == "dst":
+                d[i] = (a, b, o, 5000 * i + 1, size)
+            else:
+                pool[o:o + size] = small[5000 * i + 1:5000 * i + 1 + size]
+                d[i] = (b, a, 500_000 + 5000 * i, o, size)
+        torch.cuda.synchronize()
+        assert H.hicr_memcpy_batch(ctx, d)[0] == H.OK, H.hicr_last_error(ctx)
+        assert H.hicr_fence(ctx) == H.OK
+        for i, o in enumerate(at):
+            got = (pool[o:o + size] if far == "dst"
+                   else small[500_000 + 5000 * i:500_000 + 5000 * i + size])
+            want = small[5000 * i + 1:5000 * i + 1 + size]
+            assert torch.equal(got, want), (far, last, i)
+        assert H.hicr_ctx_destroy(ctx) == H.OK
