@@ -140,6 +140,7 @@ struct PushArgs {
   uint32_t n_entries;  // messages written (k tokens or 1)
   uint32_t producer;
   uint64_t entry_bytes;  // size written in each entry
+  uint32_t *arrive;    // the context's arrival counter of pushes, 0 between launches
   uint64_t *publish;   // host-coherent published counter
   uint64_t publish_value;
 };

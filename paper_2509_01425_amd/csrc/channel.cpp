@@ -279,6 +279,7 @@ int hicr_channel_push(hicr_channel ch, uint32_t producer, hicr_slot src, uint64_
     pa.n_entries = (uint32_t)n_ent;
     pa.producer = producer;
     pa.entry_bytes = ent_bytes;
+    pa.arrive = c->push_sig.arrive;
     pa.publish = &ch->coord_dev[r].prod.w[0];
     pa.publish_value = h.tm + n_ent;
     hipError_t e = launch_push(pa, c->stream);

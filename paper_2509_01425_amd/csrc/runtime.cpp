@@ -214,15 +214,16 @@ static int ensure_device(hicr_ctx c, Sub &s, uint64_t n) {
 
 // The counter table is allocated once, for kMaxSlots slots (16 MiB), so its
 // address never changes: captured plans keep a valid pointer to it.  The
-// submission buffers' arrival counters lie behind it.
+// submission buffers' and the pushes' arrival counters lie behind it.
 static int alloc_counters(hicr_ctx c) {
-  const size_t bytes = (size_t)kMaxSlots * 16 + 128 * kNumSubs;
+  const size_t bytes = (size_t)kMaxSlots * 16 + 128 * (kNumSubs + 1);
   hipError_t e = hipMalloc(&c->d_counters, bytes);
   if (e == hipSuccess) e = hipMemset(c->d_counters, 0, bytes);
   if (e != hipSuccess) return hip_fail(c, e, "allocating the counter table");
   c->counter_cap = kMaxSlots;
-  for (int i = 0; i < kNumSubs; i++)
-    c->subs[i].sig.arrive = reinterpret_cast<uint32_t *>(c->d_counters + 2 * (size_t)kMaxSlots) + 32 * i;
+  uint32_t *arrive = reinterpret_cast<uint32_t *>(c->d_counters + 2 * (size_t)kMaxSlots);
+  for (int i = 0; i < kNumSubs; i++) c->subs[i].sig.arrive = arrive + 32 * i;
+  c->push_sig.arrive = arrive + 32 * kNumSubs;
   return HICR_OK;
 }
 
