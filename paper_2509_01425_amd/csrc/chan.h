@@ -29,9 +29,9 @@ struct alignas(128) CoordLine {
 //   cons.w[0]  hm      messages released by the consumer
 //   cons.w[1]  hb      bytes released by the consumer
 //   lock.w[0]  ticket  next ticket (locking MPSC)
-//   lock.w[1]  serving ticket allowed in
-//   lock.w[2]  rm      messages reserved (locking MPSC, under the lock)
-//   lock.w[3]  rb      bytes reserved     (locking MPSC, under the lock)
+//   lock.w[2]  turn    ticket allowed in (low half), messages reserved (low 32
+//                      bits, in the high half)
+//   lock.w[3]  rb      bytes reserved (written with the turn, as one unit)
 struct RingCoord {
   CoordLine prod;
   CoordLine cons;

@@ -10,7 +10,7 @@
 //             hb mod P, then publish hb + s and hm + 1 -- the notification
 //             that frees the producer's room.
 // Locking MPSC: a ticket lock (FIFO-fair) guards the room check and the
-// reservation of [rb, rb + s) / entry rm; the copy runs outside the lock and
+// reservation of [rb, rb + s) / entry rm, which are handed on with the turn; the copy runs outside the lock and
 // publication follows ticket order, so the shared ring holds one total order
 // and never overflows.  Non-locking MPSC: one ring per producer.
 //
@@ -23,9 +23,9 @@
 // release fence writes back the whole L2 of its XCD and an acquire
 // invalidates it; with one of each per batch those write-backs bounded the
 // pump (1,536 streams, 500 K messages of 16 B - 64 KiB: 6.28 ms with the
-// fences and plain payload accesses, 2.59 ms now = 6.0 TB/s of source, ring
-// and output bytes; 1,024 SPSC streams and 64 locking rings, 150 K messages to
-// 256 KiB: 7.6 ms, 3.48 ms now, set by the locking rings' ordered steps).
+// fences and plain payload accesses, 2.8 ms now = 5.6 TB/s of source, ring
+// and output bytes, what a large copy reaches; 1,024 SPSC streams and 64
+// locking rings, 150 K messages to 256 KiB: 7.6 ms, 3.1 ms now = 5.2 TB/s).
 //
 // pump_kernel is persistent: an endpoint (the producer of one stream, the
 // consumer of one or more single-producer rings) is either one wave, four of
@@ -140,6 +140,15 @@ __device__ __forceinline__ void st_pair(uint64_t a, uint64_t w0, uint64_t w1, bo
   bstore<16>(span_rsrc(a, 16), on ? 0u : ~0u, v);
 }
 
+// Read such a unit with one access, the same in every lane.
+__device__ __forceinline__ v4i ld_pair(uint64_t a) { return bload<16>(span_rsrc(a, 16), 0); }
+__device__ __forceinline__ uint64_t lo64(v4i v) {
+  return (uint32_t)v.x | (uint64_t)(uint32_t)v.y << 32;
+}
+__device__ __forceinline__ uint64_t hi64(v4i v) {
+  return (uint32_t)v.z | (uint64_t)(uint32_t)v.w << 32;
+}
+
 // Ring bytes are written without nt: the consumer reads most of them soon
 // after, and they then come from the memory-side cache (4.03 against 4.42 ms
 // a pass on the first configuration above; reading the ring without nt
@@ -212,6 +221,20 @@ struct Cast {
 constexpr uint32_t kProdBatch = 16;
 constexpr uint32_t kLockShare = 8;
 
+// Who goes first.  Beside 1,024 SPSC streams the locking rings, which move
+// their bytes in ordered steps, were left for last (their ends 2.6-3.6 ms into
+// a pass of 3.84 ms, the others' 1.1-3.3): their waves now have priority in
+// their SIMD, consumers (3) over producers (2): 3.54 ms; and so have the
+// consumers of other rings (1) over the producers (0), which keeps what a ring
+// holds nearer to its use: 3.42 ms, and without locking rings 3.03 -> 2.98.
+// A single wave also starts no message while its ring is filled to more than
+// a quarter (or kWaveFill bytes), which gives way to the locking rings without
+// keeping its consumer waiting: 3.27 ms.  (A half 3.33; with rings of 256 KiB
+// a quarter made 900 streams 4 % slower, kWaveFill nothing; whole workgroups
+// drain their rings fast enough as it is, 300 streams 1,130 -> 1,320 us.)
+// Giving the larger streams priority over the smaller made a pass 2 % slower.
+constexpr uint64_t kWaveFill = 128 << 10;
+
 // The producer of one stream (WAVES waves): it takes as many of its next
 // messages as the ring has room for, copies them as one batch and writes
 // their entries.  A batch is published at the top of the next turn, after
@@ -225,10 +248,11 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
   const DevStream st = table(&a.streams[sid]);
   const DevRing r = table(&a.rings[st.ring]);
   const bool locking = table(&a.chans[st.channel].mode) == kModeMpscLock;
+  const uint64_t fill = locking || WAVES > 1 ? r.P : r.P / 4 > kWaveFill ? r.P / 4 : kWaveFill;
+  if (locking) __builtin_amdgcn_s_setprio(2);
   const uint64_t c = r.coord;
   const uint64_t tm_a = c + offsetof(RingCoord, prod), hm_a = c + offsetof(RingCoord, cons),
-                 hb_a = hm_a + 8, tk_a = c + offsetof(RingCoord, lock), sv_a = tk_a + 8,
-                 rm_a = tk_a + 16, rb_a = tk_a + 24;
+                 hb_a = hm_a + 8, tk_a = c + offsetof(RingCoord, lock), tn_a = tk_a + 16;
   // rings are empty when a pump starts: the producer side resumes at the
   // consumer's released counters
   uint64_t tm = uni64(ld_rlx(tm_a)), tb = uni64(ld_rlx(hb_a));
@@ -287,7 +311,18 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
           ticket = __hip_atomic_fetch_add((uint64_t *)tk_a, 1ull, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
         ticket = shfl64(ticket, 0);
-        while (uni64(ld_rlx(sv_a)) != ticket) {
+        // the turn comes with the reservation counters in one 16-byte unit: a
+        // lock handed over by one store and taken with one read (one ring of
+        // 8 producers 1,850 us with a word each, 1,810 so; reading the
+        // consumer's counters in the same loop 2,010: more to poll)
+        for (;;) {
+          order();
+          const v4i turn = ld_pair(tn_a);
+          if (uni64(lo64(turn)) << 32 == ticket << 32) {
+            my_tm = r.base_m + (uint32_t)((uint32_t)(uni64(lo64(turn)) >> 32) - (uint32_t)r.base_m);
+            my_tb = uni64(hi64(turn));
+            break;
+          }
           __builtin_amdgcn_s_sleep(1);
           if (w.expired()) {
             stop = true;
@@ -295,8 +330,6 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
           }
         }
         order();
-        my_tm = uni64(ld_rlx(rm_a));
-        my_tb = uni64(ld_rlx(rb_a));
       }
       // wait until at least the first message fits, then take every leading
       // message that fits in the room seen (one view of the consumer for the
@@ -305,7 +338,7 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
       while (!stop) {
         hm = uni64(ld_rlx(hm_a));
         hb = uni64(ld_rlx(hb_a));
-        if (my_tm - hm < r.E && my_tb - hb + s0 <= r.P) break;
+        if (my_tm - hm < r.E && my_tb - hb <= fill && my_tb - hb + s0 <= r.P) break;
         __builtin_amdgcn_s_sleep(2);
         if (w.expired()) stop = true;
       }
@@ -328,18 +361,13 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
     }
     if (stop) return;
     const bool fits = have && (my_tm + lane + 1 - hm <= r.E) && (my_tb + incl - hb <= r.P) &&
+                      my_tb + incl - sz - hb <= fill &&
                       (!locking || lane == 0 || incl <= r.P / kLockShare);
     const uint64_t fm = __ballot(fits);
     const uint32_t j = (uint32_t)__ffsll((unsigned long long)~fm) - 1;  // leading fitting lanes
     const uint64_t bytes = shfl64(incl, (int)j - 1);
-    if (locking && wave == 0) {
-      if (lane == 0) {
-        st_rlx(rm_a, my_tm + j);
-        st_rlx(rb_a, my_tb + bytes);
-      }
-      drain();  // the next holder of the lock sees both
-      if (lane == 0) st_rlx(sv_a, ticket + 1);
-    }
+    if (locking && wave == 0)
+      st_pair(tn_a, (uint32_t)(ticket + 1) | (my_tm + j) << 32, my_tb + bytes, lane == 0);
     // entries (and, on a locking ring, the records the consumer team reads)
     // are written now; the wait before publication covers them
     if (wave == 0 && lane < j) {
@@ -388,6 +416,7 @@ __device__ void run_consumer(const PumpArgs &a, uint32_t uid_in, uint32_t wave, 
                              Cast *cast) {
   const uint32_t uid = __builtin_amdgcn_readfirstlane(uid_in);
   const DevChannel u = table(&a.chans[uid]);
+  __builtin_amdgcn_s_setprio(1);
   const bool mine = lane < u.n_rings;
   uint64_t coord = 0, hm = 0, hb = 0, pos = 0, out_pos = 0, cnt = 0;
   if (mine) {
@@ -520,6 +549,7 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave,
   const uint64_t hm_a = r.coord + offsetof(RingCoord, cons);
   const uint64_t last = r.base_m + u.total_msgs;  // counter after this pump's messages
   uint64_t *rounds = (uint64_t *)u.rounds;
+  __builtin_amdgcn_s_setprio(3);
   Watch w{0, a.timeout_ticks, a.err, 0};
   w.progress();
   for (;;) {
