@@ -212,9 +212,8 @@ int hicr_fence_slot(hicr_ctx ctx, hicr_slot slot, uint64_t exp_sent, uint64_t ex
 /* ------------------------------------------ persistent batch plans (growth) */
 /* Sec. 3.1.4 memcpy batches that repeat unchanged (a halo exchange, a fixed
  * gather): the batch is validated, resolved to addresses and uploaded once;
- * every hicr_plan_launch queues its fused copy launches and counter kernel
- * again -- directly, or, with HICR_PLAN_GRAPH, as one launch of a HIP graph
- * captured at creation.  One replay moves every request once
+ * every hicr_plan_launch queues its fused copy launches again -- directly,
+ * or, with HICR_PLAN_GRAPH, as one launch of a HIP graph captured at creation.  One replay moves every request once
  * and raises each request's sent/recv counters once, like one
  * hicr_memcpy_batch of the same requests; hicr_fence (and fence_slot) wait
  * for replays as for any other transfer.

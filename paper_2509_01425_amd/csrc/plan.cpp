@@ -3,10 +3,10 @@
 // A plan is a batch of memcpy requests (HiCR Sec. 3.1.4) that a caller
 // repeats unchanged.  Validation, address resolution, the upload, the split
 // into copy launches and (for batches of more than 4,096 requests) the scan
-// of the piece table happen once.  A replay queues the fused copy launches
-// and the counter kernel again, either directly or --
-// HICR_PLAN_GRAPH -- as one hipGraphLaunch of those launches captured from a
-// private stream at creation.  The graph holds kernel nodes only; nothing in
+// of the piece table happen once.  A replay queues the copy launches again,
+// and is counted in the slot table (a plan that writes host memory: by a
+// counter kernel), or is -- HICR_PLAN_GRAPH -- one hipGraphLaunch of copy
+// launches and counter kernel captured from a private stream at creation.  The graph holds kernel nodes only; nothing in
 // it needs clearing between replays.  (Measured on gfx950 with ROCm 7: a
 // graph of two or five kernel nodes launches slower than the same kernels
 // queued directly, so direct replay is the default.)
