@@ -126,7 +126,8 @@ struct PumpArgs {
   uint64_t *ts_push;   // nullable: wall clock (100 MHz) when each message was published
   uint64_t *ts_pop;    // nullable: wall clock when each message was consumed
   uint32_t *err;       // err[0] error bits, err[1] abort request, err[4..5] address of
-                       // the host's abort word (pinned; nonzero asks the pump to stop)
+                       // the host's abort word (pinned; nonzero asks the pump to stop),
+                       // beside which the errors are told (kHostErrors)
   uint64_t timeout_ticks;
 };
 
@@ -146,6 +147,7 @@ struct PushArgs {
 };
 
 enum : uint32_t { kErrTimeout = 1, kErrAbort = 2, kErrCorrupt = 4 };
+constexpr uint32_t kHostErrors = 8;  // the host's word of error e: its abort word [8 + e]
 
 hipError_t launch_pump(const PumpArgs &a, bool split, uint32_t n_wgs, hipStream_t stream);
 hipError_t launch_push(const PushArgs &a, hipStream_t stream);

@@ -708,8 +708,8 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   std::memset(h, 0, 256);
   std::memset(h + o_word, 0, o_off - o_word);
   // the host's abort request: a word of the pinned staging's zeroed head,
-  // which nothing else writes while the pump runs; its address goes up with
-  // the error words (err[4..5])
+  // which nothing else writes while the pump runs (the pump's errors come
+  // into words beside it); its address goes up with the error words (err[4..5])
   const uint64_t abort_addr = reinterpret_cast<uint64_t>(h + kAbortHostOff);
   std::memcpy(h + o_err + 16, &abort_addr, 8);
   std::memcpy(h + o_ring, rings.data(), rings.size() * sizeof(DevRing));
@@ -758,8 +758,6 @@ int pump_launch(hicr_ctx c, const std::vector<PumpStream> &st, const uint64_t *m
   if (e == hipSuccess) e = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, s);
   if (e == hipSuccess && team_zero_bytes) e = hipMemsetAsync(d + o_team, 0, team_zero_bytes, s);
   if (e == hipSuccess) e = launch_pump(a, plan.split > 1, n_wgs, s);
-  // error words come back into the (no longer needed) head of the staging
-  if (e == hipSuccess) e = hipMemcpyAsync(h, d, 8, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&x.ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(x.ev, s);
   if (e != hipSuccess) {
@@ -801,11 +799,12 @@ int pump_finish(hicr_ctx c, Extra &x) {
       c->pump_live.erase(c->pump_live.begin() + i);
       break;
     }
-  const uint32_t *err = static_cast<const uint32_t *>(x.h_buf);
-  if (err[0] & kErrCorrupt) rc = fail(c, HICR_EDEVICE, "a channel pump read a malformed entry");
-  else if (err[0] & kErrTimeout) rc = fail(c, HICR_ETIMEDOUT, "a channel pump made no progress");
-  else if (err[1]) rc = fail(c, HICR_EDEVICE, "a channel pump was aborted");
-  if (err[0] || err[1])
+  const volatile uint32_t *err = x.abort_word + kHostErrors;
+  const bool corrupt = err[kErrCorrupt], timeout = err[kErrTimeout], aborted = err[kErrAbort];
+  if (corrupt) rc = fail(c, HICR_EDEVICE, "a channel pump read a malformed entry");
+  else if (timeout) rc = fail(c, HICR_ETIMEDOUT, "a channel pump made no progress");
+  else if (aborted) rc = fail(c, HICR_EDEVICE, "a channel pump was aborted");
+  if (corrupt || timeout || aborted)
     for (hicr_channel ch : x.chans) ch->broken = true;
   {
     std::lock_guard<std::mutex> g(c->abort_mu);

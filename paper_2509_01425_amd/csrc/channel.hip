@@ -68,6 +68,20 @@ __device__ __forceinline__ void st_rlx(uint64_t a, uint64_t v) {
 // waves in the same one, cost 3 % of the pump's rate; one of 1,024, 0.3-1 %.)
 constexpr uint64_t kWatchTicks = 1000;
 
+// An error goes into the device's word, which every waiting wave looks at,
+// and into one of the host's own words beside its abort word (one per kind:
+// nothing has to be read back behind the pump: one of five streams 34 -> 32 us).
+__device__ __forceinline__ void tell_host(uint32_t *err, uint32_t bit) {
+  uint32_t *host = reinterpret_cast<uint32_t *>(__hip_atomic_load(
+      reinterpret_cast<uint64_t *>(err + 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  if (host)
+    __hip_atomic_store(host + kHostErrors + bit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void raise_error(uint32_t *err, uint32_t bit) {
+  __hip_atomic_fetch_or(&err[0], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  tell_host(err, bit);
+}
+
 struct Watch {
   uint64_t deadline, span;
   uint32_t *err;
@@ -83,8 +97,10 @@ struct Watch {
       const uint32_t *host = reinterpret_cast<const uint32_t *>(__hip_atomic_load(
           reinterpret_cast<uint64_t *>(err + 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       if (host && __hip_atomic_load(host, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) {
-        if (__lane_id() == 0)
+        if (__lane_id() == 0) {
           __hip_atomic_store(&err[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          tell_host(err, kErrAbort);
+        }
         return true;
       }
     }
@@ -92,7 +108,7 @@ struct Watch {
         __hip_atomic_load(&err[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       return true;
     if (now > deadline) {
-      __hip_atomic_fetch_or(&err[0], kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      raise_error(err, kErrTimeout);
       return true;
     }
     return false;
@@ -301,7 +317,7 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
     if (m >= st.n_msgs) return;
     if (__ballot(bad)) {
       if (wave == 0 && lane == 0)
-        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_error(a.err, kErrCorrupt);
       return;
     }
     uint64_t my_tm = tm, my_tb = tb, hm = 0, hb = 0, ticket = 0;
@@ -383,7 +399,7 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
           st_rlx(rec + 8, st.out_base + out_run + incl - sz);
           st_rlx(rec + 16, st.first_msg + m + lane);
         } else {
-          __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          raise_error(a.err, kErrCorrupt);
         }
       }
     }
@@ -474,8 +490,7 @@ __device__ void run_consumer(const PumpArgs &a, uint32_t uid_in, uint32_t wave, 
                                       q_cnt + lane >= so.n_msgs);
         if (__ballot(bad)) {
           if (lane == 0)
-            __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
+            raise_error(a.err, kErrCorrupt);
           stop = true;
         } else if (lane < k) {
           if (a.trace) a.trace[so.trace_base + q_cnt + lane] = sid;
@@ -631,7 +646,7 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave,
     }
     if (__ballot(bad)) {
       if (lane == 0)
-        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_error(a.err, kErrCorrupt);
       return;  // the same in every wave
     }
     Feed<false> f;
@@ -790,7 +805,7 @@ __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint3
       if (uni64(ld_rlx(tm_a)) != r.base_m) {  // not what the host planned for
         stop = true;
         if (lane == 0)
-          __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          raise_error(a.err, kErrCorrupt);
       }
     } else {
       while ((v = uni64(ld_rlx(base_a))) == 0 && !stop) stop = w.expired();
@@ -843,7 +858,7 @@ __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint3
                               g.run + g.incl > st.out_bytes);
     if (g.bad || __ballot(bad)) {  // the same in every wave, before a byte of the group moves
       if (wave == 0 && lane == 0)
-        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_error(a.err, kErrCorrupt);
       return;
     }
     const uint64_t end_m = r.base_m + g.first + g.hi;
@@ -907,7 +922,7 @@ __device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint3
                               g.run + g.incl > st.out_bytes);
     if (g.bad || __ballot(bad)) {  // the same in every wave
       if (lane == 0)
-        __hip_atomic_fetch_or(&a.err[0], kErrCorrupt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_error(a.err, kErrCorrupt);
       return;
     }
     if (b == 0 && wave == 0 && mine) {
