@@ -80,7 +80,9 @@ __host__ __device__ inline uint64_t piece_count(uint64_t dst, uint64_t size, uin
 
 // Launch the fused copy kernel over one sub-batch (n <= kMaxLdsDescs), piece
 // table scanned in LDS by every workgroup.
-hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, Done done, hipStream_t stream);
+hipError_t launch_copy(const DevBatch &b, DevSched s, uint32_t grid, hipStream_t stream);
+// Raise the words of `done` (armed for one workgroup) once everything before it has ended.
+hipError_t launch_done(Done done, hipStream_t stream);
 // Scan the pieces of a batch (1 <= n <= kTile * kMaxTiles, fewer than 2^31
 // pieces) into a tiled table: ends[0, n) holds each tile's inclusive prefix
 // relative to the tile, tile_tot[0, ceil(n / kTile)) the tile totals.  staged:

@@ -338,11 +338,17 @@ int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<
     const uint32_t grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 1), cap_grid);
     // the last launch of the submission tells of its end (the launches of one
     // stream run one after another)
-    Done done;
-    if (sig && !counters && &g == &segs.back()) done = arm(*sig, grid);
-    hipError_t e = g.lds ? launch_copy(seg_batch(dd, n, g), ds, grid, done, stream)
-                         : launch_copy_mem(seg_batch(dd, n, g), ds, tables + g.i0,
-                                           tables + n + g.i0, grid, done, stream);
+    const bool tell = sig && !counters && &g == &segs.back();
+    hipError_t e;
+    if (g.lds) {
+      e = launch_copy(seg_batch(dd, n, g), ds, grid, stream);
+      if (e == hipSuccess && tell) e = launch_done(arm(*sig, 1), stream);
+    } else {
+      Done done;
+      if (tell) done = arm(*sig, grid);
+      e = launch_copy_mem(seg_batch(dd, n, g), ds, tables + g.i0, tables + n + g.i0, grid, done,
+                          stream);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "launching the copy kernel");
   }
   return launch_counts(c, dd, n, counters, stream, sig);
