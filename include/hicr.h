@@ -135,8 +135,8 @@ int hicr_ctx_set_sched(hicr_ctx ctx, const hicr_sched *s);
  * CUs x this, capped by what fits).  0 (the default) picks by schedule: 4 for
  * chunks of 4 KiB or less, 1 for chunks above 16 KiB up to 32 KiB, otherwise
  * 2; at least 4 for a launch of more than 4,096 requests whose chunks are
- * 16 KiB or less or whose average request is under 16 KiB (but 64 KiB of the
- * batch per workgroup); 1 for a batch that is shared evenly (see hicr_sched).
+ * 16 KiB or less or whose average request is under 16 KiB (but 64 KiB or
+ * 48 requests of the batch per workgroup); 1 for a batch that is shared evenly (see hicr_sched).
  * Never changes a byte.
  * wgs_per_cu > 64 -> HICR_EINVAL. */
 int hicr_ctx_set_copy_grid(hicr_ctx ctx, uint32_t wgs_per_cu);

@@ -402,14 +402,16 @@ __global__ __launch_bounds__(kCopyBlock) void stream_kernel(DevBatch b, const St
 // 256 KiB 23.2 -> 20.9; a plan's requests lie in device memory, which is
 // nearer than arguments: a replay of 16 to 4 KiB 9.2 us that way, 9.6 with
 // arguments).  4 KiB of arguments hold no more.  Addresses are held as
-// 32-bit distances from the lowest of the batch, sizes as the bytes up to the
-// end of the request, from which every wave finds its share: what lies
-// between w and w + 1 times `share` bytes, cut at lines of the destinations.
+// 32-bit distances from the lowest of the batch, sizes as what the batch counts
+// for (stream_load) up to the end of the request, from which every wave finds
+// its share: what lies between w and w + 1 times `share`, cut at lines of the
+// destinations.
+constexpr uint32_t kArgShort = 1u << 31;  // in end: the request counts for kStreamExtra more
 template <uint32_t N>
 struct ArgBatch {
   Done done;
   uint64_t dst, src;
-  uint32_t n, waves, share, bytes;
+  uint32_t n, waves, share, load;
   uint32_t end[N], d[N], s[N];  // end: ~0 past the last request
 };
 template <uint32_t N>
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) 
   if (w < a.waves) {
     // every wave reads them all, so that only one trip to memory comes before
     // its first load: lane l holds requests l, l + 64, ...
-    uint32_t e[K], f[K], d[K], s[K];  // f: where it starts
+    uint32_t e[K], f[K], d[K], s[K], z[K];  // f: where it starts, z: its bytes
 #pragma unroll
     for (uint32_t k = 0; k < K; k++) {
       const uint32_t i = lane + 64 * k;
@@ -436,6 +438,13 @@ __global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) 
       s[k] = t[2 * N + i];
     }
     if (lane == 0) f[0] = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < K; k++) {
+      const uint32_t more = e[k] & kArgShort ? (uint32_t)kStreamExtra : 0;
+      e[k] &= ~kArgShort;
+      f[k] &= ~kArgShort;
+      z[k] = e[k] - f[k] - more;
+    }
     // the request where the share starts and ends (n: past the last), and the
     // byte of it
     uint32_t i[2];
@@ -443,7 +452,7 @@ __global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) 
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const uint64_t x = (uint64_t)(w + j) * a.share;
-      uint32_t c = 0, r = 0, from = 0, to = 0, upto = 0;
+      uint32_t c = 0, r = 0, from = 0, to = 0, size = 0;
 #pragma unroll
       for (uint32_t k = 0; k < K; k++) c += (uint32_t)__popcll(__ballot(e[k] <= x));
       r = min(c, a.n - 1);
@@ -451,23 +460,22 @@ __global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) 
       for (uint32_t k = 0; k < K; k++)
         if (r / 64 == k) {
           from = __builtin_amdgcn_readlane(f[k], r % 64);
-          upto = __builtin_amdgcn_readlane(e[k], r % 64);
+          size = __builtin_amdgcn_readlane(z[k], r % 64);
           to = __builtin_amdgcn_readlane(d[k], r % 64);
         }
       const uint64_t dst = a.dst + to, at = x - from;
       off[j] = min(((dst + at + kLineBytes - 1) & ~(uint64_t)(kLineBytes - 1)) - dst,
-                   (uint64_t)(upto - from));
-      if (at == 0 || x >= a.bytes) off[j] = 0;
-      i[j] = x >= a.bytes ? a.n : c;
+                   (uint64_t)size);
+      if (at == 0 || x >= a.load) off[j] = 0;
+      i[j] = x >= a.load ? a.n : c;
     }
-    if (w == 0) i[0] = 0;  // (leading empty requests)
     for (uint32_t k = i[0] / 64; k < K && 64 * k <= i[1]; k++) {
-      uint32_t ek = e[0], fk = f[0], dk = d[0], sk = s[0];
+      uint32_t zk = z[0], dk = d[0], sk = s[0];
 #pragma unroll
       for (uint32_t m = 1; m < K; m++)
-        if (k == m) ek = e[m], fk = f[m], dk = d[m], sk = s[m];
+        if (k == m) zk = z[m], dk = d[m], sk = s[m];
       const uint32_t r = lane + 64 * k;
-      const uint64_t lo = r == i[0] ? off[0] : 0, hi = r == i[1] ? off[1] : ek - fk;
+      const uint64_t lo = r == i[0] ? off[0] : 0, hi = r == i[1] ? off[1] : zk;
       stream_lanes(a.dst + dk + lo, a.src + sk + lo, r >= i[0] && r <= i[1] && r < a.n ? hi - lo : 0,
                    max(i[0], 64 * k) - 64 * k, min(i[1] + 1 - 64 * k, 64u), lane);
     }
@@ -476,7 +484,7 @@ __global__ __launch_bounds__(kCopyBlock) void stream_args_kernel(ArgBatch<N> a) 
 }
 
 template <uint32_t N>
-static void launch_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src, uint64_t bytes,
+static void launch_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src, uint64_t load,
                         uint32_t waves, Done done, hipStream_t stream) {
   ArgBatch<N> a;
   static_assert(sizeof(a) <= 4096, "kernel arguments");
@@ -487,11 +495,13 @@ static void launch_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t sr
   a.src = src;
   a.n = n;
   a.waves = waves;
-  a.share = (uint32_t)((bytes + waves - 1) / waves);
-  a.bytes = (uint32_t)bytes;
+  a.share = (uint32_t)((load + waves - 1) / waves);
+  a.load = (uint32_t)load;
   uint32_t end = 0;
   for (uint32_t i = 0; i < n; i++) {
-    a.end[i] = end += (uint32_t)h[2 * n + i];
+    const uint64_t size = h[2 * n + i];
+    end += (uint32_t)stream_load(size);
+    a.end[i] = end | (size < kStreamShort ? kArgShort : 0);
     a.d[i] = (uint32_t)(h[i] - dst);
     a.s[i] = (uint32_t)(h[n + i] - src);
   }
@@ -500,9 +510,10 @@ static void launch_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t sr
                      a);
 }
 
-bool args_fit(const uint64_t *h, uint64_t n, uint64_t bytes, uint64_t *dst, uint64_t *src) {
-  constexpr uint64_t kSpan = 0xffffffffull;  // (~0 marks the end)
-  if (!n || n > kArgReqs || bytes >= kSpan) return false;
+bool args_fit(const uint64_t *h, uint64_t n, uint64_t load, uint64_t *dst, uint64_t *src) {
+  constexpr uint64_t kSpan = 0xffffffffull;
+  // (shares run to less than load + kMaxStreamWaves, and kArgShort - 1 marks the end)
+  if (!n || n > kArgReqs || load >= kArgShort - 2 * kMaxStreamWaves) return false;
   const auto d = std::minmax_element(h, h + n), s = std::minmax_element(h + n, h + 2 * n);
   *dst = *d.first;
   *src = *s.first;
@@ -510,12 +521,12 @@ bool args_fit(const uint64_t *h, uint64_t n, uint64_t bytes, uint64_t *dst, uint
 }
 
 hipError_t launch_stream_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src,
-                              uint64_t bytes, uint32_t waves, Done done, hipStream_t stream) {
+                              uint64_t load, uint32_t waves, Done done, hipStream_t stream) {
   if (!n || n > kArgReqs || !waves) return hipErrorInvalidValue;
   if (n <= 64)
-    launch_args<64>(h, n, dst, src, bytes, waves, done, stream);
+    launch_args<64>(h, n, dst, src, load, waves, done, stream);
   else
-    launch_args<kArgReqs>(h, n, dst, src, bytes, waves, done, stream);
+    launch_args<kArgReqs>(h, n, dst, src, load, waves, done, stream);
   return hipGetLastError();
 }
 

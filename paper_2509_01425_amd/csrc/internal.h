@@ -95,20 +95,20 @@ hipError_t launch_upload(const void *h_dev, void *d, uint64_t bytes, hipStream_t
 hipError_t launch_copy_mem(const DevBatch &b, DevSched s, const uint32_t *ends,
                            const uint32_t *tile_tot, uint32_t grid, Done done,
                            hipStream_t stream);
-// Copy requests [0, n) as one stream of bytes shared evenly by `waves`
-// wavefronts: wave w moves what lies between starts[w] and starts[w + 1]
+// Copy requests [0, n) as one stream shared evenly by `waves` wavefronts: wave w moves what lies between starts[w] and starts[w + 1]
 // (starts[waves] = {0, n}).  dst, src, size and starts may lie in pinned host
 // memory.
 inline uint32_t stream_grid(uint32_t waves) { return (waves + kCopyBlock / 64 - 1) / (kCopyBlock / 64); }
 hipError_t launch_stream(const DevBatch &b, const StreamStart *starts, uint32_t waves, Done done,
                          hipStream_t stream);
 // The same for up to kArgReqs requests, which go into the kernel's arguments.
-// h holds n destinations, sources and sizes, `bytes` in all; args_fit says
-// whether they can go that way, and the lowest of both addresses.
+// h holds n destinations, sources and sizes, which count for `load` in all
+// (stream_load); args_fit says whether they can go that way, and the lowest of
+// both addresses.
 constexpr uint32_t kArgReqs = 256;
-bool args_fit(const uint64_t *h, uint64_t n, uint64_t bytes, uint64_t *dst, uint64_t *src);
+bool args_fit(const uint64_t *h, uint64_t n, uint64_t load, uint64_t *dst, uint64_t *src);
 hipError_t launch_stream_args(const uint64_t *h, uint32_t n, uint64_t dst, uint64_t src,
-                              uint64_t bytes, uint32_t waves, Done done, hipStream_t stream);
+                              uint64_t load, uint32_t waves, Done done, hipStream_t stream);
 // Raise the slot counters of n requests (slots[i] = dst | src << 32); queued
 // after the copy launches of the same requests on the same stream.
 inline uint32_t count_grid(uint64_t n) { return (uint32_t)((n + 1023) / 1024); }

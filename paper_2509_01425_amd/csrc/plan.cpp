@@ -205,11 +205,12 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
     if (p->host_count) {
       p->n_sent.assign(p->slots.size(), 0);
       p->n_recv.assign(p->slots.size(), 0);
-      uint64_t bytes = 0;
+      uint64_t bytes = 0, n_short = 0;
       for (uint64_t i = 0; i < n; i++) {
         c->slots[d[i].src_slot].tmp_sent++;
         c->slots[d[i].dst_slot].tmp_recv++;
         bytes += d[i].size;
+        n_short += d[i].size < kStreamShort;
       }
       for (size_t k = 0; k < p->slots.size(); k++) {
         Slot &x = c->slots[p->slots[k]];
@@ -217,13 +218,13 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
         p->n_recv[k] = x.tmp_recv;
         x.tmp_sent = x.tmp_recv = 0;
       }
-      p->waves = stream_waves(n, bytes, c->n_cu, c->grid_per_cu);
+      p->waves = stream_waves(n, bytes, c->n_cu, c->grid_per_cu, n_short);
       if (p->waves) {
         static_assert(sizeof(StreamStart) == 16, "two words");
         up.resize(up.size() + 2 * (p->waves + 1));
         h = up.data() + kHeadWords;
         stream_starts(h, h + 2 * n, n, bytes, p->waves, kLineBytes,
-                      reinterpret_cast<StreamStart *>(h + 4 * n));
+                      reinterpret_cast<StreamStart *>(h + 4 * n), n_short);
       }
       if (e == hipSuccess) e = take_words(c, &p->sig.words);
     }

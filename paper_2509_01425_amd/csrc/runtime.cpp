@@ -315,6 +315,8 @@ static int launch_counts(hicr_ctx c, const uint64_t *dd, uint64_t n, uint64_t *c
   return e == hipSuccess ? HICR_OK : hip_fail(c, e, "launching the counter kernel");
 }
 
+constexpr uint64_t kTableReqs = 12;  // of a scanned table, to a wave
+
 int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
                   DevSched ds, const uint32_t *tables, uint64_t *counters, hipStream_t stream,
                   Signal *sig) {
@@ -330,9 +332,12 @@ int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<
       per_cu = std::max(per_cu, 4);
     if (g.lds) per_cu = std::min(per_cu, c->occ);
     uint64_t cap_grid = (uint64_t)c->n_cu * (uint64_t)per_cu;
-    // ... of at least 16 KiB a wavefront (7,744 rows of 2,816 B: 19 us a replay
-    // that way, 24 us with four groups per CU)
-    if (c->grid_per_cu == 0 && !g.lds) cap_grid = std::min(cap_grid, std::max<uint64_t>(1, g.bytes >> 16));
+    // ... of at least 16 KiB or kTableReqs requests a wavefront (7,744 rows of
+    // 2,816 B: 19 us a replay that way, 24 us with four groups per CU; 5,000 of
+    // 16 B 415 us by bytes alone, now 15; 20,000 of 1 KiB 25 us with 6 requests,
+    // 24 with 8, 22 with 12)
+    if (c->grid_per_cu == 0 && !g.lds)
+      cap_grid = std::min(cap_grid, std::max(g.bytes >> 16, (g.i1 - g.i0) / (4 * kTableReqs) + 1));
     // every wavefront of a workgroup copies its own pieces
     const uint64_t want = (g.pieces + kCopyBlock / 64 - 1) / (kCopyBlock / 64);
     const uint32_t grid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(want, 1), cap_grid);
@@ -441,11 +446,12 @@ constexpr int kPoolThreads = 7;             // beside the calling one
 constexpr uint64_t kUploadStream = 256 << 10;  // upload bytes that go on their own stream
 
 // What pack_range found: the first rejected request (i1 if none) and its
-// code, the bytes of all, and whether one writes host memory.
+// code, the bytes of all, how many are short (stream_load), and whether one
+// writes host memory.
 struct Packed {
   uint64_t bad = 0;
   int rc = HICR_OK;
-  uint64_t bytes = 0;
+  uint64_t bytes = 0, n_short = 0;
   bool host_dst = false;
 };
 
@@ -457,10 +463,13 @@ static Packed pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0
   const Slot *sl = c->slots.data();
   Packed p;
   p.bad = i1;
+  uint64_t bytes = 0, n_short = 0;  // (not in p: they would be stored for every request)
+  uint32_t spaces = 0;
   for (uint64_t i = i0; i < i1; i++) {
     const hicr_desc &x = d[i];
-    p.rc = check_desc(c, x);
-    if (p.rc != HICR_OK) {
+    const int rc = check_desc(c, x);
+    if (rc != HICR_OK) {
+      p.rc = rc;
       p.bad = i;
       return p;
     }
@@ -468,9 +477,14 @@ static Packed pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0
     hs[i] = sl[x.src_slot].base + x.src_off;
     hz[i] = x.size;
     hp[i] = (uint64_t)x.dst_slot | ((uint64_t)x.src_slot << 32);
-    p.bytes += x.size;
-    p.host_dst |= sl[x.dst_slot].space != HICR_MEM_HBM;
+    bytes += x.size;
+    n_short += x.size < kStreamShort;
+    spaces |= sl[x.dst_slot].space;
   }
+  static_assert(HICR_MEM_HBM == 0, "any other space of a destination shows");
+  p.bytes = bytes;
+  p.n_short = n_short;
+  p.host_dst = spaces != HICR_MEM_HBM;
   return p;
 }
 
@@ -543,19 +557,21 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   const bool host_count = !no_count && !k.host_dst && n <= kMaxLdsDescs;
   uint64_t *counters = no_count || host_count ? nullptr : c->d_counters;
   Signal *sig = k.host_dst || opt ? nullptr : &s.sig;
-  const uint32_t waves = host_count && !opt ? stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu) : 0;
+  const uint32_t waves =
+      host_count && !opt ? stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short) : 0;
   s.sig.n_words = 0;
   s.host_counted = 0;
   hipError_t e = hipSuccess;
   if (waves) {
     const Done done = arm(*sig, stream_grid(waves));
+    const uint64_t load = k.bytes + k.n_short * kStreamExtra;
     uint64_t dst, src;
-    if (args_fit(h, n, k.bytes, &dst, &src)) {
-      e = launch_stream_args(h, (uint32_t)n, dst, src, k.bytes, waves, done, stream);
+    if (args_fit(h, n, load, &dst, &src)) {
+      e = launch_stream_args(h, (uint32_t)n, dst, src, load, waves, done, stream);
     } else {
       // small enough that the kernel reads the requests where they are
       StreamStart *starts = reinterpret_cast<StreamStart *>(h + 4 * n);
-      stream_starts(h, h + 2 * n, n, k.bytes, waves, kLineBytes, starts);
+      stream_starts(h, h + 2 * n, n, k.bytes, waves, kLineBytes, starts, k.n_short);
       const DevBatch b{hv, hv + n, hv + 2 * n, hv + 3 * n, (uint32_t)n};
       e = launch_stream(b, reinterpret_cast<const StreamStart *>(hv + 4 * n), waves, done, stream);
     }
