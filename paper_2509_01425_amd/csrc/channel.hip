@@ -113,6 +113,17 @@ struct Watch {
     }
     return false;
   }
+  // The same for a wait that outlasts many steps of others (an end of a split
+  // ring: its next share may lie far down the stream): a change of what it
+  // polls is progress, and so is its first look.
+  uint64_t seen;
+  __device__ void poll() { seen = ~0ull; }
+  __device__ bool stuck(uint64_t v) {
+    if (v == seen) return expired();
+    seen = v;
+    progress();
+    return false;
+  }
 };
 
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
@@ -272,7 +283,7 @@ __device__ void run_producer(const PumpArgs &a, uint32_t sid_in, uint32_t wave, 
   // rings are empty when a pump starts: the producer side resumes at the
   // consumer's released counters
   uint64_t tm = uni64(ld_rlx(tm_a)), tb = uni64(ld_rlx(hb_a));
-  Watch w{0, a.timeout_ticks, a.err, 0};
+  Watch w{0, a.timeout_ticks, a.err, 0, 0};
   w.progress();
   uint64_t m = 0;
   uint64_t out_run = 0;  // output bytes of this stream's earlier messages
@@ -442,7 +453,7 @@ __device__ void run_consumer(const PumpArgs &a, uint32_t uid_in, uint32_t wave, 
     hb = ld_rlx(coord + offsetof(RingCoord, cons) + 8);
     pos = hb % rg.P;
   }
-  Watch w{0, a.timeout_ticks, a.err, 0};
+  Watch w{0, a.timeout_ticks, a.err, 0, 0};
   w.progress();
   uint64_t done = 0;
   uint32_t rr = 0;
@@ -565,7 +576,7 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave,
   const uint64_t last = r.base_m + u.total_msgs;  // counter after this pump's messages
   uint64_t *rounds = (uint64_t *)u.rounds;
   __builtin_amdgcn_s_setprio(3);
-  Watch w{0, a.timeout_ticks, a.err, 0};
+  Watch w{0, a.timeout_ticks, a.err, 0, 0};
   w.progress();
   for (;;) {
     if (wave == 0) {
@@ -775,10 +786,12 @@ __device__ __forceinline__ bool split_gather(uint64_t words, uint64_t bytes, uin
                                              uint64_t no, uint32_t lane, Watch &w) {
   const uint64_t part = split_part(bytes, B);
   const bool on = lane > 0 && lane < B && lane * part < bytes;
-  while (__ballot(on && ld_rlx(words + 8 * lane) < no + 1)) {
-    if (w.expired()) return false;
+  w.poll();
+  for (;;) {
+    const uint64_t left = __ballot(on && ld_rlx(words + 8 * lane) < no + 1);
+    if (!left) return true;
+    if (w.stuck(left)) return false;
   }
-  return true;
 }
 
 __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint32_t wave,
@@ -791,7 +804,7 @@ __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint3
   const uint64_t tm_a = r.coord + offsetof(RingCoord, prod),
                  hm_a = r.coord + offsetof(RingCoord, cons), hb_a = hm_a + 8;
   if (st.n_msgs == 0) return;
-  Watch w{0, a.timeout_ticks, a.err, 0};
+  Watch w{0, a.timeout_ticks, a.err, 0, 0};
   w.progress();
   Groups g(a, st, r, A, lane);
   // the ring's byte counter when the pump starts: nothing is published before
@@ -836,7 +849,8 @@ __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint3
         if (lane == 0) st_rlx(words + 8 * b, no - A + 1);
       } else {
         stop = !split_gather(words, last_bytes, B, no - A, lane, w);
-        while (!stop && uni64(ld_rlx(tm_a)) != pub_m - last_j) stop = w.expired();
+        w.poll();
+        for (uint64_t tm; !stop && (tm = uni64(ld_rlx(tm_a))) != pub_m - last_j;) stop = w.stuck(tm);
         order();
         if (!stop) {
           if (a.ts_push && lane < last_j)
@@ -864,11 +878,12 @@ __device__ void run_split_producer(const PumpArgs &a, const DevRole &role, uint3
     const uint64_t end_m = r.base_m + g.first + g.hi;
     const uint64_t end_b = base_b + g.run + lane64(g.incl, g.hi - 1);
     if (wave == 0) {
+      w.poll();
       while (!stop) {
         const uint64_t hm = uni64(ld_rlx(hm_a)), hb = uni64(ld_rlx(hb_a));
         if (end_m - hm <= r.E && end_b - hb <= r.P) break;
         __builtin_amdgcn_s_sleep(1);
-        stop = w.expired();
+        stop = w.stuck(hm + hb);  // (both only grow)
       }
       order();
       if (lane == 0) cast->stop = stop;
@@ -895,7 +910,7 @@ __device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint3
   const uint64_t tm_a = r.coord + offsetof(RingCoord, prod),
                  hm_a = r.coord + offsetof(RingCoord, cons);
   if (st.n_msgs == 0) return;
-  Watch w{0, a.timeout_ticks, a.err, 0};
+  Watch w{0, a.timeout_ticks, a.err, 0, 0};
   w.progress();
   Groups g(a, st, r, A, lane);
   uint64_t no = team;
@@ -905,9 +920,10 @@ __device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint3
     if (b && b * split_part(bytes, B) >= bytes) continue;
     if (wave == 0) {
       bool stop = false;
-      while (!stop && (int64_t)(uni64(ld_rlx(tm_a)) - end_m) < 0) {
+      w.poll();
+      for (uint64_t tm; !stop && (int64_t)((tm = uni64(ld_rlx(tm_a))) - end_m) < 0;) {
         __builtin_amdgcn_s_sleep(1);
-        stop = w.expired();
+        stop = w.stuck(tm);
       }
       order();
       if (lane == 0) cast->stop = stop;
@@ -938,7 +954,8 @@ __device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint3
       } else {
         const uint64_t start = end_m - (g.hi - g.lo);
         stop = !split_gather(words, bytes, B, no, lane, w);
-        while (!stop && uni64(ld_rlx(hm_a)) != start) stop = w.expired();
+        w.poll();
+        for (uint64_t hm; !stop && (hm = uni64(ld_rlx(hm_a))) != start;) stop = w.stuck(hm);
         order();
         if (!stop)
           st_pair(hm_a, end_m, base_b + g.run + lane64(g.incl, g.hi - 1), lane == 0);
