@@ -231,7 +231,10 @@ typedef struct hicr_plan_s *hicr_plan;
 /* flags other than HICR_PLAN_GRAPH -> HICR_EINVAL. */
 int hicr_plan_create(hicr_ctx ctx, const hicr_desc *d, uint64_t n, const hicr_sched *s_or_null,
                      uint32_t flags, hicr_plan *out, uint64_t *bad_index_or_null);
-/* Replay once on `stream` (NULL: the context stream).  Asynchronous. */
+/* Replay once on `stream` (NULL: the context stream).  Asynchronous.  On a stream
+ * that the caller is capturing the replay joins the caller's graph instead: every
+ * launch of that graph moves and counts the requests once more, and fences do
+ * not wait for it. */
 int hicr_plan_launch(hicr_plan plan, void *stream);
 /* Wait for the plan's last replay, then free it and release its slots. */
 int hicr_plan_destroy(hicr_plan plan);

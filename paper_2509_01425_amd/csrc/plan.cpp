@@ -291,21 +291,24 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
       if (e == hipSuccess) e = hipStreamWaitEvent(s, p->sig.ev, 0);
     }
     const uint64_t *dd = p->batch();
+    // A captured launch is part of a graph of the caller's: it is counted on the
+    // device, as often as that runs, and is no replay that a fence waits for.
+    const bool cap = p->host_count && capturing(c, s), host_count = p->host_count && !cap;
+    uint64_t *counters = host_count ? nullptr : c->d_counters;
+    if (p->n && !host_count) c->dev_counted = true;
     if (e == hipSuccess && p->exec) {
       e = hipGraphLaunch(p->exec, s);
-      c->dev_counted = true;
     } else if (e == hipSuccess && p->waves) {
       const DevBatch b{dd, dd + p->n, dd + 2 * p->n, dd + 3 * p->n, (uint32_t)p->n};
       e = launch_stream(b, reinterpret_cast<const StreamStart *>(dd + 4 * p->n), p->waves,
-                        arm(p->sig, stream_grid(p->waves)), s);
+                        cap ? Done{} : arm(p->sig, stream_grid(p->waves)), s);
+      if (e == hipSuccess && cap) return launch_counts(c, dd, p->n, counters, s, nullptr);
     } else if (e == hipSuccess && p->n) {
       // replays are ordered (same stream, or the wait above), so the words'
       // last value is the last replay's
-      if (!p->host_count) c->dev_counted = true;
-      int rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->batch(), p->n),
-                             p->host_count ? nullptr : c->d_counters, s,
-                             p->host_count ? &p->sig : nullptr);
-      if (rc != HICR_OK) return rc;
+      int rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->batch(), p->n), counters,
+                             s, host_count ? &p->sig : nullptr);
+      if (rc != HICR_OK || cap) return rc;
     }
     if (e == hipSuccess) e = mark(c, p->sig, s);
     if (e != hipSuccess) return hip_fail(c, e, "launching a plan");

@@ -148,6 +148,14 @@ hipError_t wait_signal(hicr_ctx c, Signal &sig) {
   return e == hipSuccess ? sync_event(sig.ev) : e;
 }
 
+bool capturing(hicr_ctx c, hipStream_t s) {
+  if (c->own_stream && s == c->stream) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 bool writes_device_only(hicr_ctx c, const hicr_desc *d, uint64_t n) {
   for (uint64_t i = 0; i < n; i++)
     if (c->slots[d[i].dst_slot].space != HICR_MEM_HBM) return false;
@@ -306,7 +314,7 @@ int launch_scans(hicr_ctx c, const uint64_t *staged, const uint64_t *dd, uint64_
   return HICR_OK;
 }
 
-static int launch_counts(hicr_ctx c, const uint64_t *dd, uint64_t n, uint64_t *counters,
+int launch_counts(hicr_ctx c, const uint64_t *dd, uint64_t n, uint64_t *counters,
                          hipStream_t stream, Signal *sig) {
   if (!counters || !n) return HICR_OK;
   Done done;
@@ -552,18 +560,19 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   // copy launch raises the submission's words; a larger one is counted on the
   // device by a kernel that raises them (a host core takes ~2 ns a request);
   // bytes in host memory are only visible after the runtime's completion
-  // signal, so there the event tells.
-  const bool no_count = opt && opt->no_count;
-  const bool host_count = !no_count && !k.host_dst && n <= kMaxLdsDescs;
+  // signal, so there the event tells.  Work that a caller captures runs as
+  // often as its graph is launched: it is counted on the device.
+  const bool no_count = opt && opt->no_count, cap = capturing(c, stream);
+  const bool host_count = !no_count && !k.host_dst && !cap && n <= kMaxLdsDescs;
   uint64_t *counters = no_count || host_count ? nullptr : c->d_counters;
-  Signal *sig = k.host_dst || opt ? nullptr : &s.sig;
+  Signal *sig = k.host_dst || opt || cap ? nullptr : &s.sig;
   const uint32_t waves =
-      host_count && !opt ? stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short) : 0;
+      k.host_dst || opt ? 0 : stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short);
   s.sig.n_words = 0;
   s.host_counted = 0;
   hipError_t e = hipSuccess;
   if (waves) {
-    const Done done = arm(*sig, stream_grid(waves));
+    const Done done = sig ? arm(*sig, stream_grid(waves)) : Done{};
     const uint64_t load = k.bytes + k.n_short * kStreamExtra;
     uint64_t dst, src;
     if (args_fit(h, n, load, &dst, &src)) {
@@ -575,7 +584,8 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
       const DevBatch b{hv, hv + n, hv + 2 * n, hv + 3 * n, (uint32_t)n};
       e = launch_stream(b, reinterpret_cast<const StreamStart *>(hv + 4 * n), waves, done, stream);
     }
-    if (e != hipSuccess) rc = hip_fail(c, e, "launching the stream kernel");
+    rc = e == hipSuccess ? launch_counts(c, hv, n, counters, stream, nullptr)
+                         : hip_fail(c, e, "launching the stream kernel");
   } else {
     const DevSched ds{sched.chunk_bytes, sched.wgs_per_desc, sched.unroll, 0};
     rc = ensure_device(c, s, n);
@@ -589,7 +599,7 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
     // front of the copy reads the staging (the scan kernel, when there is a
     // table to scan): a copy engine first waits for the signal of the kernel
     // before it, and the copy kernel then for the engine's.
-    const bool behind = n * 32 >= kUploadStream && any_inflight(c);
+    const bool behind = !cap && n * 32 >= kUploadStream && any_inflight(c);
     if (behind) {
       e = hipMemcpyAsync(s.d, s.h, n * 32, hipMemcpyHostToDevice, c->up);
       if (e == hipSuccess) e = hipEventRecord(s.up_ev, c->up);

@@ -197,6 +197,8 @@ bool ended(hicr_ctx c, Signal &sig);
 hipError_t wait_signal(hicr_ctx c, Signal &sig);
 // The event behind the marked launch, recorded now if it is not yet.
 hipError_t ensure_event(hicr_ctx c, Signal &sig);
+// Whether a caller is capturing stream s into a graph.
+bool capturing(hicr_ctx c, hipStream_t s);
 // Whether every request of a batch writes device memory (HBM slots): only
 // then may done words stand for the end of the batch, since the runtime's
 // completion signal is what makes bytes written to host memory visible.
@@ -223,6 +225,9 @@ int launch_scans(hicr_ctx c, const uint64_t *staged, const uint64_t *dd, uint64_
 int launch_copies(hicr_ctx c, const uint64_t *dd, uint64_t n, const std::vector<Seg> &segs,
                   DevSched ds, const uint32_t *tables, uint64_t *counters, hipStream_t stream,
                   Signal *sig = nullptr);
+// Queue the counter kernel over the slot pairs of a batch dd (counters null: none).
+int launch_counts(hicr_ctx c, const uint64_t *dd, uint64_t n, uint64_t *counters,
+                  hipStream_t stream, Signal *sig);
 // Bytes of device memory an uploaded batch of n requests takes: the packed
 // requests (32 B each), then the piece tables: per-request prefixes (4 B
 // each) and tile totals (a launch over requests [i0, i1) keeps its tiles at
