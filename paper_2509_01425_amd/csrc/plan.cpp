@@ -17,6 +17,7 @@
 #include <mutex>
 #include <vector>
 
+#include "replays.h"
 #include "runtime.h"
 
 using namespace hicr;
@@ -43,6 +44,7 @@ struct hicr_plan_s {
   // launch raises sig's words, and a replay is counted in the slots here
   // (sent and received per entry of `slots`)
   bool host_count = false;
+  Replays replays;
   std::vector<uint64_t> n_sent, n_recv;
 };
 
@@ -127,11 +129,7 @@ bool plans_inflight(hicr_ctx c) {
 void plans_unfinished(hicr_ctx c, uint32_t slot, uint64_t *sent, uint64_t *recv) {
   for (hicr_plan p : c->plans) {
     if (!p->host_count || !p->launched || ended(c, p->sig)) continue;
-    // replays run one after another and each raises the same words to its
-    // number, so the lowest word is the number of replays that have ended
-    uint64_t done = ~0ull;
-    for (uint32_t i = 0; i < p->sig.n_words; i++)
-      done = std::min(done, __atomic_load_n(&p->sig.words[i], __ATOMIC_ACQUIRE));
+    const uint64_t done = p->replays.ended(p->sig.words);
     const size_t k = std::lower_bound(p->slots.begin(), p->slots.end(), slot) - p->slots.begin();
     if (k == p->slots.size() || p->slots[k] != slot) continue;
     *sent -= (p->sig.seq - done) * p->n_sent[k];
@@ -290,27 +288,37 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
       e = ensure_event(c, p->sig);
       if (e == hipSuccess) e = hipStreamWaitEvent(s, p->sig.ev, 0);
     }
+    if (e != hipSuccess) return hip_fail(c, e, "launching a plan");
     const uint64_t *dd = p->batch();
     // A captured launch is part of a graph of the caller's: it is counted on the
     // device, as often as that runs, and is no replay that a fence waits for.
     const bool cap = p->host_count && capturing(c, s), host_count = p->host_count && !cap;
     uint64_t *counters = host_count ? nullptr : c->d_counters;
     if (p->n && !host_count) c->dev_counted = true;
-    if (e == hipSuccess && p->exec) {
+    const uint64_t seq = p->sig.seq;
+    const uint32_t n_words = p->sig.n_words;
+    int rc = HICR_OK;
+    if (p->exec) {
       e = hipGraphLaunch(p->exec, s);
-    } else if (e == hipSuccess && p->waves) {
+    } else if (p->waves) {
       const DevBatch b{dd, dd + p->n, dd + 2 * p->n, dd + 3 * p->n, (uint32_t)p->n};
       e = launch_stream(b, reinterpret_cast<const StreamStart *>(dd + 4 * p->n), p->waves,
                         cap ? Done{} : arm(p->sig, stream_grid(p->waves)), s);
-      if (e == hipSuccess && cap) return launch_counts(c, dd, p->n, counters, s, nullptr);
-    } else if (e == hipSuccess && p->n) {
+      if (e == hipSuccess && cap) rc = launch_counts(c, dd, p->n, counters, s, nullptr);
+    } else if (p->n) {
       // replays are ordered (same stream, or the wait above), so the words'
       // last value is the last replay's
-      int rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->batch(), p->n), counters,
-                             s, host_count ? &p->sig : nullptr);
-      if (rc != HICR_OK || cap) return rc;
+      rc = launch_copies(c, dd, p->n, p->segs, p->ds, batch_tables(p->batch(), p->n), counters, s,
+                         host_count ? &p->sig : nullptr);
     }
-    if (e == hipSuccess) e = mark(c, p->sig, s);
+    if (e != hipSuccess) rc = hip_fail(c, e, "launching a plan");
+    if (rc != HICR_OK || cap) {  // no replay: the words stay with the one before
+      p->sig.seq = seq;
+      p->sig.n_words = n_words;
+      return rc;
+    }
+    if (host_count) p->replays.queued(p->sig.seq, p->sig.n_words, !p->launched);
+    e = mark(c, p->sig, s);
     if (e != hipSuccess) return hip_fail(c, e, "launching a plan");
     for (size_t k = 0; k < p->n_sent.size(); k++) {
       c->slots[p->slots[k]].sent += p->n_sent[k];
