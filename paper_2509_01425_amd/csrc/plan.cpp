@@ -14,7 +14,10 @@
 
 #include <algorithm>
 #include <cstring>
+#include <map>
 #include <mutex>
+#include <tuple>
+#include <utility>
 #include <vector>
 
 #include "replays.h"
@@ -33,6 +36,15 @@ struct hicr_plan_s {
   static constexpr size_t kHead = 128;
   std::vector<Seg> segs;      // copy launches of one replay
   uint32_t waves = 0;         // waves of the stream kernel (0: the piece kernels)
+  const StreamStart *starts = nullptr;  // their shares
+  // A stream plan's shares under each copy grid it has been launched with:
+  // waves and starts.  Kept until the plan goes, as a replay in flight or a graph
+  // of the caller's may read them; h: destinations and sizes, to cut more.
+  int per_cu = 0;             // the copy grid of `waves` and `starts`
+  std::map<int, std::pair<uint32_t, const StreamStart *>> cuts;
+  std::vector<void *> more;   // device buffers of the cuts that came later
+  std::vector<uint64_t> h;
+  uint64_t bytes = 0, n_short = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;  // HICR_PLAN_GRAPH
   DevSched ds{};
@@ -55,6 +67,7 @@ void free_plan(hicr_plan p) {
   if (p->graph) (void)hipGraphDestroy(p->graph);
   if (p->sig.ev) (void)hipEventDestroy(p->sig.ev);
   if (p->d) (void)hipFree(p->d);
+  for (void *d : p->more) (void)hipFree(d);
   if (p->sig.words) p->c->plan_words.push_back(p->sig.words);
   for (hicr_slot s : p->slots) p->c->slots[s].plan_refs--;
   delete p;
@@ -95,6 +108,34 @@ std::vector<hicr_slot> distinct_slots(hicr_ctx c, const hicr_desc *d, uint64_t n
   std::sort(sl.begin(), sl.end());
   sl.erase(std::unique(sl.begin(), sl.end()), sl.end());
   return sl;
+}
+
+// Share a stream plan out anew for the copy grid that is set now.
+hipError_t recut(hicr_ctx c, hicr_plan p) {
+  const int per_cu = c->grid_per_cu;
+  if (!p->cuts.count(per_cu)) {
+    const uint32_t w = stream_waves(p->n, p->bytes, c->n_cu, per_cu, p->n_short);
+    const StreamStart *at = nullptr;
+    for (auto &k : p->cuts)
+      if (k.second.first == w) at = k.second.second;
+    if (!at) {
+      std::vector<StreamStart> s(w + 1);
+      stream_starts(p->h.data(), p->h.data() + p->n, p->n, p->bytes, w, kLineBytes, s.data(),
+                    p->n_short);
+      void *d = nullptr;
+      p->more.reserve(p->more.size() + 1);
+      hipError_t e = hipMalloc(&d, s.size() * sizeof s[0]);
+      if (e != hipSuccess) return e;
+      p->more.push_back(d);
+      e = hipMemcpy(d, s.data(), s.size() * sizeof s[0], hipMemcpyHostToDevice);
+      if (e != hipSuccess) return e;
+      at = static_cast<const StreamStart *>(d);
+    }
+    p->cuts[per_cu] = {w, at};
+  }
+  std::tie(p->waves, p->starts) = p->cuts[per_cu];
+  p->per_cu = per_cu;
+  return hipSuccess;
 }
 
 int wait_plan(hicr_ctx c, hicr_plan p) {
@@ -203,12 +244,11 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
     if (p->host_count) {
       p->n_sent.assign(p->slots.size(), 0);
       p->n_recv.assign(p->slots.size(), 0);
-      uint64_t bytes = 0, n_short = 0;
       for (uint64_t i = 0; i < n; i++) {
         c->slots[d[i].src_slot].tmp_sent++;
         c->slots[d[i].dst_slot].tmp_recv++;
-        bytes += d[i].size;
-        n_short += d[i].size < kStreamShort;
+        p->bytes += d[i].size;
+        p->n_short += d[i].size < kStreamShort;
       }
       for (size_t k = 0; k < p->slots.size(); k++) {
         Slot &x = c->slots[p->slots[k]];
@@ -216,13 +256,16 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
         p->n_recv[k] = x.tmp_recv;
         x.tmp_sent = x.tmp_recv = 0;
       }
-      p->waves = stream_waves(n, bytes, c->n_cu, c->grid_per_cu, n_short);
+      p->per_cu = c->grid_per_cu;
+      p->waves = stream_waves(n, p->bytes, c->n_cu, p->per_cu, p->n_short);
       if (p->waves) {
         static_assert(sizeof(StreamStart) == 16, "two words");
         up.resize(up.size() + 2 * (p->waves + 1));
         h = up.data() + kHeadWords;
-        stream_starts(h, h + 2 * n, n, bytes, p->waves, kLineBytes,
-                      reinterpret_cast<StreamStart *>(h + 4 * n), n_short);
+        stream_starts(h, h + 2 * n, n, p->bytes, p->waves, kLineBytes,
+                      reinterpret_cast<StreamStart *>(h + 4 * n), p->n_short);
+        p->h.assign(h, h + n);
+        p->h.insert(p->h.end(), h + 2 * n, h + 3 * n);
       }
       if (e == hipSuccess) e = take_words(c, &p->sig.words);
     }
@@ -230,6 +273,10 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
       e = hipMalloc(&p->d, std::max(hicr_plan_s::kHead + batch_bytes(n), up.size() * 8));
     if (e == hipSuccess && n) e = hipMemcpy(p->d, up.data(), up.size() * 8, hipMemcpyHostToDevice);
     p->sig.arrive = static_cast<uint32_t *>(p->d);
+    if (p->waves && p->d) {
+      p->starts = reinterpret_cast<const StreamStart *>(p->batch() + 4 * n);
+      p->cuts[p->per_cu] = {p->waves, p->starts};
+    }
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e != hipSuccess) {
       if (cs) (void)hipStreamDestroy(cs);
@@ -295,6 +342,10 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
     const bool cap = p->host_count && capturing(c, s), host_count = p->host_count && !cap;
     uint64_t *counters = host_count ? nullptr : c->d_counters;
     if (p->n && !host_count) c->dev_counted = true;
+    if (p->waves && p->per_cu != c->grid_per_cu && !cap) {
+      e = recut(c, p);
+      if (e != hipSuccess) return hip_fail(c, e, "sharing out a plan");
+    }
     const uint64_t seq = p->sig.seq;
     const uint32_t n_words = p->sig.n_words;
     int rc = HICR_OK;
@@ -302,7 +353,7 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
       e = hipGraphLaunch(p->exec, s);
     } else if (p->waves) {
       const DevBatch b{dd, dd + p->n, dd + 2 * p->n, dd + 3 * p->n, (uint32_t)p->n};
-      e = launch_stream(b, reinterpret_cast<const StreamStart *>(dd + 4 * p->n), p->waves,
+      e = launch_stream(b, p->starts, p->waves,
                         cap ? Done{} : arm(p->sig, stream_grid(p->waves)), s);
       if (e == hipSuccess && cap) rc = launch_counts(c, dd, p->n, counters, s, nullptr);
     } else if (p->n) {
