@@ -598,13 +598,14 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
     // its own, so the upload overlaps their copies.  Otherwise a kernel in
     // front of the copy reads the staging (the scan kernel, when there is a
     // table to scan): a copy engine first waits for the signal of the kernel
-    // before it, and the copy kernel then for the engine's.
+    // before it, and the copy kernel then for the engine's.  A timed submission
+    // is uploaded before the first event in any case.
     const bool behind = !cap && n * 32 >= kUploadStream && any_inflight(c);
     if (behind) {
       e = hipMemcpyAsync(s.d, s.h, n * 32, hipMemcpyHostToDevice, c->up);
       if (e == hipSuccess) e = hipEventRecord(s.up_ev, c->up);
       if (e == hipSuccess) e = hipStreamWaitEvent(stream, s.up_ev, 0);
-    } else if (lds) {
+    } else if (lds || opt) {
       e = launch_upload(s.h_dev, s.d, n * (counters ? 32 : 24), stream);
     }
     if (e != hipSuccess) return hip_fail(c, e, "uploading a batch");
@@ -612,7 +613,7 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
       e = hipEventRecord(opt->t0, stream);
       if (e != hipSuccess) return hip_fail(c, e, "recording a timing event");
     }
-    rc = launch_scans(c, behind || lds ? nullptr : hv, dd, n, c->segs, ds, tables, stream);
+    rc = launch_scans(c, behind || lds || opt ? nullptr : hv, dd, n, c->segs, ds, tables, stream);
     if (rc == HICR_OK) rc = launch_copies(c, dd, n, c->segs, ds, tables, counters, stream, sig);
     if (rc == HICR_OK && opt && opt->t1) {
       e = hipEventRecord(opt->t1, stream);
