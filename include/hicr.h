@@ -92,10 +92,10 @@ typedef struct {
  * when it is large enough; unroll sets the depth of the copy loop: a lane
  * moves rounds of 4 x unroll 16-byte vectors, two rounds in flight.  The
  * schedule never changes a byte of the result.  (It sets how batches from
- * about 256 MiB are copied; a smaller one of at most 4,096 requests into HBM
- * is shared evenly among the wavefronts under every schedule, and launches
- * over a scanned table use chunk_bytes and wgs_per_desc only to share out the
- * batch.)
+ * about 256 MiB are copied, from about 160 MiB with chunk_bytes of at most
+ * 4 KiB; a smaller one of at most 4,096 requests into HBM is shared evenly
+ * among the wavefronts under every schedule, and launches over a scanned table
+ * use chunk_bytes and wgs_per_desc only to share out the batch.)
  * mode: HICR_SCHED_FIXED uses the fields as given; HICR_SCHED_TUNED looks the
  * batch up in the context's autotuned table; HICR_SCHED_LEARNED lets the
  * schedule network pick the class from the batch's size histogram: for a

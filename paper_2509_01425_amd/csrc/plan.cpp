@@ -257,7 +257,8 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
         x.tmp_sent = x.tmp_recv = 0;
       }
       p->per_cu = c->grid_per_cu;
-      p->waves = stream_waves(n, p->bytes, c->n_cu, p->per_cu, p->n_short);
+      if (p->bytes <= stream_most(n, ds.chunk))
+        p->waves = stream_waves(n, p->bytes, c->n_cu, p->per_cu, p->n_short);
       if (p->waves) {
         static_assert(sizeof(StreamStart) == 16, "two words");
         up.resize(up.size() + 2 * (p->waves + 1));

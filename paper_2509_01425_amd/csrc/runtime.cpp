@@ -567,7 +567,9 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   uint64_t *counters = no_count || host_count ? nullptr : c->d_counters;
   Signal *sig = k.host_dst || opt || cap ? nullptr : &s.sig;
   const uint32_t waves =
-      k.host_dst || opt ? 0 : stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short);
+      k.host_dst || opt || k.bytes > stream_most(n, sched.chunk_bytes)
+          ? 0
+          : stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short);
   s.sig.n_words = 0;
   s.host_counted = 0;
   hipError_t e = hipSuccess;

@@ -20,6 +20,17 @@ constexpr uint64_t kStreamShare = 4096;       // fewest bytes worth a wave
 constexpr uint64_t kStreamMaxBytes = 256ull << 20;
 constexpr uint64_t kStreamPerReq = 160 << 10;
 
+// Bytes up to which a batch of n requests is one for the stream kernel under a
+// schedule of `chunk`-byte pieces.  Pieces of 4 KiB keep a batch of a few hundred
+// MiB together best, and so are preferred earlier (stream against pieces of 4
+// and of 64 KiB, us: 16 requests of 160 MiB in all 75 / 74 / 79, of 192 MiB 89 /
+// 85 / 91, of 256 MiB 119 / 111 / 118; 256 requests of 192 MiB 94 / 94 / 104, of
+// 224 MiB 107 / 107 / 111; 1,024 of 256 MiB 127 / 130 / 133).
+constexpr uint32_t kStreamSmallPiece = 4 << 10;
+inline uint64_t stream_most(uint64_t n, uint32_t chunk) {
+  return (chunk <= kStreamSmallPiece ? 160ull << 20 : kStreamMaxBytes) + n * kStreamPerReq;
+}
+
 // A request costs a wave a step of its own however short it is, and a run of
 // short ones must not be left to one wave: so a request below kStreamShort
 // bytes counts for kStreamExtra more wherever a batch is shared out, which
