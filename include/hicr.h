@@ -250,7 +250,10 @@ int hicr_sched_features(const hicr_desc *descs, uint64_t n, float *out32);
 /* Autotuner: run the batch under each of the 12 classes, `reps` timed runs
  * (1..64) after one warm-up, and store the median copy-kernel time of each
  * class in times_ms[12] (and the fastest class, ties to the lowest, in
- * *best_or_null).  The bytes really move (12 * (reps + 1) times in all),
+ * *best_or_null).  Timed are the launches that a class shapes, also for a
+ * batch that a submission would share out evenly instead (see hicr_sched; a
+ * graph plan, a submission without allocation and one into host memory would
+ * not).  The bytes really move (12 * (reps + 1) times in all),
  * so the batch must be hazard-free: its result is then that of one
  * application.  Slot counters are not raised.  Synchronous.  descs NULL, n
  * == 0, reps outside 1..64 or times_ms NULL -> HICR_EINVAL. */
@@ -285,7 +288,8 @@ int hicr_mlp_set_params(hicr_ctx ctx, const float *params); /* also resets Adam 
 int hicr_mlp_get_params(hicr_ctx ctx, float *params_out);
 int hicr_mlp_forward(hicr_ctx ctx, const float *x_dev, uint32_t batch, float *logits_dev);
 /* Class the network chose for the most recent HICR_SCHED_LEARNED submission
- * or plan; HICR_EINVAL before the first. */
+ * or plan, also where the batch is copied the same under every class (see
+ * hicr_sched); HICR_EINVAL before the first. */
 int hicr_last_choice(hicr_ctx ctx, uint32_t *cls);
 /* Gradient of the mean softmax cross-entropy (and the mean loss, if loss_dev). */
 int hicr_mlp_grad(hicr_ctx ctx, const float *x_dev, const int32_t *y_dev, uint32_t batch,

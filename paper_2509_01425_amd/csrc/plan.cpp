@@ -211,7 +211,7 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
     if (sched.mode == HICR_SCHED_TUNED || sched.mode == HICR_SCHED_LEARNED) {
       // resolved once, the network's class by the device forward kernel:
       // every replay uses the class chosen now
-      int rc = choose_sched(c, d, n, sched.mode, &sched, true);
+      int rc = choose_sched(c, d, n, sched.mode, &sched, true, flags & HICR_PLAN_GRAPH);
       if (rc != HICR_OK) return rc;
     } else if (sched.mode != HICR_SCHED_FIXED) {
       return fail(c, HICR_EINVAL, "unknown schedule mode %u", sched.mode);

@@ -162,6 +162,19 @@ bool writes_device_only(hicr_ctx c, const hicr_desc *d, uint64_t n) {
   return true;
 }
 
+bool same_under_every_class(hicr_ctx c, const hicr_desc *d, uint64_t n) {
+  if (n > kStreamMaxReqs) return false;
+  const uint64_t most = stream_most(n, 0);
+  uint64_t bytes = 0;
+  for (uint64_t i = 0; i < n; i++) {
+    if (d[i].dst_slot >= c->slots.size() || c->slots[d[i].dst_slot].space != HICR_MEM_HBM ||
+        d[i].size > most)
+      return false;
+    bytes += d[i].size;
+  }
+  return bytes <= most;
+}
+
 int wait_sub(hicr_ctx c, Sub &s) {
   if (!s.inflight) return HICR_OK;
   hipError_t e = wait_signal(c, s.sig);

@@ -248,9 +248,14 @@ void plans_unfinished(hicr_ctx c, uint32_t slot, uint64_t *sent, uint64_t *recv)
 // (nearest tuned-table entry) or LEARNED (the network: on the host, in the
 // device kernels' arithmetic, per submission; by the device forward kernel
 // when on_device, as for a plan's one-time choice); the context default when
-// neither has data.
+// neither has data, or when no class would change how the batch is copied
+// (unless pieces: the piece kernels take it whatever its size) and the table
+// would be searched for nothing.  The network is asked in any case
+// (hicr_last_choice).
 int choose_sched(hicr_ctx c, const hicr_desc *d, uint64_t n, uint32_t mode, hicr_sched *out,
-                 bool on_device = false);
+                 bool on_device = false, bool pieces = false);
+// Whether a batch (not checked yet) is copied as one stream under every schedule.
+bool same_under_every_class(hicr_ctx c, const hicr_desc *d, uint64_t n);
 void destroy_sched(hicr_ctx c);
 
 // Channel pushes and pumps (channel.cpp).

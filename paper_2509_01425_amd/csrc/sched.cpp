@@ -238,7 +238,7 @@ static int device_class(hicr_ctx c, SchedState *s, const float *f, uint32_t *cls
 }
 
 int choose_sched(hicr_ctx c, const hicr_desc *d, uint64_t n, uint32_t mode, hicr_sched *out,
-                 bool on_device) {
+                 bool on_device, bool pieces) {
   SchedState *s = c->sched;
   if (mode == HICR_SCHED_LEARNED && s && s->net_loaded && on_device) {
     float f[kMlpIn];
@@ -267,7 +267,7 @@ int choose_sched(hicr_ctx c, const hicr_desc *d, uint64_t n, uint32_t mode, hicr
     return hicr_sched_class(k, out);
   }
   // tuned table, the fallback when no network is loaded; default if empty
-  if (s && !s->feats.empty() && n) {
+  if (s && !s->feats.empty() && n && (pieces || !same_under_every_class(c, d, n))) {
     float f[kMlpIn];
     batch_features(&d[0].size, n, sizeof(hicr_desc), f);
     return hicr_sched_class(nearest(s, f), out);
