@@ -14,9 +14,10 @@ scope, which give the same orders):
   their room with two stores (bytes, then entries).  With S > 1 a full
   sub-batch of B messages may wait for up to S - 1 more before one store
   publishes them all (whether it waits is left open: both choices are
-  explored, so every rule the kernel may use to decide is covered), and a
-  producer that finds no room for its next message publishes what it holds
-  first (the consumer cannot free room for messages it has not seen).
+  explored, so every rule a producer may use to decide is covered; the pump's
+  now hold none, S = 1), and a producer that finds no room for its next message
+  publishes what it holds first (the consumer cannot free room for messages it
+  has not seen).
 * ``explore_team`` -- a locking MPSC ring (ticket lock held only to check
   room and reserve entries and bytes) drained by a team of consumers: a
   member claims the next round number, defines the round once the previous
@@ -28,7 +29,8 @@ scope, which give the same orders):
   arrive at any moment: an actor that is waiting may then exit, one with
   work in hand carries on to its next wait; no actor may be left waiting
   forever (the pump's waits all look at its abort word).
-* ``explore_striped`` -- ping-pong between two groups of W members over two
+* ``explore_striped`` -- ping-pong between two groups of W members (up to 16;
+  more of them count through the tree of ``protocol_split``) over two
   one-message rings whose counters count stripes: a message is visible when
   all W stripes have arrived (counter >= W (k + 1)), a ring is free when all
   W stripes of the previous message were read (counter >= W k).
