@@ -44,7 +44,8 @@ struct hicr_plan_s {
   std::map<int, std::pair<uint32_t, const StreamStart *>> cuts;
   std::vector<void *> more;   // device buffers of the cuts that came later
   std::vector<uint64_t> h;
-  uint64_t bytes = 0, n_short = 0;
+  uint64_t bytes = 0, host_bytes = 0, n_short = 0;
+  uint32_t share(int grid) const;  // its waves under a copy grid
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;  // HICR_PLAN_GRAPH
   DevSched ds{};
@@ -59,6 +60,10 @@ struct hicr_plan_s {
   Replays replays;
   std::vector<uint64_t> n_sent, n_recv;
 };
+
+uint32_t hicr_plan_s::share(int grid) const {
+  return stream_waves(n, bytes, c->n_cu, grid, n_short, 2 * host_bytes > bytes);
+}
 
 namespace {
 
@@ -114,7 +119,7 @@ std::vector<hicr_slot> distinct_slots(hicr_ctx c, const hicr_desc *d, uint64_t n
 hipError_t recut(hicr_ctx c, hicr_plan p) {
   const int per_cu = c->grid_per_cu;
   if (!p->cuts.count(per_cu)) {
-    const uint32_t w = stream_waves(p->n, p->bytes, c->n_cu, per_cu, p->n_short);
+    const uint32_t w = p->share(per_cu);
     const StreamStart *at = nullptr;
     for (auto &k : p->cuts)
       if (k.second.first == w) at = k.second.second;
@@ -248,6 +253,7 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
         c->slots[d[i].src_slot].tmp_sent++;
         c->slots[d[i].dst_slot].tmp_recv++;
         p->bytes += d[i].size;
+        if (c->slots[d[i].src_slot].space != HICR_MEM_HBM) p->host_bytes += d[i].size;
         p->n_short += d[i].size < kStreamShort;
       }
       for (size_t k = 0; k < p->slots.size(); k++) {
@@ -258,7 +264,7 @@ int hicr_plan_create(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sche
       }
       p->per_cu = c->grid_per_cu;
       if (p->bytes <= stream_most(n, ds.chunk))
-        p->waves = stream_waves(n, p->bytes, c->n_cu, p->per_cu, p->n_short);
+        p->waves = p->share(p->per_cu);
       if (p->waves) {
         static_assert(sizeof(StreamStart) == 16, "two words");
         up.resize(up.size() + 2 * (p->waves + 1));

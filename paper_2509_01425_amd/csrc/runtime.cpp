@@ -467,12 +467,12 @@ constexpr int kPoolThreads = 7;             // beside the calling one
 constexpr uint64_t kUploadStream = 256 << 10;  // upload bytes that go on their own stream
 
 // What pack_range found: the first rejected request (i1 if none) and its
-// code, the bytes of all, how many are short (stream_load), and whether one
-// writes host memory.
+// code, the bytes of all and of those read from host memory, how many are short
+// (stream_load), and whether one writes host memory.
 struct Packed {
   uint64_t bad = 0;
   int rc = HICR_OK;
-  uint64_t bytes = 0, n_short = 0;
+  uint64_t bytes = 0, host_bytes = 0, n_short = 0;
   bool host_dst = false;
 };
 
@@ -484,8 +484,9 @@ static Packed pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0
   const Slot *sl = c->slots.data();
   Packed p;
   p.bad = i1;
-  uint64_t bytes = 0, n_short = 0;  // (not in p: they would be stored for every request)
-  uint32_t spaces = 0;
+  // (not in p: they would be stored for every request)
+  uint64_t bytes = 0, host_bytes = 0, n_short = 0;
+  uint32_t to = 0;  // spaces
   for (uint64_t i = i0; i < i1; i++) {
     const hicr_desc &x = d[i];
     const int rc = check_desc(c, x);
@@ -500,12 +501,14 @@ static Packed pack_range(hicr_ctx c, const hicr_desc *d, uint64_t n, uint64_t i0
     hp[i] = (uint64_t)x.dst_slot | ((uint64_t)x.src_slot << 32);
     bytes += x.size;
     n_short += x.size < kStreamShort;
-    spaces |= sl[x.dst_slot].space;
+    to |= sl[x.dst_slot].space;
+    host_bytes += x.size & (0 - (uint64_t)(sl[x.src_slot].space != HICR_MEM_HBM));
   }
   static_assert(HICR_MEM_HBM == 0, "any other space of a destination shows");
   p.bytes = bytes;
+  p.host_bytes = host_bytes;
   p.n_short = n_short;
-  p.host_dst = spaces != HICR_MEM_HBM;
+  p.host_dst = to != HICR_MEM_HBM;
   return p;
 }
 
@@ -582,7 +585,7 @@ int submit(hicr_ctx c, const hicr_desc *d, uint64_t n, const hicr_sched &sched,
   const uint32_t waves =
       k.host_dst || opt || k.bytes > stream_most(n, sched.chunk_bytes)
           ? 0
-          : stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short);
+          : stream_waves(n, k.bytes, c->n_cu, c->grid_per_cu, k.n_short, 2 * k.host_bytes > k.bytes);
   s.sig.n_words = 0;
   s.host_counted = 0;
   hipError_t e = hipSuccess;
