@@ -441,12 +441,13 @@ typedef struct {
 #define HICR_PUMP_DEVICE_TABLES 0x1u
 
 /* Run every stream through its device-endpoint channel in one persistent
- * launch on `stream`: one GPU wave per producer stream.  The consumer side
- * of each channel is a team of workgroups: a locking MPSC channel's shared
- * ring is drained in its total order by up to 16 workgroups that take turns
- * (rounds of consecutive messages, ring room released in order); the rings
- * with a single producer (SPSC rings, non-locking MPSC sub-rings) are spread
- * over the remaining workgroups the device holds, balanced by bytes.  Validated on the host (slots, ranges, sizes, one stream per
+ * launch on `stream`.  A producer stream is a GPU wave, or a workgroup, or
+ * several while compute units are unused, and so is the consumer of a ring with
+ * a single producer (SPSC rings, non-locking MPSC sub-rings; with more rings
+ * than waves a wave consumes several, balanced by bytes).  A locking MPSC
+ * channel's shared ring is drained in its total order by a team of up to 16
+ * workgroups that take turns (rounds of consecutive messages, ring room
+ * released in order).  Validated on the host (slots, ranges, sizes, one stream per
  * (channel, producer)); HICR_EINVAL if the launch would not fit on the device
  * at once.  Asynchronous; hicr_fence reports a time-out or abort.  Pumps of
  * one context never overlap unsafely: a pump queued on another stream than

@@ -3,10 +3,10 @@
 // device pump.
 //
 // Host-endpoint channels keep their coordination counters in host-coherent
-// pinned memory: a push enqueues push_kernel, which copies the payload into
-// the HBM ring and then publishes the new message counter with a
-// system-scope release; the host consumer reads that counter, and its pop
-// stores the released counters that the host producer checks for room.
+// pinned memory: a push enqueues push_kernel, which writes the payload through
+// to the HBM ring, waits for those stores and then stores the new message
+// counter (relaxed, system scope); the host consumer reads that counter, and
+// its pop stores the released counters that the host producer checks for room.
 // Device-endpoint channels keep their counters in HBM and are driven by
 // pump_kernel.
 #include <algorithm>
@@ -24,9 +24,10 @@
 using namespace hicr;
 
 // Offset of a pump's abort word in its pinned staging: inside the 256-byte
-// head that every launch zeroes, past the 8 bytes of error words that come
-// back from the device at the end.
+// head that every launch zeroes, past the words that go up to the device.  The
+// words in which the pump tells its errors lie behind it.
 constexpr uint64_t kAbortHostOff = 128;
+static_assert(kAbortHostOff + 4 * (kHostErrors + kErrCorrupt + 1) <= 256, "one head");
 
 struct hicr_channel_s {
   hicr_ctx ctx = nullptr;

@@ -691,8 +691,8 @@ __device__ void run_lock_team(const PumpArgs &a, uint32_t uid_in, uint32_t wave,
 
 // A ring with one producer whose two ends are each split over workgroups.
 // The stream's messages are cut into groups of consecutive ones: up to
-// kSplitMost, and up to an eighth of the ring's bytes unless the first is
-// larger.  Every member finds the same groups in the size table (the
+// kSplitMost, and up to P / (teams + 2) of the ring's bytes unless the first is
+// larger, so that every team's group fits beside the others' and one to come.  Every member finds the same groups in the size table (the
 // consumers check the entries against it).  Group g belongs to team g mod A;
 // the B workgroups of a team move a share of its bytes each.  Where a message
 // lies in the ring and in the output follows from the sizes before it, so a
@@ -969,8 +969,10 @@ __device__ void run_split_consumer(const PumpArgs &a, const DevRole &role, uint3
 }
 
 // kSplit: the rings that have one producer are split (no endpoint is a wave
-// or a workgroup of its own but a locking ring's); the forms are two kernels
-// because one with all of them spills registers.
+// or a workgroup of its own but a locking ring's).  The forms are two kernels to
+// keep the split ends' spills (7 VGPRs, 24 B of scratch, 182 SGPRs to lanes) out
+// of the other one, which spills 113 SGPRs to lanes and has no scratch; one
+// kernel with all of them needs 28 B and 200.
 template <bool kSplit>
 __global__ __launch_bounds__(kPumpBlock) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void pump_kernel(PumpArgs a) {

