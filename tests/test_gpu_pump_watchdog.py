@@ -34,7 +34,7 @@ def test_split_ring_outlasts_its_timeout_while_it_moves(env, large):  # noqa: F8
     rc, ch = H.hicr_channel_create(ctx, H.make_channel_cfg(
         H.CH_VAR, H.CH_SPSC, 1, H.CH_DEVICE, slots[2], slots[3], capacity=P, entries=E))
     assert rc == H.OK, H.hicr_last_error(ctx)
-    timeout_ns = 2_000_000
+    timeout_ns = 5_000_000
     _say("pump watchdog", large, n, timeout_ns)
     assert H.hicr_channel_pump(ctx, [(ch, 0, slots[0], slots[1], 0, n)], off, size, 0, ts.data_ptr(),
                                timeout_ns=timeout_ns) == H.OK, H.hicr_last_error(ctx)
